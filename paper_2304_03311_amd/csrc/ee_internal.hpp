@@ -56,6 +56,11 @@ struct alignas(256) JobDev {
   uint32_t reverse;     // EE_FLAG_REVERSE
   uint32_t spin_format; // ee_spin_format
   uint32_t magic_R, shift_R, magic_Ly, shift_Ly;  // unsigned division by R and ly
+  // Byte tables, by neighbour index 0..7, of the top halves of the bulk
+  // thresholds offset by 0x8000 (the unsigned order of 16-bit fields becomes
+  // the signed order): the high bytes in pt[0], pt[1], the low ones in pt[2],
+  // pt[3], as v_perm_b32 selects them.
+  uint32_t pt[4];
   double beta;
   const uint32_t* ramp_thr;
   uint32_t* spins;

@@ -24,481 +24,118 @@
 #include "ee_dd.hpp"
 #include "ee_internal.hpp"
 #include "ee_lanes.hpp"
+#include "ee_rows.hpp"
 
 namespace {
 
-using ee::JobDev;
-using ee::Unit;
-using namespace ee::lanes;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
-__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <typename T>
-__device__ __forceinline__ T* uni_ptr(T* p) {
-  uint64_t v = reinterpret_cast<uint64_t>(p);
-  uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const lds_u32*)(const uint32_t*)p;
 }
 
-// Philox4x32-10 (Salmon et al., SC'11): 10 rounds of two 32x32->64 products;
-// the two xors of each output word are one 3-input bitwise op (table 0x96).
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
-  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
-}
-
-__device__ __forceinline__ void philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                         uint32_t k0, uint32_t k1, uint32_t out[4]) {
-#pragma unroll
-  for (int i = 0; i < 10; ++i) {
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
-    c1 = (uint32_t)p1;
-    c3 = (uint32_t)p0;
-    c0 = n0;
-    c2 = n2;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
-}
-
-// Philox4x32-10 whose output words 0 and 2 come xored with m: those words
-// are the three-input xors of the last round, so m joins its (uniform) key
-// at no cost.
-__device__ __forceinline__ void philox10_x02(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                             uint32_t k0, uint32_t k1, uint32_t m, uint32_t out[4]) {
-#pragma unroll
-  for (int i = 0; i < 10; ++i) {
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, (i == 9) ? (k0 ^ m) : k0);
-    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, (i == 9) ? (k1 ^ m) : k1);
-    c1 = (uint32_t)p1;
-    c3 = (uint32_t)p0;
-    c0 = n0;
-    c2 = n2;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
-}
-
-__device__ __forceinline__ JP load_jp(const JobDev* J) {
-  JP P;
-  P.dim = uni(J->dim);
-  P.n = uni(J->n); P.lt = uni(J->lt); P.ly = uni(J->ly); P.l = uni(J->l); P.N = uni(J->N);
-  P.S = uni(J->S); P.subsets = uni(J->subsets); P.whole = uni(J->whole);
-  P.H = uni(J->H); P.G = uni(J->G); P.R = uni(J->R); P.traj_words = uni(J->traj_words);
-  P.G8 = (P.H + 7) >> 3;
-  P.packed_row_words = (P.H + 31) >> 5;
-  P.key0 = uni(J->key0); P.key1 = uni(J->key1);
-  P.thr0 = uni(J->thr_bulk[0]); P.thr1 = uni(J->thr_bulk[1]); P.thr2 = uni(J->thr_bulk[2]);
-  P.reverse = uni(J->reverse); P.spin_format = uni(J->spin_format);
-  // Top halves of the bulk thresholds thr[a] (a anti-aligned neighbours;
-  // 2^32-1 for a >= dim), offset by 0x8000 so that the unsigned order of
-  // 16-bit fields becomes the signed order, as high and low byte tables
-  // indexed by a through v_perm_b32 (a <= 7).
-  P.pt_hi0 = P.pt_hi1 = P.pt_lo0 = P.pt_lo1 = 0;
-  for (int a = 0; a < 8; ++a) {
-    const uint32_t th = (a == 0) ? P.thr0 : (a == 1) ? P.thr1 : (a == 2 && P.dim == 3) ? P.thr2 : 0xFFFFFFFFu;
-    const uint32_t t16 = (th >> 16) ^ 0x8000u;
-    const uint32_t sh = 8u * (uint32_t)(a & 3);
-    if (a < 4) {
-      P.pt_hi0 |= (t16 >> 8) << sh;
-      P.pt_lo0 |= (t16 & 0xFFu) << sh;
-    } else {
-      P.pt_hi1 |= (t16 >> 8) << sh;
-      P.pt_lo1 |= (t16 & 0xFFu) << sh;
-    }
-  }
-  P.mR = uni(J->magic_R); P.sR = uni(J->shift_R); P.mLy = uni(J->magic_Ly); P.sLy = uni(J->shift_Ly);
-  P.ramp = uni_ptr(J->ramp_thr);
-  P.spins = uni_ptr(J->spins);
-  P.work = uni_ptr(J->work);
-  return P;
-}
-
-// (a ^ b) + c as one v_xad_u32.  Written out because the compiler splits a
-// chain of them into separate xors and three-input adds (six instructions
-// for the four neighbours of a word instead of four).
-__device__ __forceinline__ uint32_t xad_op(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t d;
-  asm("v_xad_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-  return d;
-}
-
-// Ramp position (0..S) of row y when the protocol stands at position pos
-// (0..N): every row follows pos, or (subset protocol) row y moves during
-// steps [y S, (y+1) S).
-__device__ __forceinline__ int row_m(const JP& P, int y, int pos) {
-  if (!P.subsets) return pos;
-  const int m = pos - y * P.S;
-  return m < 0 ? 0 : (m > P.S ? P.S : m);
-}
-
-// Output word o (0..3, possibly not a compile-time constant) of a Philox
-// result, by selects rather than a dynamically indexed register array.
-__device__ __forceinline__ uint32_t pick4(const uint32_t u[4], int o) {
-  const uint32_t lo = (o & 1) ? u[1] : u[0];
-  const uint32_t hi = (o & 1) ? u[3] : u[2];
-  return (o & 2) ? hi : lo;
-}
-
-// Two 16-bit lanes per 32-bit word: saturating signed difference a - b, and
-// unsigned minimum (v_pk_sub_i16 with clamp, v_pk_min_u16).
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t sub_sat_s16x2(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(s16x2, a),
-                                                                    __builtin_bit_cast(s16x2, b)));
-}
-__device__ __forceinline__ uint32_t min_u16x2(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
-                                                                __builtin_bit_cast(u16x2, b)));
-}
-
-// The W consecutive words p[0..W-1] of a lane as one 4W-byte access.  Where
-// W is 2 or 4, p is 4W-byte aligned (w, the row pitch G and every plane and
-// trajectory offset are multiples of W), and the lanes of a wave then cover
-// consecutive LDS banks; W separate dword accesses at a lane stride of W
-// words would conflict W-fold.  W = 3 (rows of three words, one lane per
-// row) reads dwords: an odd lane stride does not conflict.
-// GM: p points into device memory (the HBM-streaming path).  The access is
-// then made through a global-address-space pointer: a flat access, which is
-// what a pointer of unknown space compiles to, also counts against the
-// LDS/scalar wait counter, so every LDS or scalar wait would drain the HBM
-// loads in flight.
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) uint32_t g_u32;
-typedef __attribute__((address_space(1))) u32x2 g_u32x2;
-typedef __attribute__((address_space(1))) u32x4 g_u32x4;
-
-template <bool GM>
-__device__ __forceinline__ uint32_t ld_word(const uint32_t* p) {
-  if constexpr (GM) return *(const g_u32*)p;
-  else return *p;
-}
-
-template <int W, bool GM = false>
-__device__ __forceinline__ void ld_words(const uint32_t* p, uint32_t v[W]) {
-  if constexpr (GM && W == 4) {
-    const u32x4 x = *(const g_u32x4*)p;
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-  } else if constexpr (GM && W == 2) {
-    const u32x2 x = *(const g_u32x2*)p;
-    v[0] = x.x; v[1] = x.y;
-  } else if constexpr (W == 4) {
-    const uint4 x = *reinterpret_cast<const uint4*>(p);
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-  } else if constexpr (W == 2) {
-    const uint2 x = *reinterpret_cast<const uint2*>(p);
-    v[0] = x.x; v[1] = x.y;
-  } else {
-#pragma unroll
-    for (int q = 0; q < W; ++q) v[q] = ld_word<GM>(p + q);
-  }
-}
-template <int W, bool GM = false>
-__device__ __forceinline__ void st_words(uint32_t* p, const uint32_t v[W]) {
-  if constexpr (GM && W == 4) {
-    *(g_u32x4*)p = u32x4{v[0], v[1], v[2], v[3]};
-  } else if constexpr (GM && W == 2) {
-    *(g_u32x2*)p = u32x2{v[0], v[1]};
-  } else if constexpr (GM) {
-#pragma unroll
-    for (int q = 0; q < W; ++q) *(g_u32*)(p + q) = v[q];
-  } else if constexpr (W == 4) {
-    *reinterpret_cast<uint4*>(p) = make_uint4(v[0], v[1], v[2], v[3]);
-  } else if constexpr (W == 2) {
-    *reinterpret_cast<uint2*>(p) = make_uint2(v[0], v[1]);
-  } else {
-#pragma unroll
-    for (int q = 0; q < W; ++q) p[q] = v[q];
-  }
-}
-
-// 16-bit half hi (0 low, 1 high) of a Philox output word.
-__device__ __forceinline__ uint32_t half16(uint32_t word, int hi) { return hi ? (word >> 16) : (word & 0xFFFFu); }
-
-// The Metropolis update of the sites of one row of colour c that a lane
-// owns (words w .. w+W-1 of the row).
-//   Lc, Lo  the row's own colour plane and the other one (LDS or HBM)
-//   thr     LDS table: thr[a] = threshold of a bulk/glued site with a
-//           anti-aligned neighbours (2^32-1 for a >= DIM)
-//   (r, t, y)  the row; pC, pO  word w of the row in Lc and in Lo
-//   tmo, tpo, ymo, ypo  offsets from pO of the same words in rows t-1,
+// The Metropolis update of the sites of one row of colour c that a lane owns
+// (words w .. w+W-1 of the row), parity of the row known only at run time.
+//   aC, aO  locations of word w of the row in its own colour plane and in the
+//           other one
+//   tmo, tpo, ymo, ypo  word offsets from aO of the same words in rows t-1,
 //           t+1, y-1 and y+1 (periodic)
-//   c0, c3  Philox counter words 0 and 3 of the row's first call
-//   pos     protocol position of this sweep; dpos  pos minus the previous
-//           position (+1 forward, -1 reverse, 0 while thermalising)
+//   gmem, ag  where the glued partner row is (CUT; a location that may be
+//           read also for rows away from the cut)
+//   (r, t, y)  the row; c0, c3 Philox counter words 0 and 3 of its first call
 // FULL: lx/2 is a multiple of 4 (no pad bytes, x-neighbours by byte
 // alignment of two words).  W: consecutive words per lane (2 or 4 need
 // FULL and a word count that W divides; 3 needs FULL and rows of exactly
 // three words, so that w = 0 and words 0, 1 share a Philox call while word
-// 2 takes the next one).  PAR: the row's x parity p = (c + t + y) & 1 when
-// the caller knows it at compile time, else -1.  CUT: the code for rows next
-// to the cut (t = 0, 1) is compiled in; without it the row must have t > 1.
-// XG: the glued partner row is at Lo + og_in (a layout other than the
-// colour-plane storage order), with the parity known only at run time.
-// LA (lookahead): the row's Philox outputs (phase 1) come in preU, computed
-// during the previous half-sweep, and this update computes those of the
-// same row in sweep g_next with counter word c3_next into nextU.  They do
-// not depend on spins, so that chain overlaps this row's loads and
-// decisions instead of lengthening the next half-sweep.
-template <int DIM, bool FULL, int W, int PAR, bool CUT, bool XG = false, bool LA = false, bool GM = false>
-__device__ __forceinline__ void row_update(const JP& P, const int w, const int wl, const int wr,
-                                           uint32_t* __restrict__ Lc, const uint32_t* __restrict__ Lo,
-                                           const uint32_t* __restrict__ thr, const int c, const uint32_t g,
-                                           const uint32_t j, const int pos, const int dpos, const bool work,
-                                           int& dI, const int r, const int t, const int y,
-                                           uint32_t* __restrict__ pC, const uint32_t* __restrict__ pO,
-                                           const int tmo, const int tpo, const int ymo, const int ypo,
-                                           const uint32_t c0, const uint32_t c3, const int og_in = 0,
-                                           const uint32_t* gm_in = nullptr, const uint32_t* preU = nullptr,
-                                           uint32_t* nextU = nullptr, const uint32_t g_next = 0,
-                                           const uint32_t c3_next = 0) {
+// 2 takes the next one).  CUT: the code for rows next to the cut (t = 0, 1)
+// is compiled in; without it the row must have t > 1.
+template <int DIM, bool FULL, int W, bool CUT, bool LA, typename M, typename GM>
+__device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M& mem, const uint32_t aC,
+                                           const uint32_t aO, const GM& gmem, const uint32_t ag, const int w,
+                                           const int wl, const int wr, const uint32_t* __restrict__ thr, const int c,
+                                           const uint32_t g, const uint32_t j, const int pos, const int dpos,
+                                           const bool work, int& dI, const int t, const int y, const int tmo,
+                                           const int tpo, const int ymo, const int ypo, const uint32_t c0,
+                                           const uint32_t c3, uint32_t* nextU = nullptr) {
   static_assert(W == 1 || ((W == 2 || W == 3 || W == 4) && FULL), "several words per lane need whole rows");
-  constexpr int NC = (W + 1) / 2;  // Philox calls per row: 8 sites each
   const int G = P.G;
   const int tailsh = 8 * ((P.H - 1) & 3);
   const uint32_t valid = (!FULL && w == G - 1 && tailsh != 24) ? ((1u << (tailsh + 8)) - 1u) : 0xFFFFFFFFu;
   const uint32_t fmask = valid & 0x01010101u;  // bit 0 of every real site's byte
-  const uint32_t rshift = (w == G - 1) ? (uint32_t)tailsh : 24u;
-  const int p = (PAR >= 0) ? PAR : ((c + t + y) & 1);  // x parity of this row's sites
-  uint32_t A[W], B[W], S[W], a[W];
-  ld_words<W, GM>(pO, A);
-  if (LA) {
+  const int p = (c + t + y) & 1;               // x parity of this row's sites
+  const auto at = [&](int words) { return aO + 4u * (uint32_t)words; };
+  uint32_t A[W], B[W], S[1][W], Tm[W], Tp[W], idx[1][W], Sn[1][W];
+  CutRow<W> cr[1];
+  // towards the cut and away from it, by address: the sum is symmetric
+  const int toff0 = (CUT && t == 1) ? tmo : tpo, toff1 = (CUT && t == 1) ? tpo : tmo;
+  ld_words<W>(mem, aO, A);
+  const uint32_t E = ld_word(mem, at((p ? wr : wl) - w));
+  ld_words<W>(mem, aC, S[0]);
+  ld_words<W>(mem, at(toff0), Tp);
+  ld_words<W>(mem, at(toff1), Tm);
+  if constexpr (CUT) ld_words<W>(gmem, ag, cr[0].Tg);
+  uint32_t Ym[W], Yp[W];
+  if constexpr (DIM == 3) {
+    ld_words<W>(mem, at(ymo), Ym);
+    ld_words<W>(mem, at(ypo), Yp);
+  } else {
 #pragma unroll
-    for (int k = 0; k < NC; ++k) philox10_x02(c0 + k, g_next, j, c3_next, P.key0, P.key1, 0x80008000u, nextU + 4 * k);
+    for (int q = 0; q < W; ++q) Ym[q] = Yp[q] = 0;
+  }
+  // LA (lookahead): K is the keys of the next half-sweep; this row's Philox
+  // outputs come in nextU, computed during the previous half-sweep, and the
+  // next ones replace them.  They do not depend on spins, so that chain
+  // overlaps this row's loads and decisions instead of lengthening the next
+  // half-sweep.
+  constexpr int NC = (W + 1) / 2;
+  uint32_t U[NC][4], Un[NC][4];
+  fields_of_row<W>(K, c0, Un);
+#pragma unroll
+  for (int k = 0; k < NC; ++k)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      U[k][e] = LA ? nextU[4 * k + e] : Un[k][e];
+      if (LA) nextU[4 * k + e] = Un[k][e];
+    }
+  if constexpr (CUT) {
+    cr[0].on = t <= 1;
+    cr[0].p = p;
+    cr[0].y = y;
+    cr[0].ramp = cr[0].on && p == (P.l & 1) && ramp_lane<W>(P, w);
+#pragma unroll
+    for (int q = 0; q < W; ++q) cr[0].Tc[q] = Tp[q];
+    uint32_t gm[W];
+    glued_bits<W>(P, cr[0].on && !P.whole, p, w, gm);
+    cut_partner<W>(cr[0], gm, Tp);
   }
   if (FULL) {
-    // the sites' x-1 (p = 0) or x+1 (p = 1) neighbours straddle two words
-    const uint32_t E = ld_word<GM>(pO + ((p ? wr : wl) - w));
-    const uint32_t sh = p ? 1u : 3u;
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-      const uint32_t nxt = (q + 1 < W) ? A[q + 1] : E;
-      const uint32_t prv = (q > 0) ? A[q - 1] : E;
-      B[q] = __builtin_amdgcn_alignbyte(p ? nxt : A[q], p ? A[q] : prv, sh);
-    }
+    x_words<W, -1>(A, E, p, B);
   } else {
-    const uint32_t nb = ld_word<GM>(pO + ((p ? wr : wl) - w));
-    const uint32_t Br = (A[0] >> 8) | ((nb & 0xFFu) << rshift);
-    const uint32_t Bl = (A[0] << 8) | ((w == 0) ? ((nb >> tailsh) & 0xFFu) : (nb >> 24));
+    const uint32_t rshift = (w == G - 1) ? (uint32_t)tailsh : 24u;
+    const uint32_t Br = (A[0] >> 8) | ((E & 0xFFu) << rshift);
+    const uint32_t Bl = (A[0] << 8) | ((w == 0) ? ((E >> tailsh) & 0xFFu) : (E >> 24));
     B[0] = p ? Br : Bl;
   }
-  // t -+ 1 neighbours
-  uint32_t Tm[W], Tp[W];
-  ld_words<W, GM>(pC, S);
-  ld_words<W, GM>(pO + tmo, Tm);
-  ld_words<W, GM>(pO + tpo, Tp);
 #pragma unroll
-  for (int q = 0; q < W; ++q) a[q] = xad_op(A[q], S[q], xad_op(B[q], S[q], xad_op(Tm[q], S[q], Tp[q] ^ S[q])));
-  if (DIM == 3) {
-    uint32_t Ym[W], Yp[W];
-    ld_words<W, GM>(pO + ymo, Ym);
-    ld_words<W, GM>(pO + ypo, Yp);
-#pragma unroll
-    for (int q = 0; q < W; ++q) a[q] = xad_op(Ym[q], S[q], xad_op(Yp[q], S[q], a[q]));
-  }
-  // Rows next to the cut (t = 0, 1; compiled in with CUT): for glued
-  // columns x < l the temporal partner across the cut is in replica r+1
-  // (t = 0) or r-1 (t = 1).
-  // Tgl: the glued partners' words; Tcu: the own-replica partners across
-  // the cut (Tp on t = 0, Tm on t = 1); Tef: the partners counted in a.
-  const bool cutrow = CUT && t <= 1;
-  uint32_t Tgl[W], Tcu[W], Tef[W];
-  // gmq(q): bytes of word q with x < l (precomputed per lane where the
-  // caller knows the parity at compile time)
-  const auto gmq = [&](int q) { return (PAR >= 0) ? gm_in[q] : glued_mask(P.l - p - 8 * (w + q)); };
-  if (cutrow) {
-    const int og = (PAR >= 0 || XG) ? og_in : glued_row(P, r, t, y) * G + w;
-    ld_words<W, GM>(Lo + og, Tgl);
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-      Tcu[q] = (t == 0) ? Tp[q] : Tm[q];
-      Tef[q] = Tcu[q];
-      if (!P.whole) {
-        const uint32_t gm = gmq(q);
-        Tef[q] = (Tgl[q] & gm) | (Tcu[q] & ~gm);
-        a[q] = a[q] - (Tcu[q] ^ S[q]) + (Tef[q] ^ S[q]);
-      }
-    }
-  }
-  // Random numbers: one Philox call serves the 8 sites of this row with the
-  // same h >> 3; site i of word q uses the 16-bit half (i & 1) of output
-  // word ob + 2q + (i >> 1).  The decision u <= U with u = 2^16 v + w is
-  // v < U >> 16 unless v equals U >> 16; only then is w (a phase-2 call)
-  // needed.  Sites 0, 1 of word q take the halves of one output word and
-  // sites 2, 3 those of the next, so both sides are compared two at a time
-  // as 16-bit lanes: d = sat(v' - t) with v' = v ^ 0x8000 and
-  // t = (U >> 16) ^ 0x8000 has the sign of v - (U >> 16), and d = 0 marks
-  // a tie.
-  // Call k serves words 2k and 2k+1 of the lane (W >= 2) or, with W = 1,
-  // the lane's word alone, whose fields start at output word ob.  The
-  // outputs are kept (as v ^ 0x8000 per field) for tied and ramped sites.
-  const int ob = (W == 1) ? 2 * (w & 1) : 0;
-  uint32_t f[W];
-  uint32_t U[NC][4];
-  uint32_t dmk[NC];  // per call: minimum of its d's (a zero half marks a tie)
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    // u[0], u[2] arrive as v ^ 0x8000 per field; u[1], u[3] are xored here
-    uint32_t u[4];
-    if (LA) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) u[e] = preU[4 * k + e];
-    } else {
-      philox10_x02(c0 + k, g, j, c3, P.key0, P.key1, 0x80008000u, u);
-    }
-    u[1] ^= 0x80008000u;
-    u[3] ^= 0x80008000u;
-    dmk[k] = 0xFFFFFFFFu;
-#pragma unroll
-    for (int q = 2 * k; q < 2 * k + 2 && q < W; ++q) {
-      // bulk/glued sites: t of site i from the byte tables, selected by byte i of a
-      const uint32_t th = __builtin_amdgcn_perm(P.pt_hi1, P.pt_hi0, a[q]);
-      const uint32_t tl = __builtin_amdgcn_perm(P.pt_lo1, P.pt_lo0, a[q]);
-      const int o = (ob + 2 * q) & 3;
-      const uint32_t d01 = sub_sat_s16x2(pick4(u, o), __builtin_amdgcn_perm(th, tl, 0x05010400u));
-      const uint32_t d23 = sub_sat_s16x2(pick4(u, o + 1), __builtin_amdgcn_perm(th, tl, 0x07030602u));
-      dmk[k] = min_u16x2(dmk[k], min_u16x2(d01, d23));
-      // byte i <- the high byte of site i's difference: its bit 7 is the flip
-      f[q] = __builtin_amdgcn_perm(d23, d01, 0x07050301u);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) U[k][e] = u[e];
-  }
-  uint32_t dmin = dmk[0];
-#pragma unroll
-  for (int k = 1; k < NC; ++k) dmin = min_u16x2(dmin, dmk[k]);
-  const auto tied = [](uint32_t d) { return ((d & 0xFFFFu) == 0) | ((d >> 16) == 0); };
-  if (__builtin_expect(tied(dmin), 0)) {
-    // rare (2^-16 per site): decide the tied sites on u = 2^16 v + w, with
-    // the phase-2 call of only the calls that have a tie
-#pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      if (!tied(dmk[k])) continue;
-      uint32_t u2[4];
-      philox10(c0 + k, g, j, c3 + (1u << 28), P.key0, P.key1, u2);
-#pragma unroll
-      for (int q = 2 * k; q < 2 * k + 2 && q < W; ++q) {
-        const uint32_t a4 = a[q] << 2;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t th = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(thr) +
-                                                                 ((a4 >> (8 * i)) & 0xFFu));
-          const int o = ((ob + 2 * q) & 3) + (i >> 1);
-          if ((half16(pick4(U[k], o), i & 1) ^ 0x8000u) == (th >> 16)) {
-            const uint32_t acc = half16(pick4(u2, o), i & 1) <= (th & 0xFFFFu);
-            f[q] = (f[q] & ~(0xFFu << (8 * i))) | (acc << (8 * i + 7));
-          }
-        }
-      }
-    }
-  }
-  if (cutrow) {
-    // rows next to the cut: the ramped sites (one column, or with the
-    // whole-region protocol every column x < l), decided after the bulk
-    // and tie decisions, which they replace for their bytes
-    const int ramp_w = P.l >> 3;
-    const int ramp_sh = 8 * ((P.l >> 1) & 3);
-    if (!P.whole && p == (P.l & 1) && (unsigned)(ramp_w - w) < (unsigned)W) {
-      // ramped site x = l of a row next to the cut (one lane per row).
-      // K = s (S a_fix + (S-m) s_intra + m s_inter) in units of beta/S.
-      const int m = row_m(P, y, pos);
-#pragma unroll
-      for (int q = 0; q < W; ++q) {
-        if (w + q != ramp_w) continue;
-        const uint32_t fa = ((a[q] - (Tef[q] ^ S[q])) >> ramp_sh) & 0xFFu;
-        const uint32_t bb = ((Tcu[q] ^ S[q]) >> ramp_sh) & 1u;
-        const uint32_t cc = ((Tgl[q] ^ S[q]) >> ramp_sh) & 1u;
-        const uint32_t Ur = P.ramp[m * (8 * DIM) + fa * 4 + bb * 2 + cc];
-        const int ri = ramp_sh >> 3;
-        const int o = ((ob + 2 * q) & 3) + (ri >> 1);
-        const uint32_t vr = half16(pick4(U[q >> 1], o), ri & 1) ^ 0x8000u;
-        uint32_t acc = vr < (Ur >> 16);
-        if (vr == (Ur >> 16)) {
-          uint32_t u2[4];
-          philox10(c0 + (q >> 1), g, j, c3 + (1u << 28), P.key0, P.key1, u2);
-          acc = half16(pick4(u2, o), ri & 1) <= (Ur & 0xFFFFu);
-        }
-        f[q] = (f[q] & ~(0xFFu << ramp_sh)) | (acc << (ramp_sh + 7));
-        if (work) {
-          // the ramped site of colour 0 sees phi_k: its bonds' weights moved
-          // by (m - m_prev), so the D_k term is (m - m_prev) 2 (b - c)
-          const int dm = m - row_m(P, y, pos - dpos);
-          dI += dm * 2 * ((int)bb - (int)cc);
-        }
-      }
-    }
-    if (P.whole && 8 * w + p < P.l) {
-      // whole-region protocol: every site x < l of a row next to the cut is
-      // ramped and none is glued.  Per site K = s (S a_fix + (S-m) s_intra +
-      // m s_inter) from the ramp table, replacing the bulk decision.
-      const int m = row_m(P, y, pos);
-      const uint32_t* __restrict__ Um = P.ramp + m * (8 * DIM);
-#pragma unroll
-      for (int q = 0; q < W; ++q) {
-        const uint32_t rm = gmq(q);  // bytes with x < l
-        if (rm == 0) continue;
-        const uint32_t bw = Tcu[q] ^ S[q];  // intra partner anti-aligned (bit 0 of each byte)
-        const uint32_t cw = Tgl[q] ^ S[q];  // inter partner anti-aligned
-        const uint32_t fw = a[q] - bw;      // the 2 dim - 1 fixed neighbours
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (!((rm >> (8 * i)) & 1u)) continue;
-          const uint32_t fa = (fw >> (8 * i)) & 0xFFu;
-          const uint32_t bb = (bw >> (8 * i)) & 1u;
-          const uint32_t cc = (cw >> (8 * i)) & 1u;
-          const uint32_t Ur = Um[fa * 4 + bb * 2 + cc];
-          const int o = ((ob + 2 * q) & 3) + (i >> 1);
-          const uint32_t vr = half16(pick4(U[q >> 1], o), i & 1) ^ 0x8000u;
-          uint32_t acc = vr < (Ur >> 16);
-          if (vr == (Ur >> 16)) {
-            uint32_t u2[4];
-            philox10(c0 + (q >> 1), g, j, c3 + (1u << 28), P.key0, P.key1, u2);
-            acc = half16(pick4(u2, o), i & 1) <= (Ur & 0xFFFFu);
-          }
-          f[q] = (f[q] & ~(0xFFu << (8 * i))) | (acc << (8 * i + 7));
-        }
-        if (work) {
-          // colour-0 ramped sites see phi_k; each adds (m - m_prev) 2 (b - c)
-          const int dm = m - row_m(P, y, pos - dpos);
-          const uint32_t sel = rm & 0x01010101u;
-          dI += dm * 2 * (__popc(bw & sel) - __popc(cw & sel));
-        }
-      }
-    }
-  }
-  uint32_t Snew[W];
-#pragma unroll
-  for (int q = 0; q < W; ++q) {
-    // S ^ ((f >> 7) & fmask) in one three-input op (table 0x78 = a ^ (b & c))
-    Snew[q] = __builtin_amdgcn_bitop3_b32(S[q], f[q] >> 7, fmask, 0x78);
-  }
-  st_words<W, GM>(pC, Snew);
+  for (int q = 0; q < W; ++q) idx[0][q] = nbr_index<DIM>(S[0][q], A[q], B[q], Tm[q], Tp[q], Ym[q], Yp[q]);
+  decide_rows<DIM, W, 1, CUT>(P, U, &c0, c3, g, j, w, fmask, thr, S, idx, cr, pos, dpos, work, dI, Sn,
+                              [&](int, uint32_t* Tc, uint32_t* Tg) {
+                                ld_words<W>(mem, at(toff0), Tc);
+                                ld_words<W>(gmem, ag, Tg);
+                              });
+  st_words<W>(mem, aC, Sn[0]);
 }
 
 // One half-sweep of colour c over the lane's rows of one trajectory, in the
 // order of the lane map (any map; the streaming path's and the general
-// on-chip one).  L: the trajectory (two colour planes).  UJ: the
-// trajectory index is uniform per wave.  GM: L is in device memory (the
-// streaming path), accessed through global-address-space pointers.
-template <int DIM, bool FULL, bool UJ, int W, bool GM = false>
-__device__ __forceinline__ void half_sweep(const JP& P, const Lane& ln, uint32_t* __restrict__ L,
-                                           const uint32_t* __restrict__ thr, const int c,
-                                           const uint32_t g, uint32_t j, const int pos, const int dpos,
-                                           const bool work, int& dI) {
-  if (UJ) j = __builtin_amdgcn_readfirstlane(j);
+// on-chip one).  base: location of the trajectory (two colour planes).
+template <int DIM, bool FULL, int W, typename M>
+__device__ __forceinline__ void half_sweep(const JP& P, PhKey& K, const Lane& ln, const M& mem, const uint32_t base,
+                                           const uint32_t* __restrict__ thr, const int c, const uint32_t g,
+                                           const uint32_t j, const int pos, const int dpos, const bool work, int& dI) {
   const int G = P.G;
   const int cw = P.n * P.R * G;  // words per colour plane
-  uint32_t* __restrict__ Lc = L + c * cw;
-  const uint32_t* __restrict__ Lo = L + (c ^ 1) * cw;
+  const uint32_t bC = base + 4u * (uint32_t)(c * cw), bO = base + 4u * (uint32_t)((c ^ 1) * cw);
   const int LyG = P.ly * G;
   const int ltLyG = P.lt * LyG;
   const int ywrap = (P.ly - 1) * G;
@@ -513,11 +150,15 @@ __device__ __forceinline__ void half_sweep(const JP& P, const Lane& ln, uint32_t
     const int ymo = (y == 0) ? ywrap : -G;
     const int ypo = (y == P.ly - 1) ? -ywrap : G;
     const uint32_t c0 = (uint32_t)((t * P.ly + y) * P.G8 + (w >> 1));
+    const uint32_t c3 = ctr3 | ((uint32_t)r << 1);
+    K.x0 = c3 ^ P.key1;
+    const uint32_t off = 4u * (uint32_t)(rowbase + w);
     const auto row = [&](auto cut) {
-      const int tmo = -LyG + ((decltype(cut)::value && t == 0) ? ltLyG : 0);
-      row_update<DIM, FULL, W, -1, decltype(cut)::value, false, false, GM>(
-          P, w, ln.wl, ln.wr, Lc, Lo, thr, c, g, j, pos, dpos, work, dI, r, t, y, Lc + rowbase + w, Lo + rowbase + w,
-          tmo, tpo, ymo, ypo, c0, ctr3 | ((uint32_t)r << 1));
+      constexpr bool CUT = decltype(cut)::value;
+      const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
+      const uint32_t ag = (CUT && t <= 1) ? bO + 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : bO + off;
+      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, bO + off, mem, ag, w, ln.wl, ln.wr, thr, c, g, j, pos,
+                                           dpos, work, dI, t, y, tmo, tpo, ymo, ypo, c0, c3);
     };
     // the code for rows next to the cut runs only where some lane of the
     // wave has such a row
@@ -539,114 +180,200 @@ __device__ __forceinline__ void half_sweep(const JP& P, const Lane& ln, uint32_t
   }
 }
 
-// Rows of colour C of the lane in parity-major order: class 0 (x parity C)
-// and class 1 (x parity C ^ 1) in each step.
-template <int DIM, int W, int C>
-__device__ __forceinline__ void rows_pm(const JP& P, const LanePM& lp, uint32_t* __restrict__ Lc,
-                                        const uint32_t* __restrict__ Lo, const uint32_t* __restrict__ thr,
-                                        const uint32_t g, const uint32_t j, const int pos, const int dpos,
-                                        const bool work, int& dI) {
-  const int LyG = P.ly * P.G;
-  const int ltLyG = P.lt * LyG;
-  const int drw = lp.dt * LyG;
-  const uint32_t dc0 = (uint32_t)(lp.dt * P.ly * P.G8);
-  const uint32_t c3 = lp.c3 | (uint32_t)C;
-  int t = lp.t;
-  // The two row addresses as LDS byte addresses, opaque to the compiler at
-  // each step (the empty asm statement emits nothing): every access is then
-  // one register plus at most one offset, instead of one induction variable
-  // per access plus the LDS base.
-  typedef __attribute__((address_space(3))) uint32_t lds_u32;
-  uint32_t aC = (uint32_t)(uintptr_t)(lds_u32*)(Lc + lp.rw);
-  uint32_t aO = (uint32_t)(uintptr_t)(const lds_u32*)(Lo + lp.rw);
-  const uint32_t da = 4u * (uint32_t)drw;
-  uint32_t c0 = lp.c0;
-  for (; t < P.lt; t += lp.dt, aC += da, aO += da, c0 += dc0) {
-    asm volatile("" : "+v"(aC), "+v"(aO));
-    uint32_t* __restrict__ pC = (uint32_t*)(lds_u32*)(uintptr_t)aC;
-    const uint32_t* __restrict__ pO = (const uint32_t*)(const lds_u32*)(uintptr_t)aO;
-    // class 0.  2D: t is even, so only the wrap below t = 0 can occur.
-    // class 1.  2D: the row t + 1 (odd), whose only possible wrap is above
-    // t + 1 = lt - 1; 3D: the same t.  The wrap below t = 0 belongs to a
-    // row next to the cut, so only the cut variant has it.
-    const int t1 = (DIM == 2) ? t + 1 : t;
-    const int wrap_p = (DIM == 3 && t == P.lt - 1) ? ltLyG : 0;
-    const int wrap_p1 = (DIM == 3) ? wrap_p : ((t1 == P.lt - 1) ? ltLyG : 0);
-    const auto rows = [&](auto cut) {
-      constexpr bool CUT = decltype(cut)::value;
-      const int wrap_m = (CUT && t == 0) ? ltLyG : 0;
-      const int wrap_m1 = (DIM == 3) ? wrap_m : 0;
-      row_update<DIM, true, W, C, CUT>(P, lp.w, lp.wl, lp.wr, Lc, Lo, thr, C, g, j, pos, dpos, work, dI, lp.r0,
-                                       t, lp.y[0], pC, pO, wrap_m - LyG, LyG - wrap_p, lp.ymo[0], lp.ypo[0], c0,
-                                       c3, lp.og[0], lp.gm[C]);
-      row_update<DIM, true, W, C ^ 1, CUT>(P, lp.w, lp.wl, lp.wr, Lc, Lo, thr, C, g, j, pos, dpos, work, dI,
-                                           lp.r0, t1, lp.y[1], pC + lp.d_rw, pO + lp.d_rw, wrap_m1 - LyG,
-                                           LyG - wrap_p1, lp.ymo[1], lp.ypo[1], c0 + lp.d_c0, c3, lp.og[1],
-                                           lp.gm[C ^ 1]);
-    };
-    // Both rows of a step are next to the cut or neither is (t <= 1 implies
-    // t1 <= 1 in 2D, t1 = t in 3D).  The code for rows next to the cut runs
-    // only in steps where some lane of the wave has such a row.
-    if (__builtin_amdgcn_ballot_w64(t <= 1) != 0) rows(std::true_type{});
-    else rows(std::false_type{});
-  }
-}
-
 // half_sweep for lanes that own at most one row (small, latency-bound
 // lattices): the row's Philox outputs U were computed during the previous
-// half-sweep, and this one computes those of the next (sweep g_next,
-// colour c_next) into U.
-template <int DIM, bool FULL, bool UJ, int W>
-__device__ __forceinline__ void half_sweep_la(const JP& P, const Lane& ln, uint32_t* __restrict__ L,
+// half-sweep, and this one computes those of the next (keys Kn) into U.
+template <int DIM, bool FULL, int W>
+__device__ __forceinline__ void half_sweep_la(const JP& P, const Lane& ln, const uint32_t base,
                                               const uint32_t* __restrict__ thr, const int c, const uint32_t g,
-                                              uint32_t j, const int pos, const int dpos, const bool work, int& dI,
-                                              uint32_t* U, const uint32_t g_next, const int c_next) {
-  if (UJ) j = __builtin_amdgcn_readfirstlane(j);
+                                              const uint32_t j, const int pos, const int dpos, const bool work, int& dI,
+                                              uint32_t* U, const PhKey& Kn) {
   if (ln.kstart >= ln.kend) return;
+  const LdsMem mem;
   const int G = P.G;
   const int cw = P.n * P.R * G;  // words per colour plane
-  uint32_t* __restrict__ Lc = L + c * cw;
-  const uint32_t* __restrict__ Lo = L + (c ^ 1) * cw;
+  const uint32_t bC = base + 4u * (uint32_t)(c * cw), bO = base + 4u * (uint32_t)((c ^ 1) * cw);
   const int LyG = P.ly * G;
   const int ltLyG = P.lt * LyG;
   const int ywrap = (P.ly - 1) * G;
   const int w = ln.w, r = ln.r0, t = ln.t0, y = ln.y0;
-  const int rowbase = ln.rowbase0;
   const int tpo = LyG - ((t == P.lt - 1) ? ltLyG : 0);
   const int ymo = (y == 0) ? ywrap : -G;
   const int ypo = (y == P.ly - 1) ? -ywrap : G;
+  const uint32_t off = 4u * (uint32_t)(ln.rowbase0 + w);
   const uint32_t c0 = (uint32_t)((t * P.ly + y) * P.G8 + (w >> 1));
   const uint32_t c3 = (1u << 28) | ((uint32_t)r << 1) | (uint32_t)c;
-  const uint32_t c3n = (1u << 28) | ((uint32_t)r << 1) | (uint32_t)c_next;
-  constexpr int NC = (W + 1) / 2;
-  uint32_t Un[4 * NC];
   const auto row = [&](auto cut) {
-    const int tmo = -LyG + ((decltype(cut)::value && t == 0) ? ltLyG : 0);
-    row_update<DIM, FULL, W, -1, decltype(cut)::value, false, true>(
-        P, w, ln.wl, ln.wr, Lc, Lo, thr, c, g, j, pos, dpos, work, dI, r, t, y, Lc + rowbase + w, Lo + rowbase + w,
-        tmo, tpo, ymo, ypo, c0, c3, 0, nullptr, U, Un, g_next, c3n);
+    constexpr bool CUT = decltype(cut)::value;
+    const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
+    const uint32_t ag = (CUT && t <= 1) ? bO + 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : bO + off;
+    update_row<DIM, FULL, W, CUT, true>(P, Kn, mem, bC + off, bO + off, mem, ag, w, ln.wl, ln.wr, thr, c, g, j, pos,
+                                        dpos, work, dI, t, y, tmo, tpo, ymo, ypo, c0, c3, U);
   };
   if (__builtin_amdgcn_ballot_w64(t <= 1) != 0) row(std::true_type{});
   else row(std::false_type{});
+}
+
+// Word left of (p = 0) or right of (p = 1) the lane's W words of a row that is
+// one lane or an aligned pair of lanes wide (GW = 1, 2): from the lane's or
+// its neighbour's registers.
+template <int W, int PAR, int GW>
+__device__ __forceinline__ uint32_t edge_word(const uint32_t A[W]) {
+  if constexpr (GW == 1) return PAR ? A[0] : A[W - 1];
+  return __builtin_amdgcn_mov_dpp(PAR ? A[0] : A[W - 1], 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]: lane ^ 1
+}
+
+// Rows of colour C of the lane in parity-major order: class 0 (x parity C)
+// and class 1 (x parity C ^ 1) together in each step.  The two rows are
+// neighbours of each other (2D: t and t + 1; 3D: the two y of a pair), so
+// each one's words of the other colour serve both, and their two to four
+// Philox calls run side by side.  The rows lie in LDS class by class
+// (PmPos), which makes every access of a wave consecutive.
+// Bound by VALU issue: 280 instructions for the 32 sites of a step (bulk, 2D;
+// 298 in 3D), of which 148 are the four Philox calls.  Measured against one
+// row at a time with scalar keys and the rows in storage order: 2D 64x64, 64
+// jobs x 1024 trajectories 151 against 177 ms (10.6 against 12.3
+// instructions per attempt), 3D 32^3 x 512 trajectories 21.4 against 25.1 ms.
+// has_cut: some lane of the wave starts with rows next to the cut.  cut_mask:
+// the lane's glued_bits in its rows next to the cut (0 if it has none), of
+// word q and x parity p moved to bit 4 p + q of each byte.  has_ramp: these
+// rows hold the ramped site.
+template <int DIM, int W, int GW, int C>
+__device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp, const PmPos& pp, const uint32_t base,
+                                        const uint32_t* __restrict__ thr, const uint32_t ones, const uint32_t g,
+                                        const uint32_t j, const int pos, const int dpos, const bool work, int& dI,
+                                        const bool has_cut, const uint32_t cut_mask, const bool has_ramp) {
+  const LdsMem mem;
+  const int cw4 = 4 * P.n * P.R * P.G;           // bytes per colour plane
+  const int d4 = 2 * P.R * P.G;                  // class-0 row to class-1 row
+  const int row4 = (DIM == 2) ? 4 * P.G : 2 * P.ly * P.G;  // m to the m of t + 2 (2D), t + 1 (3D)
+  const int wrap4 = d4;
+  const uint32_t da = 4u * (uint32_t)pp.step;
+  const uint32_t dc0 = (uint32_t)(lp.dt * P.ly * P.G8);
+  const uint32_t c3 = lp.c3 | (uint32_t)C;
+  K.x0 = c3 ^ P.key1;
+  const uint32_t bO = base + (uint32_t)(C ? 0 : cw4);
+  const int e0 = 4 * ((C ? lp.wr : lp.wl) - lp.w), e1 = 4 * ((C ? lp.wl : lp.wr) - lp.w);
+  // The two row locations and the counter are opaque to the compiler at each
+  // step (the empty asm statement emits nothing): every access is then one
+  // register plus at most one offset, instead of one induction variable per
+  // access, and nothing of the first step is carried over from sweep to sweep
+  // (in registers that the loop lacks).
+  uint32_t aO = bO + 4u * (uint32_t)pp.rw;
+  uint32_t aC = aO + (uint32_t)(C ? cw4 : -cw4);
+  uint32_t c0 = lp.c0;
+  int t = lp.t;
+  const auto step = [&](auto cut) {
+    constexpr bool CUT = decltype(cut)::value;
+    asm volatile("" : "+v"(aC), "+v"(aO), "+v"(c0));
+    uint32_t A0[W], A1[W], B0[W], B1[W], S[2][W], idx[2][W], Sn[2][W];
+    const uint32_t cc[2] = {c0, c0 + lp.d_c0};
+    uint32_t U[2 * ((W + 1) / 2)][4], E0, E1;
+    CutRow<W> cr[2];
+    const uint32_t aO1 = aO + (uint32_t)d4, aC1 = aC + (uint32_t)d4;
+    // What only the cut needs is made anew from values that the compiler
+    // cannot see through: hoisted out of the sweep loop it would take
+    // registers from every step.
+    int w = lp.w, og0 = pp.og[0], og1 = pp.og[1];
+    if constexpr (CUT) {
+      asm volatile("" : "+v"(w), "+v"(og0), "+v"(og1));
 #pragma unroll
-  for (int e = 0; e < 4 * NC; ++e) U[e] = Un[e];
+      for (int r = 0; r < 2; ++r) {
+        cr[r].on = t <= 1;
+        cr[r].p = C ^ r;
+        cr[r].y = lp.y[r];
+        cr[r].ramp = has_ramp && cr[r].p == (P.l & 1);
+      }
+    }
+    // 2D: rows t (even) and t + 1.  3D: both rows at t; towards the cut
+    // (t + 1 for t = 0, t - 1 for t = 1) and away from it by address.  The
+    // wrap below t = 0 belongs to a row next to the cut, so only the cut
+    // variant has it.
+    const uint32_t up = (uint32_t)(row4 - ((DIM == 3 && t == P.lt - 1) ? wrap4 : 0));
+    const uint32_t dn = (uint32_t)(((CUT && t == 0) ? wrap4 : 0) - row4);
+    const uint32_t tc = (CUT && t == 1) ? dn : up, ta = (CUT && t == 1) ? up : dn;
+    const uint32_t tp = (uint32_t)(row4 - ((DIM == 2 && t + 2 == P.lt) ? wrap4 : 0));
+    // Row 0: its words are loaded, its Philox outputs made while they
+    // arrive, then they are summed; then the same for row 1.  (All loads
+    // first, for both rows, took too many registers: the spills cost more
+    // than the one latency saved.)
+    uint32_t T0[W], T1[W], Y[W];
+    ld_words<W>(mem, aO, A0);
+    ld_words<W>(mem, aO1, A1);
+    ld_words<W>(mem, aC, S[0]);
+    if constexpr (CUT) ld_words<W>(mem, bO + 4u * (uint32_t)og0, cr[0].Tg);
+    if constexpr (DIM == 2) {
+      ld_words<W>(mem, aO1 + dn, T0);  // t - 1
+    } else {
+      ld_words<W>(mem, aO1 + tc, T1);
+      ld_words<W>(mem, aO1 + ta, T0);
+      ld_words<W>(mem, aO1 + 4u * (uint32_t)pp.yo[0], Y);
+    }
+    if constexpr (GW == 0) { E0 = ld_word(mem, aO + (uint32_t)e0); E1 = ld_word(mem, aO1 + (uint32_t)e1); }
+    fields_of_row<W>(K, cc[0], U);
+    if constexpr (GW != 0) { E0 = edge_word<W, C, GW>(A0); E1 = edge_word<W, C ^ 1, GW>(A1); }
+    x_words<W, C>(A0, E0, C, B0);
+    if constexpr (DIM == 2) {
+#pragma unroll
+      for (int q = 0; q < W; ++q) T1[q] = A1[q];
+    }
+    if constexpr (CUT) {
+#pragma unroll
+      for (int q = 0; q < W; ++q) cr[0].Tc[q] = T1[q];
+      uint32_t gm[W];
+#pragma unroll
+      for (int q = 0; q < W; ++q) gm[q] = cut_mask >> (4 * cr[0].p + q);
+      cut_partner<W>(cr[0], gm, T1);
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) idx[0][q] = nbr_index<DIM>(S[0][q], A0[q], B0[q], T0[q], T1[q], A1[q], Y[q]);
+    ld_words<W>(mem, aC1, S[1]);
+    if constexpr (CUT) ld_words<W>(mem, bO + 4u * (uint32_t)og1, cr[1].Tg);
+    if constexpr (DIM == 2) {
+      ld_words<W>(mem, aO + tp, T0);  // t + 2
+    } else {
+      ld_words<W>(mem, aO + tc, T1);
+      ld_words<W>(mem, aO + ta, T0);
+      ld_words<W>(mem, aO + 4u * (uint32_t)pp.yo[1], Y);
+    }
+    fields_of_row<W>(K, cc[1], U + (W + 1) / 2);
+    x_words<W, C ^ 1>(A1, E1, C ^ 1, B1);
+    if constexpr (DIM == 2) {
+#pragma unroll
+      for (int q = 0; q < W; ++q) T1[q] = A0[q];
+    }
+    if constexpr (CUT) {
+#pragma unroll
+      for (int q = 0; q < W; ++q) cr[1].Tc[q] = T1[q];
+      uint32_t gm[W];
+#pragma unroll
+      for (int q = 0; q < W; ++q) gm[q] = cut_mask >> (4 * cr[1].p + q);
+      cut_partner<W>(cr[1], gm, T1);
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) idx[1][q] = nbr_index<DIM>(S[1][q], A1[q], B1[q], T0[q], T1[q], A0[q], Y[q]);
+    decide_rows<DIM, W, 2, CUT>(P, U, cc, c3, g, j, w, ones, thr, S, idx, cr, pos, dpos, work, dI, Sn,
+                                [&](int r, uint32_t* Tc, uint32_t* Tg) {
+                                  ld_words<W>(mem, (r ? aO : aO1) + ((DIM == 3) ? tc : 0u), Tc);
+                                  ld_words<W>(mem, bO + 4u * (uint32_t)(r ? og1 : og0), Tg);
+                                });
+    st_words<W>(mem, aC, Sn[0]);
+    st_words<W>(mem, aC1, Sn[1]);
+    t += lp.dt;
+    aC += da;
+    aO += da;
+    c0 += dc0;
+  };
+  // Rows next to the cut are met in the first step only (t grows); outside
+  // the loop, what that step needs does not weigh on the others.
+  if (has_cut && t < P.lt) step(std::true_type{});
+  while (t < P.lt) step(std::false_type{});
 }
 
-template <int DIM, bool UJ, int W>
-__device__ __forceinline__ void half_sweep_pm(const JP& P, const LanePM& lp, uint32_t* __restrict__ L,
-                                              const uint32_t* __restrict__ thr, const int c,
-                                              const uint32_t g, uint32_t j, const int pos, const int dpos,
-                                              const bool work, int& dI) {
-  if (UJ) j = __builtin_amdgcn_readfirstlane(j);
-  const int cw = P.n * P.R * P.G;
-  uint32_t* __restrict__ Lc = L + c * cw;
-  const uint32_t* __restrict__ Lo = L + (c ^ 1) * cw;
-  if (c == 0) rows_pm<DIM, W, 0>(P, lp, Lc, Lo, thr, g, j, pos, dpos, work, dI);
-  else rows_pm<DIM, W, 1>(P, lp, Lc, Lo, thr, g, j, pos, dpos, work, dI);
-}
-
-// Initial spins (phase 0 of the Philox streams): +1 iff u < 2^31.
-__device__ void init_spins(const JP& P, uint32_t* L, uint32_t j, int lt_, int T) {
+// Initial spins (phase 0 of the Philox streams): +1 iff u < 2^31.  PM: into
+// the class-by-class rows of the parity-major order.
+template <bool PM, typename M>
+__device__ void init_spins(const JP& P, const M& mem, uint32_t base, uint32_t j, int lt_, int T) {
   const int nR = P.n * P.R;
   for (int q = lt_; q < P.traj_words; q += T) {
     const int w = q % P.G;
@@ -661,134 +388,188 @@ __device__ void init_spins(const JP& P, uint32_t* L, uint32_t j, int lt_, int T)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (4 * w + i < P.H) word |= (uint32_t)(u[i] < 0x80000000u) << (8 * i);
-    L[q] = word;
+    const int at = PM ? (rowg - rho + pm_row(P, rho)) * P.G + w : q;
+    st_words<1>(mem, base + 4u * (uint32_t)at, &word);
   }
 }
 
-__device__ void load_spins(const JP& P, uint32_t* L, uint32_t j, int lt_, int T) {
-  if (P.spin_format == EE_SPINS_INT8) {
-    const uint32_t* src = P.spins + (size_t)j * P.traj_words;
-    for (int q = lt_; q < P.traj_words; q += T) L[q] = src[q];
-  } else {
-    const int PW = P.packed_row_words;
-    const uint32_t* src = P.spins + (size_t)j * (2 * P.n * P.R * PW);
-    for (int q = lt_; q < P.traj_words; q += T) {
-      const int w = q % P.G;
-      const int rowg = q / P.G;
+// Row (over colours and replicas) rowg of the storage order in LDS.
+template <bool PM>
+__device__ __forceinline__ int lds_row(const JP& P, int rowg) {
+  if (!PM) return rowg;
+  const int rho = rowg - (int)fdiv((uint32_t)rowg, P.mR, P.sR) * P.R;
+  return rowg - rho + pm_row(P, rho);
+}
+
+template <bool PM>
+__device__ void load_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T) {
+  const LdsMem mem;
+  const bool int8 = P.spin_format == EE_SPINS_INT8;
+  const int PW = P.packed_row_words;
+  const uint32_t* src = P.spins + (size_t)j * (int8 ? P.traj_words : 2 * P.n * P.R * PW);
+  for (int q = lt_; q < P.traj_words; q += T) {
+    const int rowg = q / P.G;
+    const int w = q - rowg * P.G;
+    uint32_t word;
+    if (int8) {
+      word = src[q];
+    } else {
       const uint32_t nib = (src[rowg * PW + (w >> 3)] >> (4 * (w & 7))) & 0xFu;
-      L[q] = (nib * 0x00204081u) & 0x01010101u;  // 4 bits -> 4 bytes
+      word = (nib * 0x00204081u) & 0x01010101u;  // 4 bits -> 4 bytes
     }
+    st_words<1>(mem, base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * P.G + w), &word);
   }
 }
 
-__device__ void store_spins(const JP& P, const uint32_t* L, uint32_t j, int lt_, int T) {
+template <bool PM>
+__device__ void store_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T) {
+  const LdsMem mem;
   if (P.spin_format == EE_SPINS_INT8) {
     uint32_t* dst = P.spins + (size_t)j * P.traj_words;
-    for (int q = lt_; q < P.traj_words; q += T) dst[q] = L[q];
+    for (int q = lt_; q < P.traj_words; q += T) {
+      const int rowg = q / P.G;
+      dst[q] = ld_word(mem, base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * P.G + q - rowg * P.G));
+    }
   } else {
     const int PW = P.packed_row_words;
     const int total = 2 * P.n * P.R * PW;
     uint32_t* dst = P.spins + (size_t)j * total;
     for (int q = lt_; q < total; q += T) {
-      const int wb = q % PW;
       const int rowg = q / PW;
+      const int wb = q - rowg * PW;
+      const uint32_t row = base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * P.G);
       uint32_t packed = 0;
       for (int k = 0; k < 8; ++k) {
         const int w = 8 * wb + k;
-        if (w < P.G) packed |= (((L[rowg * P.G + w] * 0x01020408u) >> 24) & 0xFu) << (4 * k);
+        if (w < P.G) packed |= (((ld_word(mem, row + 4u * (uint32_t)w) * 0x01020408u) >> 24) & 0xFu) << (4 * k);
       }
       dst[q] = packed;
     }
   }
 }
 
-// All sweeps of one work unit: k trajectories of one job, one per LDS slot.
-// PM: the rows in parity-major order (half_sweep_pm), else in the order of
-// the lane map.
-template <int DIM, bool FULL, bool UJ, int W, bool PM>
-__device__ __forceinline__ void run_unit(const JP& P, uint32_t* lds, int* s_dI, uint32_t* s_thr, int j0,
-                                         int cnt, int kslots, uint32_t flags, int n_therm, int g0) {
+// Words (from the end of the trajectory slots) of the workgroup's small
+// tables in dynamic LDS: unit index, per-slot work sums, threshold table.
+constexpr int kTabUnit = 0, kTabWork = 4, kTabThr = 4 + ee::kMaxSlots;
+
+// All sweeps of one work unit: cnt trajectories of one job, one per LDS slot
+// of T lanes.  PM: the rows in parity-major order (rows_pm; GW as in
+// edge_word), else in the order of the lane map.  A function of its own (one call per unit, which
+// lives for milliseconds): its registers are allocated for this variant
+// alone.  Inlined into one kernel, the variants' uniform values shared 100
+// scalar registers and 1250 of them were spilled.
+template <int DIM, bool FULL, int W, bool PM, int GW = 0>
+__device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t tab, int T_, int j0_, int cnt_,
+                                      uint32_t flags_, int n_therm_, int g0_) {
   static_assert(!PM || FULL, "the parity-major order needs rows of whole words");
+  const JP P = load_jp(uni_ptr(J));
+  const int T = uni(T_), j0 = uni(j0_), cnt = uni(cnt_), n_therm = uni(n_therm_);
+  const uint32_t flags = uni(flags_);
+  lds = uni(lds);
+  tab = uni(tab);
+  const LdsMem mem;
+  int* const s_dI = (int*)mem.at<int>(tab + 4u * kTabWork);
+  uint32_t* const s_thr = (uint32_t*)mem.at<uint32_t>(tab + 4u * kTabThr);
   const int tid = threadIdx.x;
-  const int T = blockDim.x / kslots;
   const int slot = tid / T;
   const int lt_ = tid - slot * T;
   const bool active = slot < cnt;
-  uint32_t* L = lds + (size_t)slot * P.traj_words;
-  const uint32_t j = (uint32_t)(j0 + slot);
+  const uint32_t L = lds + 4u * (uint32_t)(slot * P.traj_words);
+  // one trajectory per wave or more: its index is uniform
+  const uint32_t j = ((T & 63) == 0) ? uni((uint32_t)(j0 + slot)) : (uint32_t)(j0 + slot);
   if (tid < ee::kMaxSlots) s_dI[tid] = 0;
-  if (tid < 8) s_thr[tid] = (tid == 0) ? P.thr0 : (tid == 1) ? P.thr1 : (tid == 2 && DIM == 3) ? P.thr2 : 0xFFFFFFFFu;
+  if (tid < 8) s_thr[tid] = thr_entry(P, DIM, tid);
   if (active) {
-    if (flags & ee::kFlagInit) init_spins(P, L, j, lt_, T);
-    else load_spins(P, L, j, lt_, T);
+    if (flags & ee::kFlagInit) init_spins<PM>(P, mem, L, j, lt_, T);
+    else load_spins<PM>(P, L, j, lt_, T);
   }
-  Lane ln;
-  LanePM lp;
-  bool on = active;
-  if constexpr (PM) {
-    lp = make_lane_pm<DIM, W>(P, lt_, T);
-  } else {
-    ln = make_lane(P, lt_, T, W, true);
-    on = active && ln.kstart < ln.kend;
-  }
+  PhKey K;
+  key_unit(K, P);
+  const uint32_t ones = in_vgpr(0x01010101u);
   __syncthreads();
 
   int dI = 0;
-  uint32_t g = (uint32_t)g0;
+  uint32_t g = (uint32_t)uni(g0_);
   const int pos0 = P.reverse ? P.N : 0;
-  const auto half = [&](int c, uint32_t gg, int pos, int dpos, bool work) {
-    if constexpr (PM) half_sweep_pm<DIM, UJ, W>(P, lp, L, s_thr, c, gg, j, pos, dpos, work, dI);
-    else half_sweep<DIM, FULL, UJ, W>(P, ln, L, s_thr, c, gg, j, pos, dpos, work, dI);
-  };
   // n_therm sweeps at the starting position, then (protocol) the N sweeps
   // k = 0 .. N-1 at positions k+1 (forward) or N-1-k (reverse); the work
-  // is taken at the colour-0 half of each protocol sweep.  One call site
-  // of the half-sweep keeps the code to one copy of the row update.
+  // is taken at the colour-0 half of each protocol sweep.
   const bool proto = (flags & ee::kFlagProto) != 0;
   const int n_sweeps = n_therm + (proto ? P.N : 0);
   const int dpos_p = P.reverse ? -1 : 1;
-  // Lane-map order with at most one row per lane (uniform, from the shape:
-  // the row slots of a replica cover its rows): the Philox outputs of each
-  // half-sweep are computed during the one before.
-  bool lookahead = false;
-  if constexpr (!PM) {
-    const int slots = T / (P.G / W);
-    lookahead = n_sweeps > 0 && ((slots >= P.n) ? (slots / P.n >= P.R) : (slots >= P.n * P.R));
-  }
-  if (lookahead) {
-    constexpr int NC = (W + 1) / 2;
-    uint32_t U[4 * NC];
-    if (on) {
-      const uint32_t jj = UJ ? __builtin_amdgcn_readfirstlane(j) : j;
-      const uint32_t c0 = (uint32_t)((ln.t0 * P.ly + ln.y0) * P.G8 + (ln.w >> 1));
-      const uint32_t c3 = (1u << 28) | ((uint32_t)ln.r0 << 1);  // colour 0
+  const auto sweeps = [&](auto half) {
+    for (int s = 0; s < n_sweeps; ++s, ++g) {
+      const int k = s - n_therm;
+      const bool in_proto = k >= 0;
+      const int pos = in_proto ? (P.reverse ? P.N - 1 - k : k + 1) : pos0;
+      half(pos, in_proto ? dpos_p : 0, in_proto);
+    }
+  };
+  if constexpr (PM) {
+    LanePM lp = make_lane_pm<DIM, W>(P, lt_, T);
+    const bool has_cut = __builtin_amdgcn_ballot_w64(lp.t <= 1) != 0;
+    const PmPos pp = make_pm_pos<DIM>(P, lp);
+    uint32_t cut_mask = 0;
 #pragma unroll
-      for (int k = 0; k < NC; ++k) philox10_x02(c0 + k, g, jj, c3, P.key0, P.key1, 0x80008000u, U + 4 * k);
+    for (int p = 0; p < 2; ++p) {
+      uint32_t gm[W];
+      glued_bits<W>(P, lp.t <= 1 && !P.whole, p, lp.w, gm);
+#pragma unroll
+      for (int q = 0; q < W; ++q) cut_mask |= gm[q] << (4 * p + q);
     }
-    for (int s = 0; s < n_sweeps; ++s, ++g) {
-      const int k = s - n_therm;
-      const bool in_proto = k >= 0;
-      const int pos = in_proto ? (P.reverse ? P.N - 1 - k : k + 1) : pos0;
-      const int dpos = in_proto ? dpos_p : 0;
-#pragma unroll 1
-      for (int c = 0; c < 2; ++c) {
-        if (on)
-          half_sweep_la<DIM, FULL, UJ, W>(P, ln, L, s_thr, c, g, j, pos, dpos, in_proto && c == 0, dI, U,
-                                          c == 0 ? g : g + 1, c ^ 1);
-        __syncthreads();
-      }
-    }
+    const bool has_ramp = lp.t <= 1 && ramp_lane<W>(P, lp.w);
+    if (!active) lp.t = P.lt;  // no rows
+    sweeps([&](int pos, int dpos, bool in_proto) {
+      key_sweep(K, P, g, j);
+      rows_pm<DIM, W, GW, 0>(P, K, lp, pp, L, s_thr, ones, g, j, pos, dpos, in_proto, dI, has_cut, cut_mask, has_ramp);
+      __syncthreads();
+      rows_pm<DIM, W, GW, 1>(P, K, lp, pp, L, s_thr, ones, g, j, pos, dpos, false, dI, has_cut, cut_mask, has_ramp);
+      __syncthreads();
+    });
   } else {
-    for (int s = 0; s < n_sweeps; ++s, ++g) {
-      const int k = s - n_therm;
-      const bool in_proto = k >= 0;
-      const int pos = in_proto ? (P.reverse ? P.N - 1 - k : k + 1) : pos0;
-      const int dpos = in_proto ? dpos_p : 0;
-#pragma unroll 1
-      for (int c = 0; c < 2; ++c) {
-        if (on) half(c, g, pos, dpos, in_proto && c == 0);
-        __syncthreads();
+    const Lane ln = make_lane(P, lt_, T, W, true);
+    const bool on = active && ln.kstart < ln.kend;
+    // Lane-map order with at most one row per lane (uniform, from the shape:
+    // the row slots of a replica cover its rows): the Philox outputs of each
+    // half-sweep are computed during the one before.
+    const int slots = T / (P.G / W);
+    const bool lookahead = n_sweeps > 0 && ((slots >= P.n) ? (slots / P.n >= P.R) : (slots >= P.n * P.R));
+    if (lookahead) {
+      constexpr int NC = (W + 1) / 2;
+      uint32_t U[4 * NC];
+      // K runs one half-sweep ahead
+      K.x0 = ((1u << 28) | ((uint32_t)ln.r0 << 1)) ^ P.key1;  // colour 0
+      key_sweep(K, P, g, j);
+      if (on) {
+        uint32_t c0[NC], u[NC][4];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) c0[k] = (uint32_t)((ln.t0 * P.ly + ln.y0) * P.G8 + (ln.w >> 1)) + k;
+        philox_rows<NC>(K, c0, u);
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) U[4 * k + e] = u[k][e];
       }
+      sweeps([&](int pos, int dpos, bool in_proto) {
+#pragma unroll 1
+        for (int c = 0; c < 2; ++c) {
+          K.x0 ^= 1u;
+          if (c == 1) key_sweep(K, P, g + 1, j);
+          if (on)
+            half_sweep_la<DIM, FULL, W>(P, ln, L, s_thr, c, g, j, pos, dpos, in_proto && c == 0, dI, U, K);
+          __syncthreads();
+        }
+      });
+    } else {
+      sweeps([&](int pos, int dpos, bool in_proto) {
+        key_sweep(K, P, g, j);
+#pragma unroll 1
+        for (int c = 0; c < 2; ++c) {
+          if (on)
+            half_sweep<DIM, FULL, W>(P, K, ln, mem, L, s_thr, c, g, j, pos, dpos, in_proto && c == 0, dI);
+          __syncthreads();
+        }
+      });
     }
   }
   if (proto) {
@@ -796,78 +577,69 @@ __device__ __forceinline__ void run_unit(const JP& P, uint32_t* lds, int* s_dI, 
     __syncthreads();
     if (active && lt_ == 0) P.work[j] = (int64_t)s_dI[slot];
   }
-  if (active) store_spins(P, L, j, lt_, T);
+  if (active) store_spins<PM>(P, L, j, lt_, T);
   __syncthreads();
 }
 
-template <int DIM, bool UJ, int W>
-__device__ __forceinline__ void run_unit_full(const JP& P, uint32_t* lds, int* s_dI, uint32_t* s_thr, int j0,
-                                              int cnt, int kslots, uint32_t flags, int n_therm, int g0) {
-  if (use_pm(P, blockDim.x / kslots, W))
-    run_unit<DIM, true, UJ, W, true>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-  else
-    run_unit<DIM, true, UJ, W, false>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-}
-
+// The variant of a work unit: the dimension, the words per lane, the row
+// order (all uniform over the workgroup).
 template <int DIM>
-__device__ __forceinline__ void run_unit_dispatch(const JP& P, uint32_t* lds, int* s_dI, uint32_t* s_thr,
-                                                  int j0, int cnt, int kslots, uint32_t flags, int n_therm,
-                                                  int g0) {
+__device__ __forceinline__ void run_unit_dispatch(const JobDev* J, uint32_t lds, uint32_t tab, int j0, int cnt,
+                                                  int kslots, uint32_t flags, int n_therm, int g0) {
+  JP P;
+  P.dim = DIM;
+  P.n = uni(J->n); P.ly = uni(J->ly); P.H = uni(J->H); P.G = uni(J->G); P.R = uni(J->R);
   const int T = blockDim.x / kslots;
-  const bool full = (P.H & 3) == 0;
-  const bool uj = (T & 63) == 0;
-  switch (words_per_lane(P, T)) {
-    case 4:
-      if (uj) run_unit_full<DIM, true, 4>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      else run_unit_full<DIM, false, 4>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      return;
-    case 3:
-      if (uj) run_unit_full<DIM, true, 3>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      else run_unit_full<DIM, false, 3>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      return;
-    case 2:
-      if (uj) run_unit_full<DIM, true, 2>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      else run_unit_full<DIM, false, 2>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      return;
-    default:
-      if (full && uj) run_unit_full<DIM, true, 1>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      else if (full) run_unit_full<DIM, false, 1>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-      else run_unit<DIM, false, false, 1, false>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
+  const int W = words_per_lane(P, T);
+  const bool pm = (P.H & 3) == 0 && use_pm(P, T, W);
+  // lanes per row, where the row's edge words come from registers (a pair of
+  // lanes only if the slot's lanes start at an even lane)
+  const int gw = P.G / W;
+  const bool one = gw == 1, two = gw == 2 && (T & 1) == 0;
+#define EE_RUN(...) return run_unit<__VA_ARGS__>(J, lds, tab, T, j0, cnt, flags, n_therm, g0)
+  if (W == 4) {
+    if (pm && one) EE_RUN(DIM, true, 4, true, 1);
+    if (pm && two) EE_RUN(DIM, true, 4, true, 2);
+    if (pm) EE_RUN(DIM, true, 4, true);
+    EE_RUN(DIM, true, 4, false);
   }
+  if (W == 3) {
+    if (pm) EE_RUN(DIM, true, 3, true, 1);
+    EE_RUN(DIM, true, 3, false);
+  }
+  if (W == 2) {
+    if (pm && one) EE_RUN(DIM, true, 2, true, 1);
+    if (pm) EE_RUN(DIM, true, 2, true);
+    EE_RUN(DIM, true, 2, false);
+  }
+  if (pm) EE_RUN(DIM, true, 1, true);
+  if ((P.H & 3) == 0) EE_RUN(DIM, true, 1, false);
+  EE_RUN(DIM, false, 1, false);
+#undef EE_RUN
 }
 
 // Per-job mode (units == nullptr): workgroup b runs trajectories
 // [b*single_k, b*single_k + single_k) of single_job.  Batch mode: persistent
 // workgroups draw units from the queue until it is empty.  The dimension of
 // each unit's job selects the 2D or 3D sweep (uniform per workgroup).
-// tail: word offset, in the dynamic LDS, of the workgroup's small tables
-// (unit index, per-slot work sums, threshold table), which follow the
-// trajectory slots.  The kernel has no static LDS, so the slots start at
-// LDS address 0 and the row addresses need no base added.
-__device__ __forceinline__ void sweep_body(const JobDev* single_job, int single_k, const Unit* units, int n_units,
-                                           int* queue, const JobDev* const* jobtab, uint32_t flags, int n_therm,
-                                           int g0, int tail) {
+// tail: word offset, in the dynamic LDS, of the workgroup's small tables,
+// which follow the trajectory slots.  The kernel has no static LDS.  4 waves
+// per SIMD (128 VGPRs) and up to four words per lane, so that the per-row
+// address and loop work is spread over 16 sites.
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+sweep_kernel(const JobDev* single_job, int single_k, const Unit* units, int n_units, int* queue,
+             const JobDev* const* jobtab, uint32_t flags, int n_therm, int g0, int tail) {
   extern __shared__ __align__(16) uint32_t lds_raw[];
-  // The LDS base as an opaque scalar register value rather than the
-  // (link-time) address of the array: the compiler then folds it into the
-  // row address induction variables instead of adding it at every access.
-  // The empty asm statement only hides the value's origin; it emits nothing.
-  typedef __attribute__((address_space(3))) uint32_t lds_u32;
-  uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_u32*)lds_raw;
-  asm volatile("" : "+s"(lds_addr));
-  uint32_t* const lds = (uint32_t*)(lds_u32*)(uintptr_t)lds_addr;
-  int* const s_tab = reinterpret_cast<int*>(lds + tail);
-  int& s_unit = s_tab[0];
-  int* const s_dI = s_tab + 4;
-  uint32_t* const s_thr = reinterpret_cast<uint32_t*>(s_dI + ee::kMaxSlots);
-  const int tid = threadIdx.x;
+  const uint32_t lds = lds_address(lds_raw);
+  const uint32_t tab = lds + 4u * (uint32_t)tail;
+  int* const s_unit = reinterpret_cast<int*>(lds_raw + tail + kTabUnit);
   for (int iter = 0;; ++iter) {
     const JobDev* J;
     int j0, cnt, kslots;
     if (units != nullptr) {
-      if (tid == 0) s_unit = atomicAdd(queue, 1);
+      if (threadIdx.x == 0) *s_unit = atomicAdd(queue, 1);
       __syncthreads();
-      const int u = s_unit;
+      const int u = uni(*s_unit);
       if (u >= n_units) break;
       const Unit U = units[u];
       J = uni_ptr(jobtab[uni(U.job)]);
@@ -881,21 +653,9 @@ __device__ __forceinline__ void sweep_body(const JobDev* single_job, int single_
       j0 = blockIdx.x * kslots;
       cnt = min(kslots, J->n_traj - j0);
     }
-    const JP P = load_jp(J);
-    if (uni(J->dim) == 3)
-      run_unit_dispatch<3>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
-    else
-      run_unit_dispatch<2>(P, lds, s_dI, s_thr, j0, cnt, kslots, flags, n_therm, g0);
+    if (uni(J->dim) == 3) run_unit_dispatch<3>(J, lds, tab, j0, cnt, kslots, flags, n_therm, g0);
+    else run_unit_dispatch<2>(J, lds, tab, j0, cnt, kslots, flags, n_therm, g0);
   }
-}
-
-// The sweep kernel: up to 4 waves per SIMD (128 VGPRs) and up to four words
-// per lane, so that the per-row address and loop work is spread over 16
-// sites.
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
-sweep_kernel(const JobDev* single_job, int single_k, const Unit* units, int n_units, int* queue,
-             const JobDev* const* jobtab, uint32_t flags, int n_therm, int g0, int tail) {
-  sweep_body(single_job, single_k, units, n_units, queue, jobtab, flags, n_therm, g0, tail);
 }
 
 // ---------------------------------------------------------------------------
@@ -930,11 +690,14 @@ __device__ __forceinline__ void stream_half(const JP& P, uint32_t* s_thr, int la
   xcd_block(bx, (int)gridDim.x, jj, b);
   const int lt_ = b * blockDim.x + threadIdx.x;
   const uint32_t j = (uint32_t)jj;
-  uint32_t* L = P.spins + (size_t)j * P.traj_words;
+  const HbmMem mem{P.spins + (size_t)j * P.traj_words};
   int dI = 0;
+  PhKey K;
+  key_unit(K, P);
+  key_sweep(K, P, g, j);
   const Lane ln = make_lane(P, lt_ < lanes ? lt_ : 0, lanes, W, false);
   if (lt_ < lanes && ln.kstart < ln.kend)
-    half_sweep<DIM, FULL, true, W, true>(P, ln, L, s_thr, c, g, j, pos, dpos, work, dI);
+    half_sweep<DIM, FULL, W>(P, K, ln, mem, 0u, s_thr, c, g, j, pos, dpos, work, dI);
   if (dI != 0) atomicAdd(reinterpret_cast<unsigned long long*>(&P.work[j]), (unsigned long long)(long long)dI);
 }
 
@@ -946,8 +709,7 @@ __device__ __forceinline__ void stream_body(const JobDev* J, int lanes, int c, u
   const JP P = load_jp(J);
   const int dim = uni(J->dim);
   if (threadIdx.x < 8)
-    s_thr[threadIdx.x] = (threadIdx.x == 0) ? P.thr0 : (threadIdx.x == 1) ? P.thr1
-                       : (threadIdx.x == 2 && dim == 3) ? P.thr2 : 0xFFFFFFFFu;
+    s_thr[threadIdx.x] = thr_entry(P, dim, threadIdx.x);
   __syncthreads();
   const bool full = (P.H & 3) == 0;
   const bool w = work != 0;
@@ -1160,14 +922,18 @@ __device__ __forceinline__ RowDesc row_desc(int it, int GW, int W) {
 // thread's first row (the same in every plane).  Rows next to the cut
 // (t <= 1) come here with c = 0 only.
 template <int DIM, bool FULL, int W>
-__device__ __forceinline__ void march_colour(const JP& P, uint32_t* win, uint32_t* traj, int PW, int sm, int s0,
+__device__ __forceinline__ void march_colour(const JP& P, PhKey& K, uint32_t* win, uint32_t* traj, int PW, int sm, int s0,
                                              int sp, int c, int r, int t, const uint32_t* thr, uint32_t g,
                                              uint32_t j, int pos, int dpos, bool work, int& dI, const RowDesc& d0) {
   const int G = P.G, GW = G / W, ly = P.ly;
-  uint32_t* own = win + s0 * PW + c * ly * G;
-  const uint32_t* oth = win + s0 * PW + (c ^ 1) * ly * G;
+  const LdsMem mem;
+  const HbmMem hbm{traj};
+  const uint32_t ring = lds_address(win);
+  const uint32_t own = ring + 4u * (uint32_t)(s0 * PW + c * ly * G);
+  const uint32_t oth = ring + 4u * (uint32_t)(s0 * PW + (c ^ 1) * ly * G);
   const int tmo = (sm - s0) * PW, tpo = (sp - s0) * PW;
   const uint32_t c3 = (1u << 28) | ((uint32_t)r << 1) | (uint32_t)c;
+  K.x0 = c3 ^ P.key1;
   const auto rows = [&](auto cut) {
     constexpr bool CUT = decltype(cut)::value;
     // glued partners: colour 1 of replica r+1 in plane 1 (t = 0) or of
@@ -1180,9 +946,10 @@ __device__ __forceinline__ void march_colour(const JP& P, uint32_t* win, uint32_
       const int wl = (w == 0) ? G - 1 : w - 1, wr = (w + W == G) ? 0 : w + W;
       const int ymo = (y == 0) ? (ly - 1) * G : -G, ypo = (y == ly - 1) ? -(ly - 1) * G : G;
       const uint32_t c0 = (uint32_t)((t * ly + y) * P.G8 + (w >> 1));
-      row_update<DIM, FULL, W, -1, CUT, true>(P, w, wl, wr, own, traj, thr, c, g, j, pos, dpos, work, dI, r, t, y,
-                                              own + y * G + w, oth + y * G + w, tmo, tpo, ymo, ypo, c0, c3,
-                                              CUT ? ogl + y * G + w : 0);
+      const uint32_t off = 4u * (uint32_t)(y * G + w);
+      update_row<DIM, FULL, W, CUT, false>(P, K, mem, own + off, oth + off, hbm, CUT ? 4u * (uint32_t)ogl + off : 0u,
+                                           w, wl, wr, thr, c, g, j, pos, dpos, work, dI, t, y, tmo, tpo, ymo, ypo,
+                                           c0, c3);
       it += blockDim.x;
       if (it < ly * GW) d = row_desc(it, GW, W);
     }
@@ -1208,6 +975,9 @@ __device__ __forceinline__ void march_segment(const JP& P, uint32_t* win, const 
   const Xfer X = make_xfer(P, r);
   const RowDesc d0 = row_desc(threadIdx.x, P.G / W, W);
   int dI = 0;
+  PhKey K;
+  key_unit(K, P);
+  key_sweep(K, P, g, j);
   v4u v0 = {}, v1 = {}, v2 = {}, v3 = {};
   // planes t0-1 .. t0+1; a neighbouring segment's boundary plane
   // contributes only its colour 1
@@ -1225,14 +995,14 @@ __device__ __forceinline__ void march_segment(const JP& P, uint32_t* win, const 
     const bool fetch = p + 2 <= t1;
     const int c_lo = (p + 2 == t1) ? 1 : 0;
     if (fetch) xfer_fetch(X, P, traj, win + slot(p + 2) * PW, phys(p + 2), c_lo, v0, v1, v2, v3);
-    march_colour<DIM, FULL, W>(P, win, traj, PW, slot(p - 1), slot(p), slot(p + 1), 0, r, phys(p), thr, g, j, pos,
+    march_colour<DIM, FULL, W>(P, K, win, traj, PW, slot(p - 1), slot(p), slot(p + 1), 0, r, phys(p), thr, g, j, pos,
                                dpos, work, dI, d0);
     __syncthreads();
     // plane p-2 is final (colour 1 of the segment's first plane waits for
     // the fix-up pass)
     if (p - 2 >= t0) xfer_store(X, P, traj, win + slot(p - 2) * PW, phys(p - 2), (p - 2 > t0) ? 2 : 1);
     if (p - 1 >= t0 + 1)
-      march_colour<DIM, FULL, W>(P, win, traj, PW, slot(p - 2), slot(p - 1), slot(p), 1, r, phys(p - 1), thr, g, j,
+      march_colour<DIM, FULL, W>(P, K, win, traj, PW, slot(p - 2), slot(p - 1), slot(p), 1, r, phys(p - 1), thr, g, j,
                                  pos, dpos, false, dI, d0);
     if (fetch) xfer_put(X, win + slot(p + 2) * PW, c_lo, v0, v1, v2, v3);
     __syncthreads();
@@ -1256,8 +1026,11 @@ __device__ __forceinline__ void fixup_plane(const JP& P, const uint32_t* thr, in
   const uint32_t j = (uint32_t)jj;
   uint32_t* traj = P.spins + (size_t)j * P.traj_words;
   const int G = P.G, GW = G / W, ly = P.ly, R = P.R;
-  uint32_t* Lc = traj + P.n * R * G;  // colour 1
-  const uint32_t* Lo = traj;          // colour 0
+  const HbmMem mem{traj};
+  PhKey K;
+  key_unit(K, P);
+  key_sweep(K, P, g, j);
+  const uint32_t bC = 4u * (uint32_t)(P.n * R * G);  // colour 1; colour 0 is at 0
   const int LyG = ly * G, ltLyG = P.lt * LyG;
   const int tpo = LyG - ((t == P.lt - 1) ? ltLyG : 0);
   const int tmo = -LyG + ((t == 0) ? ltLyG : 0);
@@ -1272,8 +1045,11 @@ __device__ __forceinline__ void fixup_plane(const JP& P, const uint32_t* thr, in
       const int rowbase = (r * R + t * ly + y) * G;
       const uint32_t c0 = (uint32_t)((t * ly + y) * P.G8 + (w >> 1));
       const uint32_t c3 = (1u << 28) | ((uint32_t)r << 1) | 1u;
-      row_update<DIM, FULL, W, -1, CUT>(P, w, wl, wr, Lc, Lo, thr, 1, g, j, pos, dpos, false, dI, r, t, y,
-                                        Lc + rowbase + w, Lo + rowbase + w, tmo, tpo, ymo, ypo, c0, c3);
+      K.x0 = c3 ^ P.key1;
+      const uint32_t off = 4u * (uint32_t)(rowbase + w);
+      const uint32_t ag = CUT ? 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : off;
+      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, off, mem, ag, w, wl, wr, thr, 1, g, j, pos, dpos,
+                                           false, dI, t, y, tmo, tpo, ymo, ypo, c0, c3);
     }
   };
   if (t <= 1) rows(std::true_type{});
@@ -1290,8 +1066,7 @@ __device__ __forceinline__ void march_body(const JobDev* J, int nseg, uint32_t g
   const int PW = 2 * P.ly * P.G;
   uint32_t* thr = MAIN ? march_lds + kMarchSlots * PW : march_lds;  // after the ring (main pass) or alone (fix-up)
   if (threadIdx.x < 8)
-    thr[threadIdx.x] = (threadIdx.x == 0) ? P.thr0 : (threadIdx.x == 1) ? P.thr1
-                     : (threadIdx.x == 2 && dim == 3) ? P.thr2 : 0xFFFFFFFFu;
+    thr[threadIdx.x] = thr_entry(P, dim, threadIdx.x);
   __syncthreads();
   const bool full = (P.H & 3) == 0;
   const bool w = work != 0;
@@ -1345,7 +1120,7 @@ __global__ void __launch_bounds__(256) stream_init_kernel(const JobDev* J, int l
   const JP P = load_jp(J);
   const uint32_t j = blockIdx.y;
   const int lt_ = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lt_ < lanes) init_spins(P, P.spins + (size_t)j * P.traj_words, j, lt_, lanes);
+  if (lt_ < lanes) init_spins<false>(P, HbmMem{P.spins + (size_t)j * P.traj_words}, 0u, j, lt_, lanes);
 }
 
 __global__ void zero_work_kernel(const JobDev* J) {

@@ -201,6 +201,56 @@ EE_HDI LanePM make_lane_pm(const JP& P, int lt_, int T) {
 }
 
 
+// Row positions in LDS in parity-major order.  Lanes with consecutive m read
+// rows of one class at a time; with the rows in storage order those are two
+// rows apart, and 16-byte accesses at such a stride meet every LDS bank
+// twice.  So the rows of a (colour, replica) plane are kept class by class:
+// row (t, y) of class q = (t + y) & 1 at position q R/2 + m, with m = t / 2
+// in 2D and t ly/2 + y/2 in 3D (the order of the lanes' walk).  Consecutive
+// lanes then read consecutive words.  Every neighbour of a class-q row is of
+// class q ^ 1:
+//   2D: t -+ 1 at m - 1 and m (q = 0) or m and m + 1 (q = 1), m mod lt/2;
+//   3D: t -+ 1 at m -+ ly/2; the other row of the y pair at m, the y
+//       neighbour outside the pair at m -+ 1 (y even: -, odd: +; periodic in
+//       y).
+EE_HDI int pm_row(const JP& P, int rho) {
+  const int half = P.R >> 1;
+  if (P.dim == 2) return (rho & 1) * half + (rho >> 1);
+  const int t = (int)fdiv((uint32_t)rho, P.mLy, P.sLy), y = rho - t * P.ly;
+  return ((t + y) & 1) * half + t * (P.ly >> 1) + (y >> 1);
+}
+
+// Word offsets of a lane's rows in that layout: its first class-0 row (the
+// class-1 row of the pair is R/2 rows further on), the step between its
+// pairs, the y neighbour outside the pair of the class-q row relative to the
+// class-(q^1) row of the pair, and the glued partners' rows of its first step
+// (0 where that step is not next to the cut).
+struct PmPos {
+  int rw, step, yo[2], og[2];
+};
+
+template <int DIM>
+EE_HDI PmPos make_pm_pos(const JP& P, const LanePM& lp) {
+  const int half = P.R >> 1, hy = P.ly >> 1;
+  const bool in = lp.r0 < P.n;  // a slot past the last replica has no rows
+  const int m = !in ? 0 : (DIM == 2) ? (lp.t >> 1) : lp.t * hy + (lp.y[0] >> 1);
+  PmPos X;
+  X.rw = ((in ? lp.r0 : 0) * P.R + m) * P.G + lp.w;
+  X.step = ((DIM == 2) ? (lp.dt >> 1) : lp.dt * hy) * P.G;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int yh = lp.y[q] >> 1;
+    X.yo[q] = (DIM == 2) ? 0 : ((lp.y[q] & 1) ? ((yh == hy - 1) ? 1 - hy : 1) : ((yh == 0) ? hy - 1 : -1)) * P.G;
+    X.og[q] = 0;
+    if (in && lp.t <= 1) {
+      const int t = (DIM == 2) ? lp.t + q : lp.t;
+      const int rgl = (t == 0) ? ((lp.r0 + 1 == P.n) ? 0 : lp.r0 + 1) : ((lp.r0 == 0) ? P.n - 1 : lp.r0 - 1);
+      X.og[q] = (rgl * P.R + pm_row(P, (1 - t) * P.ly + lp.y[q])) * P.G + lp.w;
+    }
+  }
+  return X;
+}
+
 // Words per lane for a job and slot size of T lanes.  The widest W <= 4
 // that divides the row's words and still gives every row a lane group
 // (rows of exactly three words take W = 3) needs the fewest passes of the

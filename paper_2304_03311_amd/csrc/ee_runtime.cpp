@@ -705,6 +705,14 @@ ee_status ee_job_create(const ee_job_desc* desc, void* dev_arena, size_t arena_b
   D.subsets = subsets ? 1 : 0;
   D.whole = (desc->flags & EE_FLAG_WHOLE) ? 1 : 0;
   for (int a = 0; a < dim; ++a) D.thr_bulk[a] = threshold(desc->beta, (int64_t)S * (2 * dim - 2 * a), S);
+  // by neighbour index: in 2D the index of a site with a anti-aligned
+  // neighbours is a or 7 - a (by its spin), in 3D it is a
+  for (int i = 0; i < 8; ++i) {
+    const int a = (dim == 2 && i >= 4) ? 7 - i : i;
+    const uint32_t t16 = ((a < dim ? D.thr_bulk[a] : 0xFFFFFFFFu) >> 16) ^ 0x8000u;
+    D.pt[i >> 2] |= (t16 >> 8) << (8 * (i & 3));
+    D.pt[2 + (i >> 2)] |= (t16 & 0xFFu) << (8 * (i & 3));
+  }
   D.reverse = (desc->flags & EE_FLAG_REVERSE) ? 1u : 0u;
   D.spin_format = (uint32_t)desc->spin_format;
   ee::Magic mr = ee::make_magic((uint32_t)j->L.R), my = ee::make_magic((uint32_t)desc->ly);
