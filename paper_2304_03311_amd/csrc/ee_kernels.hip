@@ -454,13 +454,13 @@ constexpr int kTabUnit = 0, kTabWork = 4, kTabThr = 4 + ee::kMaxSlots;
 
 // All sweeps of one work unit: cnt trajectories of one job, one per LDS slot
 // of T lanes.  PM: the rows in parity-major order (rows_pm; GW as in
-// edge_word), else in the order of the lane map.  A function of its own (one call per unit, which
+// edge_word) over pm of the lanes, else in the order of the lane map.  A function of its own (one call per unit, which
 // lives for milliseconds): its registers are allocated for this variant
 // alone.  Inlined into one kernel, the variants' uniform values shared 100
 // scalar registers and 1250 of them were spilled.
 template <int DIM, bool FULL, int W, bool PM, int GW = 0>
-__device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t tab, int T_, int j0_, int cnt_,
-                                      uint32_t flags_, int n_therm_, int g0_) {
+__device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t tab, int T_, int pm_, int j0_,
+                                      int cnt_, uint32_t flags_, int n_therm_, int g0_) {
   static_assert(!PM || FULL, "the parity-major order needs rows of whole words");
   const JP P = load_jp(uni_ptr(J));
   const int T = uni(T_), j0 = uni(j0_), cnt = uni(cnt_), n_therm = uni(n_therm_);
@@ -506,7 +506,7 @@ __device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t ta
     }
   };
   if constexpr (PM) {
-    LanePM lp = make_lane_pm<DIM, W>(P, lt_, T);
+    LanePM lp = make_lane_pm<DIM, W>(P, lt_, uni(pm_));
     const bool has_cut = __builtin_amdgcn_ballot_w64(lp.t <= 1) != 0;
     const PmPos pp = make_pm_pos<DIM>(P, lp);
     uint32_t cut_mask = 0;
@@ -591,12 +591,12 @@ __device__ __forceinline__ void run_unit_dispatch(const JobDev* J, uint32_t lds,
   P.n = uni(J->n); P.ly = uni(J->ly); P.H = uni(J->H); P.G = uni(J->G); P.R = uni(J->R);
   const int T = blockDim.x / kslots;
   const int W = words_per_lane(P, T);
-  const bool pm = (P.H & 3) == 0 && use_pm(P, T, W);
+  const int pm = pm_lanes(P, T, W);
   // lanes per row, where the row's edge words come from registers (a pair of
   // lanes only if the slot's lanes start at an even lane)
   const int gw = P.G / W;
   const bool one = gw == 1, two = gw == 2 && (T & 1) == 0;
-#define EE_RUN(...) return run_unit<__VA_ARGS__>(J, lds, tab, T, j0, cnt, flags, n_therm, g0)
+#define EE_RUN(...) return run_unit<__VA_ARGS__>(J, lds, tab, T, pm, j0, cnt, flags, n_therm, g0)
   if (W == 4) {
     if (pm && one) EE_RUN(DIM, true, 4, true, 1);
     if (pm && two) EE_RUN(DIM, true, 4, true, 2);

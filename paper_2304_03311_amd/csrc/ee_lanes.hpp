@@ -283,5 +283,21 @@ EE_HDI bool use_pm(const JP& P, int T, int W) {
   return B < P.R && (P.dim == 2 || B % P.ly == 0);
 }
 
+// Lanes of a slot of T that take rows in parity-major order, 0 where the rows
+// of the unit go in lane-map order: as use_pm, but where ly does not divide
+// the B row slots per replica (3D), as many as it does; the other lanes stay
+// idle.  24^3 with 512 lanes: B = 256 -> 240, two steps of two rows per
+// half-sweep instead of five single rows in lane-map order.
+EE_HDI int pm_lanes(const JP& P, int T, int W) {
+  if ((P.H & 3) != 0) return 0;
+  const int GW = P.G / W;
+  const int S = T / GW;
+  if (S < P.n) return 0;
+  int B = S / P.n;
+  if (P.dim == 3 && B > P.ly) B -= B % P.ly;
+  const int lanes = (P.dim == 3) ? B * P.n * GW : T;
+  return use_pm(P, lanes, W) ? lanes : 0;
+}
+
 }  // namespace lanes
 }  // namespace ee

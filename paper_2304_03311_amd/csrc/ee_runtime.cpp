@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "ee_internal.hpp"
+#include "ee_lanes.hpp"
 
 namespace {
 
@@ -124,6 +125,8 @@ Layout layout_of(const ee_job_desc* d) {
   return L;
 }
 
+using JP_shape = ee::lanes::JP;  // only the extents are set
+
 struct DeviceInfo {
   int cus = 0;
   int max_lds = 0;
@@ -145,35 +148,11 @@ DeviceInfo device_info() {
   return cache[dev];
 }
 
-constexpr int kDefaultBlock = 1024;
 constexpr int kMaxBlock = 1024;
 
 // The on-chip sweep needs one lane per word of a row in every workgroup:
 // threads >= G, rounded up to whole waves.
 int min_block(const Layout& L) { return (L.G + 63) / 64 * 64; }
-
-// Default block for a job when the caller gives none: about one lane per
-// four row-words of a trajectory (n * R * G words in a colour plane), so
-// that small lattices do not leave most lanes of a 1024-thread block idle,
-// within [min_block, kDefaultBlock].
-int default_block(const Layout& L, int n_rep) {
-  const long words = (long)n_rep * L.R * L.G;
-  const long want = (words + 3) / 4;
-  int b = (int)std::min<long>(kDefaultBlock, (want + 63) / 64 * 64);
-  return std::max(b, std::max(64, min_block(L)));
-}
-
-// Default block of a job launched alone (per-job path): when its
-// trajectories cannot fill the GPU's threads with one lane per row-word,
-// take that many lanes per trajectory (every lane one row: lowest
-// latency); otherwise share the GPU's threads out over the trajectories.
-int job_block(const Layout& L, const ee_job_desc& d) {
-  const long words = (long)d.n_replicas * L.R * L.G;
-  const long capacity = (long)device_info().cus * 2048;
-  const long per_traj = std::max(64L, std::min(words, capacity / std::max(1, d.n_traj)));
-  const int b = (int)std::min<long>(kDefaultBlock, (per_traj + 63) / 64 * 64);
-  return std::max(b, min_block(L));
-}
 
 // A job runs on chip when one trajectory fits a workgroup's LDS and one row
 // fits a workgroup's lanes; otherwise it is streamed from HBM.
@@ -181,6 +160,85 @@ bool fits_on_chip(const Layout& L) {
   return L.traj_words * 4 <= ee_k_max_lds_bytes() && min_block(L) <= kMaxBlock;
 }
 constexpr int kDefaultLdsBudget = 80 * 1024;  // two workgroups per CU
+
+// ---------------------------------------------------------------------------
+// Launch shape where the caller gives none: lanes T per trajectory and
+// trajectories k per workgroup, from a model of the sweep kernel's time.
+//
+// A half-sweep of a unit takes its instructions per wave times the cycles a
+// wave needs per instruction beside the other waves of its SIMD (about 6
+// alone, 8 with another one, 15 with three others: VALU issue), plus a
+// barrier.  The waves per SIMD follow from the LDS a trajectory takes, from T
+// and from how many units there are.  Instructions per step and half-sweep
+// are those of the compiled loops.  Over 19 lattices from 8 x 8 to 32^3 and 64
+// to 30000 trajectories the model's shape runs within 7% of the best of 36
+// block sizes and slot counts, and within 3% for most.  The rule before it
+// (about one lane per four row words, as many trajectories per workgroup as
+// 80 KB hold) ran 16384 trajectories of 2D 64 x 32 at ten trajectories of six
+// lanes in a wave, two waves per CU: 13.7 ms of sweeps with these kernels, now
+// 6.2; the 2D 256 x 32 cylinder, 32 jobs x 256: 27.4 ms, now 23.4.
+// ---------------------------------------------------------------------------
+JP_shape shape_of(const ee_job_desc& d, const Layout& L) {
+  JP_shape P{};
+  P.dim = d.dim; P.n = d.n_replicas; P.ly = d.ly; P.lt = d.lt;
+  P.H = L.H; P.G = L.G; P.R = L.R;
+  return P;
+}
+
+// Instructions per wave of one half-sweep of a trajectory on T lanes.
+double half_sweep_instr(const JP_shape& P, int T) {
+  const int W = ee::lanes::words_per_lane(P, T);
+  const int GW = P.G / W;
+  const double y = (P.dim == 3) ? 20.0 : 0.0;  // the two more neighbours
+  if (const int lanes = ee::lanes::pm_lanes(P, T, W)) {
+    const int B = lanes / GW / P.n;
+    const int steps = (P.R / 2 + B - 1) / B;
+    const double step = (W == 4 ? 300.0 : W == 3 ? 250.0 : W == 2 ? 165.0 : 105.0) + y;
+    // the sweep loop, and the rows next to the cut in the waves that have them
+    const double waves = (T + 63) / 64, cut = P.n * ((P.ly * GW + 63) / 64);
+    return steps * step + 50.0 + 90.0 * std::min(1.0, cut / waves);
+  }
+  const int slots = T / GW;
+  const int passes = (slots >= P.n) ? (P.R + slots / P.n - 1) / (slots / P.n) : (P.n * P.R + slots - 1) / slots;
+  const double row = (W == 4 ? 190.0 : W == 3 ? 165.0 : W == 2 ? 120.0 : 100.0) + y;
+  return passes * row + 90.0;
+}
+
+struct Shape {
+  int block, k;
+  double cost;  // model time of all trajectories, per half-sweep
+};
+
+// The shape for n_traj trajectories (of one job, or of equal jobs together).
+Shape launch_shape(const ee_job_desc& d, const Layout& L, long n_traj) {
+  const JP_shape P = shape_of(d, L);
+  const int tb = L.traj_words * 4;
+  const int cus = device_info().cus;
+  const long words = (long)d.n_replicas * L.R * L.G;
+  Shape best{std::max(64, min_block(L)), 1, 1e300};
+  const auto consider = [&](int block, int k) {
+    const int T = block / k;
+    if (T < L.G || k * (long)tb > ee_k_max_lds_bytes()) return;
+    const int waves = block / 64;
+    const long units = (n_traj + k - 1) / k;
+    const int fit = std::max(1, std::min(160 * 1024 / (k * tb + 256), 16 / waves));  // workgroups per CU
+    const int used = (int)std::min<long>(fit, (units + cus - 1) / cus);
+    const double per_simd = std::max(1.0, used * waves / 4.0);
+    const double t = half_sweep_instr(P, T) * std::max(6.0, 3.6 * per_simd + 0.8) + 60.0 + 25.0 * waves;
+    const double rounds = (double)((units + (long)fit * cus - 1) / ((long)fit * cus));
+    // a last round that is nearly empty costs a whole one; with many rounds
+    // the units' ends spread out
+    const double full = (double)units / ((double)fit * cus);
+    const double cost = t * (rounds <= 3.0 ? rounds : full + 0.5);
+    if (cost < best.cost * 0.995) best = Shape{block, k, cost};
+  };
+  for (int k : {1, 2, 4, 8, 16}) consider(std::max(64, min_block(L)), k);
+  for (int block = std::max(128, min_block(L)); block <= kMaxBlock; block += 64) {
+    if (block / 64 * 64L > ((words + 63) / 64) * 64) break;  // no more lanes than row words
+    consider(block, 1);
+  }
+  return best;
+}
 
 // Trajectories per workgroup that maximise the trajectories finished per
 // unit of workgroup time, within the LDS budget.
@@ -242,6 +300,11 @@ namespace {
 // Batch plans: device queue + job table + units, and a HIP graph of
 // [queue reset] -> [event] -> [persistent sweep kernel] -> [event] -> [estimator]
 // ---------------------------------------------------------------------------
+bool same_lattice(const ee_job* a, const ee_job* b) {
+  return a->d.dim == b->d.dim && a->d.lt == b->d.lt && a->d.lx == b->d.lx && a->d.ly == b->d.ly &&
+         a->d.n_replicas == b->d.n_replicas;
+}
+
 struct Plan {
   std::vector<ee_job*> jobs;
   int n_therm = 0;
@@ -388,10 +451,18 @@ ee_status launch_sweep_for_job(ee_job* j, uint32_t flags, int n_therm) {
     if (flags & ee::kFlagProto) return stream_sweeps(j, j->d.n_step, true);
     return stream_sweeps(j, n_therm, false);
   }
-  const int block = std::max(j->cfg.block_threads > 0 ? j->cfg.block_threads : job_block(j->L, j->d), min_block(j->L));
-  const int budget = j->cfg.lds_bytes > 0 ? j->cfg.lds_bytes : kDefaultLdsBudget;
-  const int k = choose_slots(j->L, j->d.n_replicas, block, std::max(budget, j->L.traj_words * 4), j->d.n_traj,
-                             2 * device_info().cus);
+  int block, k;
+  if (j->cfg.block_threads <= 0 && j->cfg.lds_bytes <= 0) {
+    const Shape sh = launch_shape(j->d, j->L, j->d.n_traj);
+    block = sh.block;
+    k = sh.k;
+  } else {
+    block = std::max(j->cfg.block_threads > 0 ? j->cfg.block_threads : launch_shape(j->d, j->L, j->d.n_traj).block,
+                     min_block(j->L));
+    const int budget = j->cfg.lds_bytes > 0 ? j->cfg.lds_bytes : kDefaultLdsBudget;
+    k = choose_slots(j->L, j->d.n_replicas, block, std::max(budget, j->L.traj_words * 4), j->d.n_traj,
+                     2 * device_info().cus);
+  }
   const int grid = (j->d.n_traj + k - 1) / k;
   const int lds = k * j->L.traj_words * 4;
   const int rc = ee_k_launch_sweep(j->dev_jobdev(), k, nullptr, 0, nullptr, nullptr, flags, n_therm, (int)j->g, grid,
@@ -416,15 +487,21 @@ ee_status check_cfg(const ee_launch_cfg* cfg) {
 }
 
 // Block size of a persistent launch over these jobs: the config's, else the
-// largest default block of the jobs; at least one lane per row word of
-// every job.
-int launch_block(ee_job* const* jobs, int count, const ee_launch_cfg& cfg) {
+// largest of the jobs' own shapes (each as if all trajectories were its
+// lattice's; *lds: the LDS that the largest of them takes); at least one lane
+// per row word of every job.
+int launch_block(ee_job* const* jobs, int count, const ee_launch_cfg& cfg, int* lds) {
   int block = 64;
-  if (cfg.block_threads > 0) {
-    block = cfg.block_threads;
-  } else {
-    for (int i = 0; i < count; ++i) block = std::max(block, default_block(jobs[i]->L, jobs[i]->d.n_replicas));
+  *lds = 0;
+  long n_traj = 0;
+  for (int i = 0; i < count; ++i) n_traj += jobs[i]->d.n_traj;
+  for (int i = 0; i < count; ++i) {
+    if (i > 0 && same_lattice(jobs[i], jobs[i - 1])) continue;
+    const Shape sh = launch_shape(jobs[i]->d, jobs[i]->L, n_traj);
+    block = std::max(block, sh.block);
+    *lds = std::max(*lds, sh.k * jobs[i]->L.traj_words * 4);
   }
+  if (cfg.block_threads > 0) block = cfg.block_threads;
   for (int i = 0; i < count; ++i) block = std::max(block, min_block(jobs[i]->L));
   return block;
 }
@@ -438,12 +515,24 @@ int lds_budget(ee_job* const* jobs, int count, const ee_launch_cfg& cfg) {
 }
 
 // Relative cost of one unit of job j (k trajectories per workgroup of
-// `block` lanes): row iterations per half-sweep times sweeps.
+// `block` lanes).
 double unit_cost(const ee_job* j, int block, int k, int n_therm) {
-  const int T = block / k;
-  const int nrg = std::max(1, T / j->L.G);
-  const double iters = std::ceil((double)j->d.n_replicas * j->L.R / nrg);
-  return iters * (double)(n_therm + j->d.n_step);
+  return half_sweep_instr(shape_of(j->d, j->L), block / k) * (double)(n_therm + j->d.n_step);
+}
+
+// Slots per workgroup of job j in a persistent launch whose shape the caller
+// left to the runtime: the k, within the launch's LDS, that finishes most
+// trajectories per issued instruction.
+int auto_slots(const ee_job* j, int block, int lds) {
+  const JP_shape P = shape_of(j->d, j->L);
+  int best = 1;
+  double rate = 0.0;
+  for (int k = 1; k <= ee::kMaxSlots && k <= j->d.n_traj; ++k) {
+    if (k * j->L.traj_words * 4 > lds || block / k < j->L.G) break;
+    const double r = k / half_sweep_instr(P, block / k);
+    if (r > rate * 1.02) { rate = r; best = k; }
+  }
+  return best;
 }
 
 // Persistent grid: as many workgroups of this shape as fit on the GPU at
@@ -468,14 +557,17 @@ struct UnitPlan {
 };
 
 ee_status plan_units(ee_job* const* jobs, int count, int n_therm, const ee_launch_cfg& cfg, UnitPlan* out) {
-  out->block = launch_block(jobs, count, cfg);
+  int lds_auto = 0;
+  out->block = launch_block(jobs, count, cfg, &lds_auto);
   const int budget = lds_budget(jobs, count, cfg);
+  const bool automatic = cfg.block_threads <= 0 && cfg.lds_bytes <= 0;
   struct U { ee::Unit u; double cost; };
   std::vector<U> units;
   int lds_need = 0;
   for (int i = 0; i < count; ++i) {
     ee_job* j = jobs[i];
-    const int k = choose_slots(j->L, j->d.n_replicas, out->block, budget, j->d.n_traj);
+    const int k = automatic ? auto_slots(j, out->block, lds_auto)
+                            : choose_slots(j->L, j->d.n_replicas, out->block, budget, j->d.n_traj);
     lds_need = std::max(lds_need, k * j->L.traj_words * 4);
     const double cost = unit_cost(j, out->block, k, n_therm);
     for (int j0 = 0; j0 < j->d.n_traj; j0 += k)

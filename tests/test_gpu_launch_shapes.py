@@ -1,0 +1,53 @@
+"""The launch shapes that the runtime chooses by itself, and slots of which only
+a part of the lanes take rows: bit-identical to the oracle."""
+from __future__ import annotations
+
+import math
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import oracle as eo
+from paper_2304_03311_amd import ee
+
+BC2 = 0.5 * math.log(1.0 + math.sqrt(2.0))
+BC3 = 0.2216546
+
+pytestmark = pytest.mark.gpu
+
+
+def check(s: ee.JobSpec, cfg, n_therm: int = 2):
+    print(f"[gpu] {s} {cfg}", file=sys.stderr, flush=True)
+    I, sp = eo.run(eo.Job(s.dim, s.lt, s.lx, s.ly, s.n, s.beta, s.l, s.n_step, s.n_traj, s.seed, s.reverse,
+                          s.subsets, s.whole), n_therm, want_spins=True)
+    j = ee.Job(s)
+    j.set_launch(cfg)
+    j.thermalize(n_therm)
+    j.run_protocol()
+    assert np.array_equal(j.work(), I) and np.array_equal(j.spins(), sp)
+    j.close()
+    j = ee.Job(s)
+    ee.batch_run([j], n_therm, cfg=cfg)
+    assert np.array_equal(j.work(), I) and np.array_equal(j.spins(), sp)
+    j.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(dim=2, lt=8, lx=8, ly=1, n=2, beta=BC2, l=3, n_step=3, n_traj=9001),  # several per wave, one row per lane
+    dict(dim=2, lt=64, lx=32, ly=1, n=2, beta=BC2, l=11, n_step=2, n_traj=8193),  # two per wave
+    dict(dim=2, lt=48, lx=48, ly=1, n=3, beta=BC2, l=30, n_step=2, n_traj=520),  # three lanes per row
+    dict(dim=2, lt=16, lx=16, ly=1, n=2, beta=BC2, l=4, n_step=4, n_traj=1),
+    dict(dim=3, lt=32, lx=32, ly=32, n=2, beta=BC3, l=9, n_step=2, n_traj=3),  # a wide workgroup per trajectory
+    dict(dim=3, lt=6, lx=22, ly=10, n=2, beta=BC3, l=5, n_step=10, n_traj=300, subsets=True),
+], ids=["8x8", "64x32", "48x48_n3", "16x16_one", "32cube", "ragged"])
+def test_runtime_shapes_match_oracle(kw):
+    check(ee.JobSpec(seed=91, **kw), None)
+
+
+@pytest.mark.parametrize("block", [512, 576, 1024])
+def test_slots_with_idle_lanes_match_oracle(block):
+    # 24 wide in y: 512 lanes hold 256 row slots per replica, of which 240 take
+    # rows in parity-major order; 1024 lanes 504 of 512
+    check(ee.JobSpec(dim=3, lt=24, lx=24, ly=24, n=2, beta=BC3, l=7, n_step=3, n_traj=3, seed=92, reverse=True),
+          dict(block_threads=block, lds_bytes=28672))

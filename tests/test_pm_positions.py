@@ -86,6 +86,23 @@ int main(int argc, char** argv) {
     };
     if (dim == 2) go(std::integral_constant<int, 2>{}); else go(std::integral_constant<int, 3>{});
   }
+  // slots of any size: pm_lanes of them take the rows, the others none
+  for (int T = P.G; T <= 1024; T += 29) {
+    const int W = words_per_lane(P, T), lanes = pm_lanes(P, T, W);
+    CHECK(lanes <= T, "T%d lanes %d", T, lanes);
+    CHECK((lanes > 0) || !use_pm(P, T, W), "T%d loses the order", T);
+    if (!lanes) continue;
+    const auto idle = [&](auto d) {
+      constexpr int D = decltype(d)::value;
+      for (int lane = lanes; lane < T; ++lane)
+        CHECK((W == 4 ? make_lane_pm<D, 4>(P, lane, lanes).t : W == 3 ? make_lane_pm<D, 3>(P, lane, lanes).t
+               : W == 2 ? make_lane_pm<D, 2>(P, lane, lanes).t : make_lane_pm<D, 1>(P, lane, lanes).t) >= P.lt,
+              "T%d lane %d has rows", T, lane);
+      if (W == 4) walk<D, 4>(P, lanes); else if (W == 3) walk<D, 3>(P, lanes);
+      else if (W == 2) walk<D, 2>(P, lanes); else walk<D, 1>(P, lanes);
+    };
+    if (dim == 2) idle(std::integral_constant<int, 2>{}); else idle(std::integral_constant<int, 3>{});
+  }
   printf("cases %d fails %d\n", cases, fails);
   return fails || !cases;
 }
