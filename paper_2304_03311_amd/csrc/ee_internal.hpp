@@ -37,7 +37,11 @@ constexpr int kMaxSlots = 16;  // trajectories per workgroup at most
 constexpr int kSweepTailBytes = 128;
 static_assert((4 + kMaxSlots + 8) * 4 <= kSweepTailBytes, "sweep LDS tables");
 inline int sweep_tail_words(int lds_bytes) { return (lds_bytes + 15) / 16 * 4; }
-constexpr int kEstimateThreads = 1024;  // workgroup size of the estimator kernel
+constexpr int kEstSmall = 895;  // trajectories of a job whose estimate is one workgroup's (n + 1 lanes and a wave)
+struct EstLaunch {              // one launch of the estimator
+  const void* fn;
+  int gx, gy, block;
+};
 constexpr uint32_t kFlagInit = 1u;   // draw the initial spins (else load them)
 constexpr uint32_t kFlagProto = 2u;  // run the N protocol sweeps after n_therm sweeps
 
@@ -95,10 +99,10 @@ int ee_k_launch_sweep(const ee::JobDev* single_job, int single_k, const ee::Unit
                       const ee::JobDev* const* jobtab, uint32_t flags, int n_therm, int g0, int grid, int block,
                       int lds_bytes, void* stream);
 int ee_k_launch_queue_reset(int* queue, void* stream);
-int ee_k_launch_estimate(const ee::JobDev* const* jobtab, int count, void* stream);
+int ee_k_launch_estimate(const ee::JobDev* const* jobtab, int count, int max_n, void* stream);
 int ee_k_sweep_kernel_ptr(const void** fn);
 int ee_k_queue_reset_ptr(const void** fn);
-int ee_k_estimate_ptr(const void** fn);
+int ee_k_estimate_plan(int count, int max_n, ee::EstLaunch out[4]);
 int ee_k_max_lds_bytes();
 int ee_k_launch_stream_sweep(const ee::JobDev* job, int n_traj, int lanes, int c, uint32_t g, int pos, int dpos,
                              int work, void* stream);

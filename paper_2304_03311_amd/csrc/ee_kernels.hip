@@ -11,10 +11,9 @@
 //   and only a tie (probability 2^-16) draws the low 16 bits from a second
 //   call.  In batch mode the workgroups are persistent and pull work units
 //   (job, block of trajectories) from a device queue.
-// estimate_kernel: Jarzynski estimator of one job per workgroup (App. A),
-//   with wave-shuffle reductions and scans:
-//   integer max/min/sum of I_j, FP64 sum of exp(beta (I_j - I_max)/N),
-//   log-sum-exp, delete-one jackknife from prefix/suffix sums.
+// estimate_kernel, est_*_kernel: Jarzynski estimator (App. A): integer
+//   max/min of I_j, FP64 sum of exp(beta (I_j - I_max)/N), log-sum-exp,
+//   delete-one jackknife.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -1134,168 +1133,295 @@ __global__ void queue_reset_kernel(int* queue) {
 }
 
 // ---------------------------------------------------------------------------
-// Estimator (App. A, Jarzynski's equality), one workgroup per job.
+// Estimator (App. A, Jarzynski's equality).
 //
 // Every floating-point result is formed by the same operations in the same
 // order as the plain definition: the n_t exponentials e_j are summed one
 // after the other in ascending j, each leave-one-out sum is its own
 // ascending sum over j != i, and the mean and variance of W are sums of the
 // terms -(beta/S) I_j in ascending j.  exp and log are the correctly
-// rounded ones of ee_dd.hpp.  The order costs no time worth counting: the
-// long sums are a few thousand dependent FP64 adds, each done by one lane
-// while other waves do the others, and the leave-one-out sums run one per
-// lane (n_t^2 adds in all, e_j broadcast from LDS tiles).
+// rounded ones of ee_dd.hpp.
+//
+// What bounds it is then the chain of dependent FP64 adds (some 17 cycles a
+// term for a wave alone on its SIMD), and how many of the n^2 adds of the leave-one-out sums run beside
+// each other.  Up to kEstSmall trajectories one workgroup does a job
+// (estimate_kernel): lane i forms sum i, lane n the full sum, all in one walk
+// over the e_j in LDS, and one more wave the other sums.  Above, four
+// launches: the exponentials over many workgroups (est_exp_kernel), the plain
+// sums in one wave per job (est_sum_kernel), the leave-one-out sums in one
+// wave per 64 of them (est_loo_kernel) and their spread (est_err_kernel).
+// Sums i of a wave start from the full sum's prefix, which is their own
+// beginning.  16384 trajectories: 0.64 against 9.8 ms in one workgroup; 64
+// jobs of 1024: 59 against 145 us; 8 trajectories: 9 against 29 us.
 // ---------------------------------------------------------------------------
 #pragma clang fp contract(off)
-constexpr int kEstThreads = ee::kEstimateThreads;
-constexpr int kEstWaves = kEstThreads / 64;
-constexpr int kEstTile = 4096;  // e_j per LDS tile (32 KiB)
-constexpr int kEstAcc = 8;      // leave-one-out sums per lane and pass
+constexpr int kEstTileN = 256;  // e_j per workgroup of est_exp_kernel
 
-// Integer reduction over the block: butterfly shuffles within each 64-lane
-// wave, then the wave results through LDS (sh: kEstWaves entries).
-template <typename Op>
-__device__ long long block_reduce_ll(long long v, long long* sh, Op op) {
+// Integer minimum and maximum over the block: butterfly shuffles within each
+// wave, then the waves' results through LDS (sh: 32 entries).
+__device__ __forceinline__ void block_min_max(long long& mn, long long& mx, long long* sh) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off, 64));
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  for (int off = 32; off > 0; off >>= 1) {
+    const long long a = __shfl_xor(mn, off, 64), b = __shfl_xor(mx, off, 64);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+  }
+  const int nw = (blockDim.x + 63) >> 6, wave = threadIdx.x >> 6;
+  if (nw == 1) return;
+  if ((threadIdx.x & 63) == 0) {
+    sh[2 * wave] = mn;
+    sh[2 * wave + 1] = mx;
+  }
   __syncthreads();
-  long long r = sh[0];
-#pragma unroll
-  for (int k = 1; k < kEstWaves; ++k) r = op(r, sh[k]);
-  __syncthreads();
-  return r;
+  for (int k = 0; k < nw; ++k) {
+    mn = sh[2 * k] < mn ? sh[2 * k] : mn;
+    mx = sh[2 * k + 1] > mx ? sh[2 * k + 1] : mx;
+  }
 }
 
-// Visit load(0), load(1), ... load(n-1) in order with add(), loading
+// Visit load(0), load(1), ... load(n-1) in order with add(j, v), loading
 // kEstGroup values ahead of their adds.
 constexpr int kEstGroup = 16;
 template <typename Load, typename Add>
 __device__ __forceinline__ void for_groups(int n, Load load, Add add) {
-  int j = 0;
-  for (; j + kEstGroup <= n; j += kEstGroup) {
-    double v[kEstGroup];
+  // pairs of groups: each group's registers are loaded again while the other
+  // one is added
+  const int full = n / (2 * kEstGroup) * (2 * kEstGroup);
+  if (full > 0) {
+    double a[kEstGroup], b[kEstGroup];
 #pragma unroll
-    for (int k = 0; k < kEstGroup; ++k) v[k] = load(j + k);
+    for (int k = 0; k < kEstGroup; ++k) a[k] = load(k);
+    for (int j = 0; j < full; j += 2 * kEstGroup) {
 #pragma unroll
-    for (int k = 0; k < kEstGroup; ++k) add(v[k]);
+      for (int k = 0; k < kEstGroup; ++k) b[k] = load(j + kEstGroup + k);
+#pragma unroll
+      for (int k = 0; k < kEstGroup; ++k) add(j + k, a[k]);
+      const int jn = (j + 2 * kEstGroup < full) ? j + 2 * kEstGroup : j;
+#pragma unroll
+      for (int k = 0; k < kEstGroup; ++k) a[k] = load(jn + k);
+#pragma unroll
+      for (int k = 0; k < kEstGroup; ++k) add(j + kEstGroup + k, b[k]);
+    }
   }
-  for (; j < n; ++j) add(load(j));
+  for (int j = full; j < n; ++j) add(j, load(j));
 }
 
-__global__ void __launch_bounds__(kEstThreads) estimate_kernel(const JobDev* const* jobtab) {
-  __shared__ double tile[kEstTile];
-  __shared__ long long shl[kEstWaves];
-  __shared__ double shd[4];
-  const JobDev* J = jobtab[blockIdx.x];
-  const int tid = threadIdx.x;
-  const int n = J->n_traj;
-  const int64_t* I = J->work;
-  const double beta = J->beta;
-  const double N = (double)J->S;  // W_j = -(beta/S) I_j
-  ee_result* res = J->result;
-  double* e = reinterpret_cast<double*>(J->work + n);  // n doubles: e_j
-  double* loo = e + n;                                 // n doubles: leave-one-out estimates
-
-  long long mx = LLONG_MIN, mn = LLONG_MAX;
-  for (int i = tid; i < n; i += kEstThreads) {
-    const long long v = I[i];
-    mx = v > mx ? v : mx;
-    mn = v < mn ? v : mn;
-  }
-  const long long imax = block_reduce_ll(mx, shl, [](long long a, long long b) { return a > b ? a : b; });
-  const long long imin = block_reduce_ll(mn, shl, [](long long a, long long b) { return a < b ? a : b; });
-  for (int i = tid; i < n; i += kEstThreads) e[i] = ee::dd::exp_cr((beta * (double)(I[i] - imax)) / N);
-  __syncthreads();
-
-  // The sums in ascending j, each by one lane of its own wave.  The loads of
-  // a group of kEstGroup terms are issued before its adds, which stay in
-  // order: one memory latency per group instead of one per term.
-  if (tid == 0) {
-    double s = 0.0;
-    for_groups(n, [&](int j) { return e[j]; }, [&](double v) { s += v; });
-    shd[0] = s;
-  } else if (tid == 64) {
-    double s2 = 0.0;
-    for_groups(n, [&](int j) { return e[j]; }, [&](double v) { s2 += v * v; });
-    shd[1] = s2;
-  } else if (tid == 128) {
-    double wm = 0.0;
-    for_groups(n, [&](int j) { return (double)I[j]; }, [&](double v) { wm += -(beta / N) * v; });
-    wm /= n;
-    double wv = 0.0;
-    for_groups(n, [&](int j) { return (double)I[j]; }, [&](double v) {
-      const double d = -(beta / N) * v - wm;
-      wv += d * d;
-    });
-    wv /= n;
-    shd[2] = wm;
-    shd[3] = wv;
-  }
-  __syncthreads();
-  const double s = shd[0];
-  const double shift = (beta * (double)imax) / N;
-  const double dF = -(shift + ee::dd::log_cr(s) - ee::dd::log_cr((double)n));
-
-  if (n >= 2) {
-    // leave-one-out sums S_i = sum_{j != i} e_j, ascending j: lane t takes
-    // i = t, t + T, ... in passes of A sums; adding +0.0 for j = i leaves a
-    // sum of non-negative terms unchanged, so it stands for skipping j.
-    const double log_n1 = ee::dd::log_cr((double)(n - 1));
-    const int per_lane = (n + kEstThreads - 1) / kEstThreads;
-    const auto passes = [&](auto acount) {
-      constexpr int A = decltype(acount)::value;
-      for (int p0 = 0; p0 < per_lane; p0 += A) {
-        double acc[A];
-        int idx[A];
+// The same for a workgroup of one wave and terms in device memory: the lanes
+// load tiles of kTileTerms terms, one tile ahead, and every lane then reads
+// them in order from LDS (buf: two tiles).  Read through the scalar cache, 16
+// terms ahead, a term took 32 cycles.
+constexpr int kTileTerms = 512;
+template <typename Load, typename Add>
+__device__ __forceinline__ void for_tiles(int n, double* buf, Load load, Add add) {
+  constexpr int K = kTileTerms / 64;
+  const int lane = threadIdx.x;
+  double v[K];
+  const auto fetch = [&](int j0) {
 #pragma unroll
-        for (int a = 0; a < A; ++a) {
-          acc[a] = 0.0;
-          idx[a] = tid + (p0 + a) * kEstThreads;
-        }
-        for (int t0 = 0; t0 < n; t0 += kEstTile) {
-          const int len = min(kEstTile, n - t0);
-          __syncthreads();
-          for (int q = tid; q < len; q += kEstThreads) tile[q] = e[t0 + q];
-          __syncthreads();
-          for (int q = 0; q < len; ++q) {
-            const double v = tile[q];
-            const int j = t0 + q;
-#pragma unroll
-            for (int a = 0; a < A; ++a) acc[a] += (j == idx[a]) ? 0.0 : v;
-          }
-        }
-#pragma unroll
-        for (int a = 0; a < A; ++a)
-          if (idx[a] < n) loo[idx[a]] = -(shift + ee::dd::log_cr(acc[a]) - log_n1);
-      }
-    };
-    if (per_lane <= 1) passes(std::integral_constant<int, 1>{});
-    else if (per_lane <= 2) passes(std::integral_constant<int, 2>{});
-    else if (per_lane <= 4) passes(std::integral_constant<int, 4>{});
-    else passes(std::integral_constant<int, kEstAcc>{});
-    __syncthreads();
-  }
-  if (tid == 0) {
-    double err = __builtin_nan("");
-    if (n >= 2) {
-      double mean = 0.0;
-      for_groups(n, [&](int i) { return loo[i]; }, [&](double v) { mean += v; });
-      mean /= n;
-      double acc = 0.0;
-      for_groups(n, [&](int i) { return loo[i]; }, [&](double v) { acc += (v - mean) * (v - mean); });
-      err = sqrt((double)(n - 1) / (double)n * acc);
+    for (int k = 0; k < K; ++k) {
+      const int j = j0 + 64 * k + lane;
+      v[k] = (j < n) ? load(j) : 0.0;
     }
+  };
+  const auto put = [&](double* b) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) b[64 * k + lane] = v[k];
+  };
+  __syncthreads();
+  fetch(0);
+  put(buf);
+  int cur = 0;
+  for (int j0 = 0; j0 < n; j0 += kTileTerms, cur ^= 1) {
+    __syncthreads();
+    if (j0 + kTileTerms < n) fetch(j0 + kTileTerms);
+    const double* b = buf + cur * kTileTerms;
+    for_groups(min(kTileTerms, n - j0), [&](int j) { return b[j]; }, [&](int j, double x) { add(j0 + j, x); });
+    if (j0 + kTileTerms < n) put(buf + (cur ^ 1) * kTileTerms);
+  }
+}
+
+struct EstJob {
+  int n;
+  double beta, N;  // W_j = -(beta/N) I_j
+  const int64_t* I;
+  double *e, *loo;
+  ee_result* res;
+  int replicas;
+};
+__device__ __forceinline__ EstJob est_job(const JobDev* J) {
+  EstJob E;
+  E.n = uni(J->n_traj);
+  E.beta = J->beta;
+  E.N = (double)uni(J->S);
+  E.I = uni_ptr(J->work);
+  E.e = reinterpret_cast<double*>(uni_ptr(J->work) + E.n);  // n doubles: e_j
+  E.loo = E.e + E.n;                                        // n doubles: leave-one-out estimates
+  E.res = uni_ptr(J->result);
+  E.replicas = uni(J->n);
+  return E;
+}
+
+// The jackknife error from the leave-one-out estimates, visited in ascending
+// i by visit(add).
+template <typename Visit>
+__device__ __forceinline__ double jackknife(int n, Visit visit) {
+  if (n < 2) return __builtin_nan("");
+  double mean = 0.0;
+  visit([&](int, double v) { mean += v; });
+  mean /= n;
+  double acc = 0.0;
+  visit([&](int, double v) { acc += (v - mean) * (v - mean); });
+  return sqrt((double)(n - 1) / (double)n * acc);
+}
+
+// One job per workgroup, n <= kEstSmall; blockDim.x: n + 1 rounded up to
+// whole waves, and one wave more.
+__global__ void __launch_bounds__(1024) estimate_kernel(const JobDev* const* jobtab) {
+  __shared__ double se[ee::kEstSmall], sl[ee::kEstSmall];
+  __shared__ long long shl[32];
+  __shared__ double shd[8];
+  const EstJob E = est_job(jobtab[blockIdx.x]);
+  const int tid = threadIdx.x, n = E.n;
+  const bool stat = (tid >> 6) == ((int)blockDim.x >> 6) - 1;  // the last wave
+  const bool mine = tid < n;  // never in the last wave
+  const long long Ii = mine ? E.I[tid] : 0;
+  long long mn = mine ? Ii : LLONG_MAX, mx = mine ? Ii : LLONG_MIN;
+  block_min_max(mn, mx, shl);
+  const double w = -(E.beta / E.N);
+  if (mine) {
+    se[tid] = ee::dd::exp_cr((E.beta * (double)(Ii - mx)) / E.N);
+    sl[tid] = w * (double)Ii;  // W_j
+  }
+  __syncthreads();
+  const double shift = (E.beta * (double)mx) / E.N;
+  const int lane = tid & 63;
+  double acc = 0.0, lg = 0.0;
+  if (stat) {
+    // lane 0: sum of e^2, lane 1: the mean and variance of W; lanes 2 and 3:
+    // log n, log (n - 1)
+    const bool sq = lane == 0;
+    for_groups(n, [&](int j) { return sq ? se[j] : sl[j]; }, [&](int, double v) { acc += sq ? v * v : v; });
+    if (lane == 0) shd[1] = acc;
+    const double wm = acc / n;
+    double wv = 0.0;
+    for_groups(n, [&](int j) { return sl[j]; }, [&](int, double v) { wv += (v - wm) * (v - wm); });
+    if (lane == 1) {
+      shd[2] = wm;
+      shd[3] = wv / n;
+    }
+    lg = ee::dd::log_cr((double)((lane == 3 && n >= 2) ? n - 1 : n));
+    if (lane == 2) shd[4] = lg;
+    if (lane == 3) shd[5] = lg;
+  } else {
+    // lane i: the sum over j != i (adding +0.0 for j = i leaves a sum of
+    // non-negative terms unchanged); lane n: the full sum
+    for_groups(n, [&](int j) { return se[j]; }, [&](int j, double v) { acc += (j == tid) ? 0.0 : v; });
+    if (tid <= n && !(n == 1 && tid == 0)) lg = ee::dd::log_cr(acc);
+    if (tid == n) {
+      shd[0] = acc;
+      shd[6] = lg;
+    }
+  }
+  __syncthreads();
+  if (mine) sl[tid] = -(shift + lg - shd[5]);
+  __syncthreads();
+  if (tid == 0) {
+    const double dF = -(shift + shd[6] - shd[4]);
+    const double err = jackknife(n, [&](auto add) { for_groups(n, [&](int i) { return sl[i]; }, add); });
+    ee_result* res = E.res;
     res->dF = dF;
-    res->dS = dF / (double)(J->n - 1);
+    res->dS = dF / (double)(E.replicas - 1);
     res->dF_err = err;
     res->w_mean = shd[2];
     res->w_var = shd[3];
-    res->ess = s * s / shd[1];
-    res->i_min = imin;
-    res->i_max = imax;
+    res->ess = shd[0] * shd[0] / shd[1];
+    res->i_min = mn;
+    res->i_max = mx;
     res->n_traj = n;
   }
+}
+
+// e_j of kEstTileN trajectories (y) of job x; every workgroup finds the
+// extreme works itself.
+__global__ void __launch_bounds__(kEstTileN) est_exp_kernel(const JobDev* const* jobtab) {
+  __shared__ long long shl[32];
+  const EstJob E = est_job(jobtab[blockIdx.x]);
+  const int i = blockIdx.y * kEstTileN + threadIdx.x;
+  if (blockIdx.y * kEstTileN >= E.n) return;
+  long long mn = LLONG_MAX, mx = LLONG_MIN;
+  for (int q = threadIdx.x; q < E.n; q += kEstTileN) {
+    const long long v = E.I[q];
+    mn = v < mn ? v : mn;
+    mx = v > mx ? v : mx;
+  }
+  block_min_max(mn, mx, shl);
+  if (i < E.n) E.e[i] = ee::dd::exp_cr((E.beta * (double)(E.I[i] - mx)) / E.N);
+  if (i == 0) {
+    E.res->i_min = mn;
+    E.res->i_max = mx;
+    E.res->n_traj = E.n;
+  }
+}
+
+// The plain sums of job x, one per lane: 0 of e (its prefix before every 64th
+// term goes to loo, where the leave-one-out sums of those 64 begin), 1 of
+// e^2, 2 of W, which then does the variance.
+__global__ void __launch_bounds__(64) est_sum_kernel(const JobDev* const* jobtab) {
+  const EstJob E = est_job(jobtab[blockIdx.x]);
+  const int lane = threadIdx.x, n = E.n;
+  __shared__ double buf[2 * kTileTerms];
+  const double w = -(E.beta / E.N);
+  double acc = 0.0;
+  if (blockIdx.y == 0) {
+    for_tiles(n, buf, [&](int j) { return E.e[j]; }, [&](int j, double v) {
+      if ((j & 63) == 0 && lane == 0) E.loo[j] = acc;
+      acc += (lane == 1) ? v * v : v;
+    });
+    const double s2 = __shfl(acc, 1, 64), s = __shfl(acc, 0, 64);
+    const double lg = ee::dd::log_cr(lane == 0 ? s : (double)n);
+    const double log_n = __shfl(lg, 1, 64);
+    if (lane == 0) {
+      const double shift = (E.beta * (double)E.res->i_max) / E.N;
+      const double dF = -(shift + lg - log_n);
+      E.res->dF = dF;
+      E.res->dS = dF / (double)(E.replicas - 1);
+      E.res->ess = s * s / s2;
+    }
+  } else {
+    const auto load = [&](int j) { return w * (double)E.I[j]; };
+    for_tiles(n, buf, load, [&](int, double v) { acc += v; });
+    const double wm = acc / n;
+    double wv = 0.0;
+    for_tiles(n, buf, load, [&](int, double v) { wv += (v - wm) * (v - wm); });
+    if (lane == 0) {
+      E.res->w_mean = wm;
+      E.res->w_var = wv / n;
+    }
+  }
+}
+
+// Leave-one-out estimates 64 y .. 64 y + 63 of job x, one per lane.
+__global__ void __launch_bounds__(64) est_loo_kernel(const JobDev* const* jobtab) {
+  const EstJob E = est_job(jobtab[blockIdx.x]);
+  const int n = E.n, i0 = blockIdx.y * 64, i = i0 + (int)threadIdx.x;
+  if (i0 >= n || n < 2) return;
+  __shared__ double buf[2 * kTileTerms];
+  const double* e = E.e + i0;
+  double acc = E.loo[i0];
+  const int own = min(64, n - i0);
+  for (int j = 0; j < own; ++j) acc += (j == (int)threadIdx.x) ? 0.0 : e[j];
+  for_tiles(n - i0 - own, buf, [&](int j) { return e[64 + j]; }, [&](int, double v) { acc += v; });
+  const double shift = (E.beta * (double)E.res->i_max) / E.N;
+  const double log_n1 = ee::dd::log_cr((double)(n - 1));
+  if (i < n) E.loo[i] = -(shift + ee::dd::log_cr(acc) - log_n1);
+}
+
+__global__ void __launch_bounds__(64) est_err_kernel(const JobDev* const* jobtab) {
+  const EstJob E = est_job(jobtab[blockIdx.x]);
+  __shared__ double buf[2 * kTileTerms];
+  const double err =
+      jackknife(E.n, [&](auto add) { for_tiles(E.n, buf, [&](int i) { return E.loo[i]; }, add); });
+  if (threadIdx.x == 0) E.res->dF_err = err;
 }
 
 }  // namespace
@@ -1346,9 +1472,18 @@ int ee_k_queue_reset_ptr(const void** fn) {
   *fn = reinterpret_cast<const void*>(&queue_reset_kernel);
   return 0;
 }
-int ee_k_estimate_ptr(const void** fn) {
-  *fn = reinterpret_cast<const void*>(&estimate_kernel);
-  return 0;
+// The launches of the estimator of `count` jobs of at most max_n
+// trajectories, in order; each takes the job table.  Returns their number.
+int ee_k_estimate_plan(int count, int max_n, ee::EstLaunch out[4]) {
+  if (max_n <= ee::kEstSmall) {
+    out[0] = {reinterpret_cast<const void*>(&estimate_kernel), count, 1, (max_n + 64) / 64 * 64 + 64};
+    return 1;
+  }
+  out[0] = {reinterpret_cast<const void*>(&est_exp_kernel), count, (max_n + kEstTileN - 1) / kEstTileN, kEstTileN};
+  out[1] = {reinterpret_cast<const void*>(&est_sum_kernel), count, 2, 64};
+  out[2] = {reinterpret_cast<const void*>(&est_loo_kernel), count, (max_n + 63) / 64, 64};
+  out[3] = {reinterpret_cast<const void*>(&est_err_kernel), count, 1, 64};
+  return 4;
 }
 
 int ee_k_launch_sweep(const ee::JobDev* single_job, int single_k, const ee::Unit* units, int n_units, int* queue,
@@ -1406,8 +1541,14 @@ int ee_k_launch_queue_reset(int* queue, void* stream) {
   return (int)hipGetLastError();
 }
 
-int ee_k_launch_estimate(const ee::JobDev* const* jobtab, int count, void* stream) {
-  hipLaunchKernelGGL(estimate_kernel, dim3(count), dim3(kEstThreads), 0, (hipStream_t)stream, jobtab);
+int ee_k_launch_estimate(const ee::JobDev* const* jobtab, int count, int max_n, void* stream) {
+  ee::EstLaunch L[4];
+  const int k = ee_k_estimate_plan(count, max_n, L);
+  void* args[] = {&jobtab};
+  for (int i = 0; i < k; ++i) {
+    const hipError_t e = hipLaunchKernel(L[i].fn, dim3(L[i].gx, L[i].gy), dim3(L[i].block), args, 0, (hipStream_t)stream);
+    if (e != hipSuccess) return (int)e;
+  }
   return (int)hipGetLastError();
 }
 

@@ -298,11 +298,17 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Batch plans: device queue + job table + units, and a HIP graph of
-// [queue reset] -> [event] -> [persistent sweep kernel] -> [event] -> [estimator]
+// [queue reset] -> [event] -> [persistent sweep kernel] -> [event] -> [estimator launches]
 // ---------------------------------------------------------------------------
 bool same_lattice(const ee_job* a, const ee_job* b) {
   return a->d.dim == b->d.dim && a->d.lt == b->d.lt && a->d.lx == b->d.lx && a->d.ly == b->d.ly &&
          a->d.n_replicas == b->d.n_replicas;
+}
+
+int max_traj(ee_job* const* jobs, int count) {
+  int n = 0;
+  for (int i = 0; i < count; ++i) n = std::max(n, (int)jobs[i]->d.n_traj);
+  return n;
 }
 
 struct Plan {
@@ -311,6 +317,7 @@ struct Plan {
   ee_launch_cfg cfg{};
   int dim = 0;
   int block = 0, lds = 0, grid = 0, n_units = 0;
+  int max_n = 0;  // most trajectories of a job
   void* dev_buf = nullptr;
   int* dev_queue = nullptr;
   const ee::JobDev** dev_jobtab = nullptr;
@@ -594,6 +601,7 @@ ee_status build_plan(ee_job* const* jobs, int count, int n_therm, const ee_launc
   P->lds = up.lds;
   P->grid = up.grid;
   P->n_units = (int)up.units.size();
+  P->max_n = max_traj(jobs, count);
   const std::vector<ee::Unit>& units = up.units;
   const void* fn = nullptr;
   int rc = ee_k_sweep_kernel_ptr(&fn);
@@ -625,10 +633,8 @@ ee_status build_plan(ee_job* const* jobs, int count, int n_therm, const ee_launc
     if (e != hipSuccess) { delete P; return fail(EE_EHIP, "hipGraphCreate: %s", hipGetErrorString(e)); }
     P->graph = g;
     const void* f_reset = nullptr;
-    const void* f_est = nullptr;
     ee_k_queue_reset_ptr(&f_reset);
-    ee_k_estimate_ptr(&f_est);
-    hipGraphNode_t n_reset, n_ev0, n_sweep, n_ev1, n_est;
+    hipGraphNode_t n_reset, n_ev0, n_sweep, n_ev1;
     int* q = P->dev_queue;
     void* a_reset[] = {&q};
     hipKernelNodeParams kp{};
@@ -656,12 +662,19 @@ ee_status build_plan(ee_job* const* jobs, int count, int n_therm, const ee_launc
     if (e == hipSuccess) e = hipGraphAddKernelNode(&n_sweep, g, &n_ev0, 1, &kp);
     if (e == hipSuccess) e = hipGraphAddEventRecordNode(&n_ev1, g, &n_sweep, 1, P->ev_stop);
     void* a_est[] = {&jt};
-    kp.func = const_cast<void*>(f_est);
-    kp.gridDim = dim3(count);
-    kp.blockDim = dim3(ee::kEstimateThreads);
-    kp.sharedMemBytes = 0;
-    kp.kernelParams = a_est;
-    if (e == hipSuccess) e = hipGraphAddKernelNode(&n_est, g, &n_ev1, 1, &kp);
+    ee::EstLaunch est[4];
+    const int n_est = ee_k_estimate_plan(count, P->max_n, est);
+    hipGraphNode_t last = n_ev1;
+    for (int i = 0; i < n_est && e == hipSuccess; ++i) {
+      kp.func = const_cast<void*>(est[i].fn);
+      kp.gridDim = dim3(est[i].gx, est[i].gy);
+      kp.blockDim = dim3(est[i].block);
+      kp.sharedMemBytes = 0;
+      kp.kernelParams = a_est;
+      hipGraphNode_t node;
+      e = hipGraphAddKernelNode(&node, g, &last, 1, &kp);
+      last = node;
+    }
     if (e == hipSuccess) e = hipGraphInstantiate(&P->exec, g, nullptr, nullptr, 0);
     if (e != hipSuccess) { delete P; return fail(EE_EHIP, "building the batch graph: %s", hipGetErrorString(e)); }
   }
@@ -715,7 +728,7 @@ ee_status run_plan(Plan* P, hipStream_t stream) {
                            ee::kFlagInit | ee::kFlagProto, P->n_therm, 0, P->grid, P->block, P->lds, stream);
     if (rc) return fail(EE_EHIP, "persistent sweep launch: %s", hipGetErrorString((hipError_t)rc));
     HIP_TRY(hipEventRecord(P->ev_stop, stream));
-    rc = ee_k_launch_estimate(P->dev_jobtab, (int)P->jobs.size(), stream);
+    rc = ee_k_launch_estimate(P->dev_jobtab, (int)P->jobs.size(), P->max_n, stream);
     if (rc) return fail(EE_EHIP, "estimator launch: %s", hipGetErrorString((hipError_t)rc));
   }
   return EE_OK;
@@ -892,7 +905,7 @@ ee_status ee_estimate(ee_job* job, ee_result* out) {
   if (!job || !out) return fail(EE_EINVAL, "NULL argument");
   if (job->state != DONE) return fail(EE_ESTATE, "ee_estimate before the protocol");
   if (!job->est_enqueued) {
-    int rc = ee_k_launch_estimate(job->dev_selfptr(), 1, job->stream);
+    int rc = ee_k_launch_estimate(job->dev_selfptr(), 1, job->d.n_traj, job->stream);
     if (rc) return fail(EE_EHIP, "estimator launch: %s", hipGetErrorString((hipError_t)rc));
     job->est_enqueued = true;
     job->est_stream = job->stream;
@@ -1057,7 +1070,7 @@ ee_status ee_batch_run_noalloc(ee_job* const* jobs, int32_t count, int32_t n_the
   if (rc == 0)
     rc = ee_k_launch_sweep(nullptr, 0, units, (int)up.units.size(), queue, jobtab, ee::kFlagInit | ee::kFlagProto,
                            n_therm, 0, up.grid, up.block, up.lds, stream);
-  if (rc == 0) rc = ee_k_launch_estimate(jobtab, count, stream);
+  if (rc == 0) rc = ee_k_launch_estimate(jobtab, count, max_traj(jobs, count), stream);
   if (rc) return fail(EE_EHIP, "allocation-free batch launch: %s", hipGetErrorString((hipError_t)rc));
   mark_batch_done(jobs, count, n_therm, stream);
   return EE_OK;
@@ -1269,7 +1282,7 @@ ee_status server_progress(ee_server* S) {
   if (!finished.empty()) {
     for (int id : finished) {
       ee_job* j = S->jobs[id].job;
-      const int rc = ee_k_launch_estimate(j->dev_selfptr(), 1, S->est_stream);
+      const int rc = ee_k_launch_estimate(j->dev_selfptr(), 1, j->d.n_traj, S->est_stream);
       if (rc) return fail(EE_EHIP, "server estimator launch: %s", hipGetErrorString((hipError_t)rc));
       // the job stays SERVED until a poll returns it
       j->spins_exist = true;
