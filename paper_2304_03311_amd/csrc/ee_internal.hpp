@@ -65,6 +65,8 @@ struct alignas(256) JobDev {
   // the signed order): the high bytes in pt[0], pt[1], the low ones in pt[2],
   // pt[3], as v_perm_b32 selects them.
   uint32_t pt[4];
+  int32_t lds_words;         // LDS words of a trajectory on chip
+  int32_t rag_W, rag_pitch;  // rows kept at their own pitch in LDS (ee_lanes.hpp: row_pitch); 0: as stored
   double beta;
   const uint32_t* ramp_thr;
   uint32_t* spins;

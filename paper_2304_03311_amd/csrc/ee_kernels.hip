@@ -117,7 +117,10 @@ __device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M&
   }
 #pragma unroll
   for (int q = 0; q < W; ++q) idx[0][q] = nbr_index<DIM>(S[0][q], A[q], B[q], Tm[q], Tp[q], Ym[q], Yp[q]);
-  decide_rows<DIM, W, 1, CUT>(P, U, &c0, c3, g, j, w, fmask, thr, S, idx, cr, pos, dpos, work, dI, Sn,
+  uint32_t fm[W];
+#pragma unroll
+  for (int q = 0; q < W; ++q) fm[q] = fmask;
+  decide_rows<DIM, W, 1, CUT>(P, U, &c0, c3, g, j, w, fm, thr, S, idx, cr, pos, dpos, work, dI, Sn,
                               [&](int, uint32_t* Tc, uint32_t* Tg) {
                                 ld_words<W>(mem, at(toff0), Tc);
                                 ld_words<W>(gmem, ag, Tg);
@@ -237,8 +240,34 @@ __device__ __forceinline__ uint32_t edge_word(const uint32_t A[W]) {
 // the lane's glued_bits in its rows next to the cut (0 if it has none), of
 // word q and x parity p moved to bit 4 p + q of each byte.  has_ramp: these
 // rows hold the ramped site.
-template <int DIM, int W, int GW, int C>
-__device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp, const PmPos& pp, const uint32_t base,
+// RAG: rows with pad sites (row_pitch; P.G is the pitch), whose lanes have
+// what RagLane says.
+struct RagLane {
+  uint32_t fm[4];    // bit 0 of every real site's byte, per word
+  uint32_t e_shift;  // brings the last site of the row to the top byte (first lane; 0 elsewhere)
+  uint32_t last;     // 0xFF in the lane that holds the row's last site, 0 elsewhere
+  int wl, wr;        // words that hold the left and right edge neighbour
+};
+template <int W>
+__device__ __forceinline__ RagLane rag_lane(int H, int w) {
+  RagLane r;
+  const int wl = (H - 1) >> 2;  // word of the row's last site
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int n = H - 4 * (w + q);
+    r.fm[q] = (q >= W || n <= 0) ? 0u : 0x01010101u >> (n >= 4 ? 0 : 32 - 8 * n);
+  }
+  const bool last = wl >= w && wl < w + W;
+  r.e_shift = (w == 0) ? 8u * (3 - ((H - 1) & 3)) : 0u;
+  r.last = last ? 0xFFu : 0u;
+  r.wl = (w == 0) ? wl : w - 1;
+  r.wr = last ? 0 : w + W;
+  return r;
+}
+
+template <int DIM, int W, int GW, int C, bool RAG = false>
+__device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp, const PmPos& pp, const RagLane& rl,
+                                        const uint32_t base,
                                         const uint32_t* __restrict__ thr, const uint32_t ones, const uint32_t g,
                                         const uint32_t j, const int pos, const int dpos, const bool work, int& dI,
                                         const bool has_cut, const uint32_t cut_mask, const bool has_ramp) {
@@ -252,7 +281,42 @@ __device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp,
   const uint32_t c3 = lp.c3 | (uint32_t)C;
   K.x0 = c3 ^ P.key1;
   const uint32_t bO = base + (uint32_t)(C ? 0 : cw4);
-  const int e0 = 4 * ((C ? lp.wr : lp.wl) - lp.w), e1 = 4 * ((C ? lp.wl : lp.wr) - lp.w);
+  const int wl = RAG ? rl.wl : lp.wl, wr = RAG ? rl.wr : lp.wr;
+  const int e0 = 4 * ((C ? wr : wl) - lp.w), e1 = 4 * ((C ? wl : wr) - lp.w);
+  uint32_t fm[W];
+#pragma unroll
+  for (int q = 0; q < W; ++q) fm[q] = RAG ? rl.fm[q] : ones;
+  // x neighbours of a row of parity p
+  const auto x_row = [&](auto par, const uint32_t A[W], uint32_t E, uint32_t B[W]) {
+    constexpr int PAR = decltype(par)::value;
+    if constexpr (!RAG) {
+      x_words<W, PAR>(A, E, PAR, B);
+    } else {
+      // E: a word whose top byte (p = 0, after the shift) is the left
+      // neighbour of the first site, or whose bottom byte is the right one of
+      // the last site: beyond the last real site of the row it takes the place
+      // of the pad byte
+      uint32_t A2[W];
+#pragma unroll
+      for (int q = 0; q < W; ++q) A2[q] = A[q];
+      if (GW == 1) {
+        uint32_t Ew = A[0];
+#pragma unroll
+        for (int q = 1; q < W; ++q)
+          if (PAR == 0 && q == ((P.H - 1) >> 2)) Ew = A[q];
+        E = Ew;
+      }
+      if (PAR == 0) {
+        E <<= rl.e_shift;
+      } else {
+        const uint32_t in = (E & rl.last) << (8 * (P.H & 3));
+#pragma unroll
+        for (int q = 0; q < W; ++q)
+          if (q == ((P.H >> 2) & (W == 3 ? 3 : W - 1))) A2[q] |= in;
+      }
+      x_words<W, PAR>(A2, E, PAR, B);
+    }
+  };
   // The two row locations and the counter are opaque to the compiler at each
   // step (the empty asm statement emits nothing): every access is then one
   // register plus at most one offset, instead of one induction variable per
@@ -310,8 +374,8 @@ __device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp,
     }
     if constexpr (GW == 0) { E0 = ld_word(mem, aO + (uint32_t)e0); E1 = ld_word(mem, aO1 + (uint32_t)e1); }
     fields_of_row<W>(K, cc[0], U);
-    if constexpr (GW != 0) { E0 = edge_word<W, C, GW>(A0); E1 = edge_word<W, C ^ 1, GW>(A1); }
-    x_words<W, C>(A0, E0, C, B0);
+    if constexpr (GW != 0 && !RAG) { E0 = edge_word<W, C, GW>(A0); E1 = edge_word<W, C ^ 1, GW>(A1); }
+    x_row(std::integral_constant<int, C>{}, A0, E0, B0);
     if constexpr (DIM == 2) {
 #pragma unroll
       for (int q = 0; q < W; ++q) T1[q] = A1[q];
@@ -336,7 +400,7 @@ __device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp,
       ld_words<W>(mem, aO + 4u * (uint32_t)pp.yo[1], Y);
     }
     fields_of_row<W>(K, cc[1], U + (W + 1) / 2);
-    x_words<W, C ^ 1>(A1, E1, C ^ 1, B1);
+    x_row(std::integral_constant<int, C ^ 1>{}, A1, E1, B1);
     if constexpr (DIM == 2) {
 #pragma unroll
       for (int q = 0; q < W; ++q) T1[q] = A0[q];
@@ -351,7 +415,7 @@ __device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp,
     }
 #pragma unroll
     for (int q = 0; q < W; ++q) idx[1][q] = nbr_index<DIM>(S[1][q], A1[q], B1[q], T0[q], T1[q], A0[q], Y[q]);
-    decide_rows<DIM, W, 2, CUT>(P, U, cc, c3, g, j, w, ones, thr, S, idx, cr, pos, dpos, work, dI, Sn,
+    decide_rows<DIM, W, 2, CUT>(P, U, cc, c3, g, j, w, fm, thr, S, idx, cr, pos, dpos, work, dI, Sn,
                                 [&](int r, uint32_t* Tc, uint32_t* Tg) {
                                   ld_words<W>(mem, (r ? aO : aO1) + ((DIM == 3) ? tc : 0u), Tc);
                                   ld_words<W>(mem, bO + 4u * (uint32_t)(r ? og1 : og0), Tg);
@@ -370,9 +434,9 @@ __device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp,
 }
 
 // Initial spins (phase 0 of the Philox streams): +1 iff u < 2^31.  PM: into
-// the class-by-class rows of the parity-major order.
+// the class-by-class rows of the parity-major order, pitch words each.
 template <bool PM, typename M>
-__device__ void init_spins(const JP& P, const M& mem, uint32_t base, uint32_t j, int lt_, int T) {
+__device__ void init_spins(const JP& P, const M& mem, uint32_t base, uint32_t j, int lt_, int T, int pitch) {
   const int nR = P.n * P.R;
   for (int q = lt_; q < P.traj_words; q += T) {
     const int w = q % P.G;
@@ -387,7 +451,7 @@ __device__ void init_spins(const JP& P, const M& mem, uint32_t base, uint32_t j,
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (4 * w + i < P.H) word |= (uint32_t)(u[i] < 0x80000000u) << (8 * i);
-    const int at = PM ? (rowg - rho + pm_row(P, rho)) * P.G + w : q;
+    const int at = PM ? (rowg - rho + pm_row(P, rho)) * pitch + w : q;
     st_words<1>(mem, base + 4u * (uint32_t)at, &word);
   }
 }
@@ -401,7 +465,7 @@ __device__ __forceinline__ int lds_row(const JP& P, int rowg) {
 }
 
 template <bool PM>
-__device__ void load_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T) {
+__device__ void load_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T, int pitch) {
   const LdsMem mem;
   const bool int8 = P.spin_format == EE_SPINS_INT8;
   const int PW = P.packed_row_words;
@@ -416,18 +480,18 @@ __device__ void load_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int 
       const uint32_t nib = (src[rowg * PW + (w >> 3)] >> (4 * (w & 7))) & 0xFu;
       word = (nib * 0x00204081u) & 0x01010101u;  // 4 bits -> 4 bytes
     }
-    st_words<1>(mem, base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * P.G + w), &word);
+    st_words<1>(mem, base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * pitch + w), &word);
   }
 }
 
 template <bool PM>
-__device__ void store_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T) {
+__device__ void store_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T, int pitch) {
   const LdsMem mem;
   if (P.spin_format == EE_SPINS_INT8) {
     uint32_t* dst = P.spins + (size_t)j * P.traj_words;
     for (int q = lt_; q < P.traj_words; q += T) {
       const int rowg = q / P.G;
-      dst[q] = ld_word(mem, base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * P.G + q - rowg * P.G));
+      dst[q] = ld_word(mem, base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * pitch + q - rowg * P.G));
     }
   } else {
     const int PW = P.packed_row_words;
@@ -436,7 +500,7 @@ __device__ void store_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int
     for (int q = lt_; q < total; q += T) {
       const int rowg = q / PW;
       const int wb = q - rowg * PW;
-      const uint32_t row = base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * P.G);
+      const uint32_t row = base + 4u * (uint32_t)(lds_row<PM>(P, rowg) * pitch);
       uint32_t packed = 0;
       for (int k = 0; k < 8; ++k) {
         const int w = 8 * wb + k;
@@ -457,11 +521,16 @@ constexpr int kTabUnit = 0, kTabWork = 4, kTabThr = 4 + ee::kMaxSlots;
 // lives for milliseconds): its registers are allocated for this variant
 // alone.  Inlined into one kernel, the variants' uniform values shared 100
 // scalar registers and 1250 of them were spilled.
-template <int DIM, bool FULL, int W, bool PM, int GW = 0>
-__device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t tab, int T_, int pm_, int j0_,
+template <int DIM, bool FULL, int W, bool PM, int GW = 0, bool RAG = false>
+__device__ __noinline__ void run_unit(const JobDev* J_, uint32_t lds, uint32_t tab, int T_, int pm_, int j0_,
                                       int cnt_, uint32_t flags_, int n_therm_, int g0_) {
-  static_assert(!PM || FULL, "the parity-major order needs rows of whole words");
-  const JP P = load_jp(uni_ptr(J));
+  static_assert(!PM || FULL || RAG, "the parity-major order needs rows of whole words");
+  const JobDev* const J = uni_ptr(J_);
+  const JP P = load_jp(J);
+  const int pitch = RAG ? uni(J->rag_pitch) : P.G;
+  const int slot_words = uni(J->lds_words);
+  JP PP = P;  // the rows as they lie in LDS
+  PP.G = pitch;
   const int T = uni(T_), j0 = uni(j0_), cnt = uni(cnt_), n_therm = uni(n_therm_);
   const uint32_t flags = uni(flags_);
   lds = uni(lds);
@@ -473,14 +542,21 @@ __device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t ta
   const int slot = tid / T;
   const int lt_ = tid - slot * T;
   const bool active = slot < cnt;
-  const uint32_t L = lds + 4u * (uint32_t)(slot * P.traj_words);
+  const uint32_t L = lds + 4u * (uint32_t)(slot * slot_words);
   // one trajectory per wave or more: its index is uniform
   const uint32_t j = ((T & 63) == 0) ? uni((uint32_t)(j0 + slot)) : (uint32_t)(j0 + slot);
   if (tid < ee::kMaxSlots) s_dI[tid] = 0;
   if (tid < 8) s_thr[tid] = thr_entry(P, DIM, tid);
   if (active) {
-    if (flags & ee::kFlagInit) init_spins<PM>(P, mem, L, j, lt_, T);
-    else load_spins<PM>(P, L, j, lt_, T);
+    if (pitch != P.G) {  // the pad words
+      const uint32_t zero = 0;
+      for (int q = lt_; q < 2 * P.n * P.R * pitch; q += T) st_words<1>(mem, L + 4u * (uint32_t)q, &zero);
+    }
+  }
+  if (pitch != P.G) __syncthreads();
+  if (active) {
+    if (flags & ee::kFlagInit) init_spins<PM>(P, mem, L, j, lt_, T, pitch);
+    else load_spins<PM>(P, L, j, lt_, T, pitch);
   }
   PhKey K;
   key_unit(K, P);
@@ -505,9 +581,10 @@ __device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t ta
     }
   };
   if constexpr (PM) {
-    LanePM lp = make_lane_pm<DIM, W>(P, lt_, uni(pm_));
+    LanePM lp = make_lane_pm<DIM, W>(PP, lt_, uni(pm_));
     const bool has_cut = __builtin_amdgcn_ballot_w64(lp.t <= 1) != 0;
-    const PmPos pp = make_pm_pos<DIM>(P, lp);
+    const PmPos pp = make_pm_pos<DIM>(PP, lp);
+    const RagLane rl = RAG ? rag_lane<W>(P.H, lp.w) : RagLane{};
     uint32_t cut_mask = 0;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
@@ -520,9 +597,9 @@ __device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t ta
     if (!active) lp.t = P.lt;  // no rows
     sweeps([&](int pos, int dpos, bool in_proto) {
       key_sweep(K, P, g, j);
-      rows_pm<DIM, W, GW, 0>(P, K, lp, pp, L, s_thr, ones, g, j, pos, dpos, in_proto, dI, has_cut, cut_mask, has_ramp);
+      rows_pm<DIM, W, GW, 0, RAG>(PP, K, lp, pp, rl, L, s_thr, ones, g, j, pos, dpos, in_proto, dI, has_cut, cut_mask, has_ramp);
       __syncthreads();
-      rows_pm<DIM, W, GW, 1>(P, K, lp, pp, L, s_thr, ones, g, j, pos, dpos, false, dI, has_cut, cut_mask, has_ramp);
+      rows_pm<DIM, W, GW, 1, RAG>(PP, K, lp, pp, rl, L, s_thr, ones, g, j, pos, dpos, false, dI, has_cut, cut_mask, has_ramp);
       __syncthreads();
     });
   } else {
@@ -576,7 +653,7 @@ __device__ __noinline__ void run_unit(const JobDev* J, uint32_t lds, uint32_t ta
     __syncthreads();
     if (active && lt_ == 0) P.work[j] = (int64_t)s_dI[slot];
   }
-  if (active) store_spins<PM>(P, L, j, lt_, T);
+  if (active) store_spins<PM>(P, L, j, lt_, T, pitch);
   __syncthreads();
 }
 
@@ -590,7 +667,23 @@ __device__ __forceinline__ void run_unit_dispatch(const JobDev* J, uint32_t lds,
   P.n = uni(J->n); P.ly = uni(J->ly); P.H = uni(J->H); P.G = uni(J->G); P.R = uni(J->R);
   const int T = blockDim.x / kslots;
   const int W = words_per_lane(P, T);
-  const int pm = pm_lanes(P, T, W);
+  if (const int rp = uni(J->rag_pitch)) {
+    // rows with pad sites: in parity-major order, or lane by word as below
+    const int rW = uni(J->rag_W), G = P.G;
+    P.G = rp;
+    const int pm = pm_lanes(P, T, rW);
+    const bool one = rp == rW;
+#define EE_RAG(...) return run_unit<DIM, false, __VA_ARGS__, true>(J, lds, tab, T, pm, j0, cnt, flags, n_therm, g0)
+    if (pm && rW == 4 && one) EE_RAG(4, true, 1);
+    if (pm && rW == 4) EE_RAG(4, true, 0);
+    if (pm && rW == 3) EE_RAG(3, true, 1);
+    if (pm && rW == 2 && one) EE_RAG(2, true, 1);
+    if (pm && rW == 2) EE_RAG(2, true, 0);
+    if (pm) EE_RAG(1, true, 0);
+#undef EE_RAG
+    P.G = G;
+  }
+  const int pm = (P.H & 3) == 0 ? pm_lanes(P, T, W) : 0;
   // lanes per row, where the row's edge words come from registers (a pair of
   // lanes only if the slot's lanes start at an even lane)
   const int gw = P.G / W;
@@ -1119,7 +1212,7 @@ __global__ void __launch_bounds__(256) stream_init_kernel(const JobDev* J, int l
   const JP P = load_jp(J);
   const uint32_t j = blockIdx.y;
   const int lt_ = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lt_ < lanes) init_spins<false>(P, HbmMem{P.spins + (size_t)j * P.traj_words}, 0u, j, lt_, lanes);
+  if (lt_ < lanes) init_spins<false>(P, HbmMem{P.spins + (size_t)j * P.traj_words}, 0u, j, lt_, lanes, P.G);
 }
 
 __global__ void zero_work_kernel(const JobDev* J) {

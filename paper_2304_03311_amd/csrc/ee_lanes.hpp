@@ -287,9 +287,9 @@ EE_HDI bool use_pm(const JP& P, int T, int W) {
 // of the unit go in lane-map order: as use_pm, but where ly does not divide
 // the B row slots per replica (3D), as many as it does; the other lanes stay
 // idle.  24^3 with 512 lanes: B = 256 -> 240, two steps of two rows per
-// half-sweep instead of five single rows in lane-map order.
+// half-sweep instead of five single rows in lane-map order.  P.G is the row
+// pitch, a multiple of W.
 EE_HDI int pm_lanes(const JP& P, int T, int W) {
-  if ((P.H & 3) != 0) return 0;
   const int GW = P.G / W;
   const int S = T / GW;
   if (S < P.n) return 0;
@@ -297,6 +297,28 @@ EE_HDI int pm_lanes(const JP& P, int T, int W) {
   if (P.dim == 3 && B > P.ly) B -= B % P.ly;
   const int lanes = (P.dim == 3) ? B * P.n * GW : T;
   return use_pm(P, lanes, W) ? lanes : 0;
+}
+
+// Rows whose words do not split evenly into lanes of several words (lx/2 not
+// a multiple of 4, or an odd word count) are kept in LDS at a pitch of a
+// multiple of the lane's W words; the last lane of a row then has pad sites,
+// which never flip.  W by the instructions of a pair of rows: about 105, 165,
+// 250 and 300 for lanes of 1 to 4 words (3 only where a row is one lane: its
+// Philox calls serve two words each).  22 sites in x: one lane of three words
+// instead of three of one, 250 instructions against 315, and one edge.
+struct RowPitch {
+  int W, pitch;  // words per lane; words per row in LDS, 0: as stored
+};
+EE_HDI RowPitch row_pitch(int H, int G) {
+  const auto cost = [&](int W) { return (G + W - 1) / W * (W == 4 ? 300 : W == 3 ? 250 : W == 2 ? 165 : 105); };
+  // what words_per_lane takes for whole rows (1 where lx/2 is no multiple of 4)
+  const int plain = (H & 15) == 0 ? 4 : H == 12 ? 3 : (H & 7) == 0 ? 2 : 1;
+  if ((H & 3) == 0 && G % plain == 0 && plain > 1) return RowPitch{plain, 0};
+  int W = 1;
+  for (int v = 2; v <= 4; ++v)
+    if ((v != 3 || G <= 3) && cost(v) < cost(W)) W = v;
+  if (W == 1 && (H & 3) == 0) return RowPitch{1, 0};
+  return RowPitch{W, (G + W - 1) / W * W};
 }
 
 }  // namespace lanes

@@ -358,7 +358,7 @@ __device__ __forceinline__ void fields_of_row(const PhKey& K, const uint32_t c0,
 //   S, idx  the spins and neighbour indices; Sn gets the new spins
 //   c0, c3  Philox counter words 0 (of each row's first call) and 3
 //   w       first word of the lane in its rows;  fmask: bit 0 of every real
-//           site's byte
+//           site's byte, per word
 //   thr     LDS table of full thresholds by neighbour index
 //   cr      rows next to the cut (CUT only)
 //   pos, dpos, work, dI  protocol position, its step (0 while thermalising),
@@ -370,7 +370,7 @@ __device__ __forceinline__ void fields_of_row(const PhKey& K, const uint32_t c0,
 template <int DIM, int W, int NR, bool CUT, typename Partners>
 __device__ __forceinline__ void decide_rows(const JP& P, const uint32_t U[NR * ((W + 1) / 2)][4],
                                             const uint32_t c0[NR], const uint32_t c3, const uint32_t g,
-                                            const uint32_t j, const int w, const uint32_t fmask,
+                                            const uint32_t j, const int w, const uint32_t fmask[W],
                                             const uint32_t* __restrict__ thr, const uint32_t S[NR][W],
                                             const uint32_t idx[NR][W], const CutRow<W>* cr, const int pos,
                                             const int dpos, const bool work, int& dI, uint32_t Sn[NR][W],
@@ -536,7 +536,7 @@ __device__ __forceinline__ void decide_rows(const JP& P, const uint32_t U[NR * (
 #pragma unroll
   for (int r = 0; r < NR; ++r)
 #pragma unroll
-    for (int q = 0; q < W; ++q) Sn[r][q] = __builtin_amdgcn_bitop3_b32(S[r][q], f[r][q], fmask, 0x78);
+    for (int q = 0; q < W; ++q) Sn[r][q] = __builtin_amdgcn_bitop3_b32(S[r][q], f[r][q], fmask[q], 0x78);
 }
 
 }  // namespace

@@ -53,6 +53,7 @@ enum State { CREATED = 0, SERVED = 1, DONE = 2 };  // SERVED: submitted to a ser
 struct Layout {
   size_t off_jobdev, off_selfptr, off_result, off_ramp, off_work, off_spins, total;
   int H, G, R, traj_words, packed_words;
+  int rag_W, rag_pitch, lds_words;  // rows at a pitch of their own in LDS (0: as stored); LDS words of a trajectory
   size_t storage_words_per_traj;
 };
 
@@ -112,6 +113,16 @@ Layout layout_of(const ee_job_desc* d) {
   L.R = d->lt * d->ly;
   L.traj_words = 2 * d->n_replicas * L.R * L.G;
   L.packed_words = 2 * d->n_replicas * L.R * ((L.H + 31) / 32);
+  const ee::lanes::RowPitch rp = ee::lanes::row_pitch(L.H, L.G);
+  L.lds_words = L.traj_words;
+  if (rp.pitch > 0) {
+    const long words = 2L * d->n_replicas * L.R * rp.pitch;
+    if (words * 4 <= ee_k_max_lds_bytes() && (rp.pitch + 63) / 64 * 64 <= 1024) {
+      L.rag_W = rp.W;
+      L.rag_pitch = rp.pitch;
+      L.lds_words = (int)words;
+    }
+  }
   L.storage_words_per_traj =
       (d->spin_format == EE_SPINS_INT8) ? (size_t)L.traj_words : (size_t)L.packed_words;
   size_t off = 0;
@@ -182,15 +193,28 @@ JP_shape shape_of(const ee_job_desc& d, const Layout& L) {
   JP_shape P{};
   P.dim = d.dim; P.n = d.n_replicas; P.ly = d.ly; P.lt = d.lt;
   P.H = L.H; P.G = L.G; P.R = L.R;
+  P.traj_words = L.rag_pitch;  // half_sweep_instr: the pitch and words per lane of rows with pad sites
+  P.packed_row_words = L.rag_W;
   return P;
 }
 
 // Instructions per wave of one half-sweep of a trajectory on T lanes.
 double half_sweep_instr(const JP_shape& P, int T) {
-  const int W = ee::lanes::words_per_lane(P, T);
-  const int GW = P.G / W;
+  int W = ee::lanes::words_per_lane(P, T);
   const double y = (P.dim == 3) ? 20.0 : 0.0;  // the two more neighbours
-  if (const int lanes = ee::lanes::pm_lanes(P, T, W)) {
+  int lanes = (P.H & 3) == 0 ? ee::lanes::pm_lanes(P, T, W) : 0;
+  int GW = P.G / W;
+  if (P.traj_words > 0) {  // rows with pad sites: traj_words holds their pitch
+    JP_shape Q = P;
+    Q.G = P.traj_words;
+    const int rW = P.packed_row_words;
+    if (const int n = ee::lanes::pm_lanes(Q, T, rW)) {
+      lanes = n;
+      W = rW;
+      GW = Q.G / rW;
+    }
+  }
+  if (lanes) {
     const int B = lanes / GW / P.n;
     const int steps = (P.R / 2 + B - 1) / B;
     const double step = (W == 4 ? 300.0 : W == 3 ? 250.0 : W == 2 ? 165.0 : 105.0) + y;
@@ -212,7 +236,7 @@ struct Shape {
 // The shape for n_traj trajectories (of one job, or of equal jobs together).
 Shape launch_shape(const ee_job_desc& d, const Layout& L, long n_traj) {
   const JP_shape P = shape_of(d, L);
-  const int tb = L.traj_words * 4;
+  const int tb = L.lds_words * 4;
   const int cus = device_info().cus;
   const long words = (long)d.n_replicas * L.R * L.G;
   Shape best{std::max(64, min_block(L)), 1, 1e300};
@@ -245,7 +269,7 @@ Shape launch_shape(const ee_job_desc& d, const Layout& L, long n_traj) {
 // min_groups > 0 (per-job launches): keep at least that many workgroups so
 // that one job alone fills the GPU.
 int choose_slots(const Layout& L, int n_rep, int block, int lds_budget, int n_traj, int min_groups = 0) {
-  const int traj_bytes = L.traj_words * 4;
+  const int traj_bytes = L.lds_words * 4;
   int kmax = std::min(ee::kMaxSlots, std::max(1, lds_budget / traj_bytes));
   kmax = std::min(kmax, std::max(1, block / L.G));
   kmax = std::min(kmax, std::max(1, n_traj));
@@ -467,11 +491,11 @@ ee_status launch_sweep_for_job(ee_job* j, uint32_t flags, int n_therm) {
     block = std::max(j->cfg.block_threads > 0 ? j->cfg.block_threads : launch_shape(j->d, j->L, j->d.n_traj).block,
                      min_block(j->L));
     const int budget = j->cfg.lds_bytes > 0 ? j->cfg.lds_bytes : kDefaultLdsBudget;
-    k = choose_slots(j->L, j->d.n_replicas, block, std::max(budget, j->L.traj_words * 4), j->d.n_traj,
+    k = choose_slots(j->L, j->d.n_replicas, block, std::max(budget, j->L.lds_words * 4), j->d.n_traj,
                      2 * device_info().cus);
   }
   const int grid = (j->d.n_traj + k - 1) / k;
-  const int lds = k * j->L.traj_words * 4;
+  const int lds = k * j->L.lds_words * 4;
   const int rc = ee_k_launch_sweep(j->dev_jobdev(), k, nullptr, 0, nullptr, nullptr, flags, n_therm, (int)j->g, grid,
                                    block, lds, j->stream);
   if (rc != 0) return fail(EE_EHIP, "sweep kernel launch failed: %s", hipGetErrorString((hipError_t)rc));
@@ -506,7 +530,7 @@ int launch_block(ee_job* const* jobs, int count, const ee_launch_cfg& cfg, int* 
     if (i > 0 && same_lattice(jobs[i], jobs[i - 1])) continue;
     const Shape sh = launch_shape(jobs[i]->d, jobs[i]->L, n_traj);
     block = std::max(block, sh.block);
-    *lds = std::max(*lds, sh.k * jobs[i]->L.traj_words * 4);
+    *lds = std::max(*lds, sh.k * jobs[i]->L.lds_words * 4);
   }
   if (cfg.block_threads > 0) block = cfg.block_threads;
   for (int i = 0; i < count; ++i) block = std::max(block, min_block(jobs[i]->L));
@@ -517,7 +541,7 @@ int launch_block(ee_job* const* jobs, int count, const ee_launch_cfg& cfg, int* 
 // trajectory of every job.
 int lds_budget(ee_job* const* jobs, int count, const ee_launch_cfg& cfg) {
   int budget = cfg.lds_bytes > 0 ? cfg.lds_bytes : kDefaultLdsBudget;
-  for (int i = 0; i < count; ++i) budget = std::max(budget, jobs[i]->L.traj_words * 4);
+  for (int i = 0; i < count; ++i) budget = std::max(budget, jobs[i]->L.lds_words * 4);
   return budget;
 }
 
@@ -535,7 +559,7 @@ int auto_slots(const ee_job* j, int block, int lds) {
   int best = 1;
   double rate = 0.0;
   for (int k = 1; k <= ee::kMaxSlots && k <= j->d.n_traj; ++k) {
-    if (k * j->L.traj_words * 4 > lds || block / k < j->L.G) break;
+    if (k * j->L.lds_words * 4 > lds || block / k < j->L.G) break;
     const double r = k / half_sweep_instr(P, block / k);
     if (r > rate * 1.02) { rate = r; best = k; }
   }
@@ -575,7 +599,7 @@ ee_status plan_units(ee_job* const* jobs, int count, int n_therm, const ee_launc
     ee_job* j = jobs[i];
     const int k = automatic ? auto_slots(j, out->block, lds_auto)
                             : choose_slots(j->L, j->d.n_replicas, out->block, budget, j->d.n_traj);
-    lds_need = std::max(lds_need, k * j->L.traj_words * 4);
+    lds_need = std::max(lds_need, k * j->L.lds_words * 4);
     const double cost = unit_cost(j, out->block, k, n_therm);
     for (int j0 = 0; j0 < j->d.n_traj; j0 += k)
       units.push_back({ee::Unit{i, j0, std::min(k, j->d.n_traj - j0), k}, cost});
@@ -804,6 +828,7 @@ ee_status ee_job_create(const ee_job_desc* desc, void* dev_arena, size_t arena_b
   D.l = desc->l; D.N = N; D.n_traj = desc->n_traj;
   D.H = j->L.H; D.G = j->L.G; D.R = j->L.R; D.traj_words = j->L.traj_words;
   D.packed_words = j->L.packed_words;
+  D.lds_words = j->L.lds_words; D.rag_W = j->L.rag_W; D.rag_pitch = j->L.rag_pitch;
   D.key0 = (uint32_t)(desc->seed & 0xFFFFFFFFu);
   D.key1 = (uint32_t)(desc->seed >> 32);
   D.S = S;
@@ -1241,7 +1266,7 @@ ee_status server_launch(ee_server* S, SrvSlot& sl) {
     }
     sl.per_job[it->second].second += 1;
     units[i] = ee::Unit{it->second, u.j0, u.count, u.k};
-    lds = std::max(lds, u.k * sj.job->L.traj_words * 4);
+    lds = std::max(lds, u.k * sj.job->L.lds_words * 4);
   }
   int grid = 0;
   ee_status s = persistent_grid(block, lds, take, S->cfg, &grid);
@@ -1387,7 +1412,7 @@ ee_status ee_server_submit(ee_server* S, ee_job* job) {
   s = server_class(S, job, &C);
   if (s) return s;
   const int block = std::max(C->block, min_block(job->L));
-  const int k = choose_slots(job->L, job->d.n_replicas, block, std::max(C->budget, job->L.traj_words * 4),
+  const int k = choose_slots(job->L, job->d.n_replicas, block, std::max(C->budget, job->L.lds_words * 4),
                              job->d.n_traj);
   const double cost = unit_cost(job, block, k, S->n_therm);
   hipEvent_t ev = nullptr;

@@ -51,3 +51,20 @@ def test_slots_with_idle_lanes_match_oracle(block):
     # rows in parity-major order; 1024 lanes 504 of 512
     check(ee.JobSpec(dim=3, lt=24, lx=24, ly=24, n=2, beta=BC3, l=7, n_step=3, n_traj=3, seed=92, reverse=True),
           dict(block_threads=block, lds_bytes=28672))
+
+
+# Rows whose words do not fill their lanes: pad sites, the edge neighbours of
+# the first and last lane, glued and ramped columns in the last word.  64 and
+# 192 lanes per trajectory hold fewer row slots than rows, so the rows go in
+# parity-major order.
+@pytest.mark.parametrize("block", [64, 192])
+@pytest.mark.parametrize("lx", [2, 6, 10, 14, 18, 20, 22, 26, 30, 34, 40, 44, 50, 56, 58, 62, 100])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_rows_with_pad_sites_match_oracle(dim, lx, block):
+    kw = dict(dim=2, lt=200, ly=1, beta=BC2, n_step=4) if dim == 2 else dict(dim=3, lt=14, ly=10, beta=BC3, n_step=10)
+    for k, opts in enumerate((dict(l=lx - 1), dict(l=lx // 2, reverse=True, spin_format=1), dict(l=lx, whole=True),
+                              dict(l=max(1, lx - 3), n=3, subsets=dim == 3))):
+        s = ee.JobSpec(lx=lx, n_traj=2, seed=200 + 4 * lx + k, **{"n": 2, **kw, **opts, "l": min(
+            opts["l"], lx if opts.get("whole") else lx - 1)})
+        if 2 * s.n * s.lt * s.ly * -(-lx // 8) * 4 <= 160 * 1024 - 256:
+            check(s, dict(block_threads=block, lds_bytes=1024), n_therm=1)
