@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libee.so")
-SOURCES = ["ee_kernels.hip", "ee_runtime.cpp"]
+SOURCES = ["ee_sweep.hip", "ee_sweep_whole.hip", "ee_kernels.hip", "ee_runtime.cpp"]
 ARCH = os.environ.get("EE_OFFLOAD_ARCH", "gfx950")
 
 # -ffp-contract=off: the host-built Metropolis thresholds must evaluate
@@ -33,7 +33,7 @@ def source_hash() -> str:
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tag = f"-DEE_SOURCE_HASH=\"{source_hash()}\""
-    # the sources compile in parallel (the kernel file takes minutes)
+    # the sources compile in parallel (the kernel files take minutes)
     procs = []
     objs = []
     for src in SOURCES:

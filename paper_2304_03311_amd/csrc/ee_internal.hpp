@@ -97,12 +97,14 @@ inline Magic make_magic(uint32_t d) {
 
 // Launch helpers implemented in ee_kernels.hip.
 extern "C" {
-int ee_k_launch_sweep(const ee::JobDev* single_job, int single_k, const ee::Unit* units, int n_units, int* queue,
-                      const ee::JobDev* const* jobtab, uint32_t flags, int n_therm, int g0, int grid, int block,
-                      int lds_bytes, void* stream);
+int ee_k_launch_sweep(int whole, const ee::JobDev* single_job, int single_k, const ee::Unit* units, int n_units,
+                      int* queue, const ee::JobDev* const* jobtab, uint32_t flags, int n_therm, int g0, int grid,
+                      int block, int lds_bytes, void* stream);
 int ee_k_launch_queue_reset(int* queue, void* stream);
 int ee_k_launch_estimate(const ee::JobDev* const* jobtab, int count, int max_n, void* stream);
-int ee_k_sweep_kernel_ptr(const void** fn);
+int ee_k_sweep_kernel_ptr(int whole, const void** fn);
+int ee_k_sweep_plain_ptr(const void** fn);
+int ee_k_sweep_whole_ptr(const void** fn);
 int ee_k_queue_reset_ptr(const void** fn);
 int ee_k_estimate_plan(int count, int max_n, ee::EstLaunch out[4]);
 int ee_k_max_lds_bytes();

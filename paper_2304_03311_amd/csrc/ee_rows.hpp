@@ -12,8 +12,17 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "ee_internal.hpp"
 #include "ee_lanes.hpp"
+
+// Whether the whole-region protocol is compiled in.  Its code takes registers
+// from the rows next to the cut in every protocol, so the on-chip kernel
+// exists without it and with it.
+#ifndef EE_WHOLE
+#define EE_WHOLE 1
+#endif
 
 namespace {
 
@@ -35,7 +44,7 @@ __device__ __forceinline__ JP load_jp(const JobDev* J) {
   JP P;
   P.dim = uni(J->dim);
   P.n = uni(J->n); P.lt = uni(J->lt); P.ly = uni(J->ly); P.l = uni(J->l); P.N = uni(J->N);
-  P.S = uni(J->S); P.subsets = uni(J->subsets); P.whole = uni(J->whole);
+  P.S = uni(J->S); P.subsets = uni(J->subsets); P.whole = EE_WHOLE ? uni(J->whole) : 0;
   P.H = uni(J->H); P.G = uni(J->G); P.R = uni(J->R); P.traj_words = uni(J->traj_words);
   P.G8 = (P.H + 7) >> 3;
   P.packed_row_words = (P.H + 31) >> 5;
@@ -499,35 +508,42 @@ __device__ __forceinline__ void decide_rows(const JP& P, const uint32_t U[NR * (
         uint32_t Tc[W], Tg[W], gm[W];
         partners(r, Tc, Tg);
         glued_bits<W>(P, true, cr[r].p, w, gm);
+        // word by word: the four sites' thresholds first (sites that are not
+        // ramped read one too), so that their loads are in flight together
 #pragma unroll
         for (int q = 0; q < W; ++q) {
-          const uint32_t rm = gm[q];  // sites with x < l
-          if (rm == 0) continue;
+          if (gm[q] == 0) continue;
           const uint32_t bw = Tc[q] ^ S[r][q];  // intra partner anti-aligned (bit 0 of each byte)
           const uint32_t cw = Tg[q] ^ S[r][q];  // inter partner anti-aligned
           const uint32_t fw = anti_count<DIM>(idx[r][q], S[r][q]) - bw;  // the 2 dim - 1 fixed neighbours
+          const uint32_t at = 4u * fw + 2u * bw + cw;                     // table index per byte
+          uint32_t Uw[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (!((rm >> (8 * i)) & 1u)) continue;
-            const uint32_t fa = (fw >> (8 * i)) & 0xFFu;
-            const uint32_t bb = (bw >> (8 * i)) & 1u;
-            const uint32_t cc = (cw >> (8 * i)) & 1u;
-            const uint32_t Uw = Um[fa * 4 + bb * 2 + cc];
-            const int o = ((ob + 2 * q) & 3) + (i >> 1);
-            const uint32_t vr = half16(pick4(U[r * NC + (q >> 1)], o), i & 1) ^ 0x8000u;
-            bool acc = vr < (Uw >> 16);
-            if (vr == (Uw >> 16)) {
-              uint32_t u2[4];
-              philox10(c0[r] + (q >> 1), g, j, c3 + (1u << 28), P.key0, P.key1, u2);
-              acc = half16(pick4(u2, o), i & 1) <= (Uw & 0xFFFFu);
-            }
-            f[r][q] = (f[r][q] & ~(0xFFu << (8 * i))) | (acc ? 0xFFu << (8 * i) : 0u);
-          }
+          for (int i = 0; i < 4; ++i) Uw[i] = Um[min((at >> (8 * i)) & 0xFFu, 8u * DIM - 1u)];
           if (work) {
             // colour-0 ramped sites see phi_k; each adds (m - m_prev) 2 (b - c)
             const int dm = m - row_m(P, cr[r].y, pos - dpos);
-            dI += dm * 2 * (__popc(bw & rm) - __popc(cw & rm));
+            dI += dm * 2 * (__popc(bw & gm[q]) - __popc(cw & gm[q]));
           }
+          uint32_t acc = 0, ties = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int o = ((ob + 2 * q) & 3) + (i >> 1);
+            const uint32_t vr = half16(pick4(U[r * NC + (q >> 1)], o), i & 1) ^ 0x8000u;
+            acc |= (vr < (Uw[i] >> 16)) ? 0xFFu << (8 * i) : 0u;
+            ties |= (vr == (Uw[i] >> 16)) ? 1u << (8 * i) : 0u;
+          }
+          if ((ties & gm[q]) != 0) {
+            uint32_t u2[4];
+            philox10(c0[r] + (q >> 1), g, j, c3 + (1u << 28), P.key0, P.key1, u2);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int o = ((ob + 2 * q) & 3) + (i >> 1);
+              const bool up = half16(pick4(u2, o), i & 1) <= (Uw[i] & 0xFFFFu);
+              if ((ties >> (8 * i)) & 1u) acc = (acc & ~(0xFFu << (8 * i))) | (up ? 0xFFu << (8 * i) : 0u);
+            }
+          }
+          f[r][q] = __builtin_amdgcn_bitop3_b32(gm[q] * 0xFFu, acc, f[r][q], 0xCA);
         }
       }
     }
@@ -537,6 +553,184 @@ __device__ __forceinline__ void decide_rows(const JP& P, const uint32_t U[NR * (
   for (int r = 0; r < NR; ++r)
 #pragma unroll
     for (int q = 0; q < W; ++q) Sn[r][q] = __builtin_amdgcn_bitop3_b32(S[r][q], f[r][q], fmask[q], 0x78);
+}
+
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const lds_u32*)(const uint32_t*)p;
+}
+
+// The Metropolis update of the sites of one row of colour c that a lane owns
+// (words w .. w+W-1 of the row), parity of the row known only at run time.
+//   aC, aO  locations of word w of the row in its own colour plane and in the
+//           other one
+//   tmo, tpo, ymo, ypo  word offsets from aO of the same words in rows t-1,
+//           t+1, y-1 and y+1 (periodic)
+//   gmem, ag  where the glued partner row is (CUT; a location that may be
+//           read also for rows away from the cut)
+//   (r, t, y)  the row; c0, c3 Philox counter words 0 and 3 of its first call
+// FULL: lx/2 is a multiple of 4 (no pad bytes, x-neighbours by byte
+// alignment of two words).  W: consecutive words per lane (2 or 4 need
+// FULL and a word count that W divides; 3 needs FULL and rows of exactly
+// three words, so that w = 0 and words 0, 1 share a Philox call while word
+// 2 takes the next one).  CUT: the code for rows next to the cut (t = 0, 1)
+// is compiled in; without it the row must have t > 1.
+template <int DIM, bool FULL, int W, bool CUT, bool LA, typename M, typename GM>
+__device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M& mem, const uint32_t aC,
+                                           const uint32_t aO, const GM& gmem, const uint32_t ag, const int w,
+                                           const int wl, const int wr, const uint32_t* __restrict__ thr, const int c,
+                                           const uint32_t g, const uint32_t j, const int pos, const int dpos,
+                                           const bool work, int& dI, const int t, const int y, const int tmo,
+                                           const int tpo, const int ymo, const int ypo, const uint32_t c0,
+                                           const uint32_t c3, uint32_t* nextU = nullptr) {
+  static_assert(W == 1 || ((W == 2 || W == 3 || W == 4) && FULL), "several words per lane need whole rows");
+  const int G = P.G;
+  const int tailsh = 8 * ((P.H - 1) & 3);
+  const uint32_t valid = (!FULL && w == G - 1 && tailsh != 24) ? ((1u << (tailsh + 8)) - 1u) : 0xFFFFFFFFu;
+  const uint32_t fmask = valid & 0x01010101u;  // bit 0 of every real site's byte
+  const int p = (c + t + y) & 1;               // x parity of this row's sites
+  const auto at = [&](int words) { return aO + 4u * (uint32_t)words; };
+  uint32_t A[W], B[W], S[1][W], Tm[W], Tp[W], idx[1][W], Sn[1][W];
+  CutRow<W> cr[1];
+  // towards the cut and away from it, by address: the sum is symmetric
+  const int toff0 = (CUT && t == 1) ? tmo : tpo, toff1 = (CUT && t == 1) ? tpo : tmo;
+  ld_words<W>(mem, aO, A);
+  const uint32_t E = ld_word(mem, at((p ? wr : wl) - w));
+  ld_words<W>(mem, aC, S[0]);
+  ld_words<W>(mem, at(toff0), Tp);
+  ld_words<W>(mem, at(toff1), Tm);
+  if constexpr (CUT) ld_words<W>(gmem, ag, cr[0].Tg);
+  uint32_t Ym[W], Yp[W];
+  if constexpr (DIM == 3) {
+    ld_words<W>(mem, at(ymo), Ym);
+    ld_words<W>(mem, at(ypo), Yp);
+  } else {
+#pragma unroll
+    for (int q = 0; q < W; ++q) Ym[q] = Yp[q] = 0;
+  }
+  // LA (lookahead): K is the keys of the next half-sweep; this row's Philox
+  // outputs come in nextU, computed during the previous half-sweep, and the
+  // next ones replace them.  They do not depend on spins, so that chain
+  // overlaps this row's loads and decisions instead of lengthening the next
+  // half-sweep.
+  constexpr int NC = (W + 1) / 2;
+  uint32_t U[NC][4], Un[NC][4];
+  fields_of_row<W>(K, c0, Un);
+#pragma unroll
+  for (int k = 0; k < NC; ++k)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      U[k][e] = LA ? nextU[4 * k + e] : Un[k][e];
+      if (LA) nextU[4 * k + e] = Un[k][e];
+    }
+  if constexpr (CUT) {
+    cr[0].on = t <= 1;
+    cr[0].p = p;
+    cr[0].y = y;
+    cr[0].ramp = cr[0].on && p == (P.l & 1) && ramp_lane<W>(P, w);
+#pragma unroll
+    for (int q = 0; q < W; ++q) cr[0].Tc[q] = Tp[q];
+    uint32_t gm[W];
+    glued_bits<W>(P, cr[0].on && !P.whole, p, w, gm);
+    cut_partner<W>(cr[0], gm, Tp);
+  }
+  if (FULL) {
+    x_words<W, -1>(A, E, p, B);
+  } else {
+    const uint32_t rshift = (w == G - 1) ? (uint32_t)tailsh : 24u;
+    const uint32_t Br = (A[0] >> 8) | ((E & 0xFFu) << rshift);
+    const uint32_t Bl = (A[0] << 8) | ((w == 0) ? ((E >> tailsh) & 0xFFu) : (E >> 24));
+    B[0] = p ? Br : Bl;
+  }
+#pragma unroll
+  for (int q = 0; q < W; ++q) idx[0][q] = nbr_index<DIM>(S[0][q], A[q], B[q], Tm[q], Tp[q], Ym[q], Yp[q]);
+  uint32_t fm[W];
+#pragma unroll
+  for (int q = 0; q < W; ++q) fm[q] = fmask;
+  decide_rows<DIM, W, 1, CUT>(P, U, &c0, c3, g, j, w, fm, thr, S, idx, cr, pos, dpos, work, dI, Sn,
+                              [&](int, uint32_t* Tc, uint32_t* Tg) {
+                                ld_words<W>(mem, at(toff0), Tc);
+                                ld_words<W>(gmem, ag, Tg);
+                              });
+  st_words<W>(mem, aC, Sn[0]);
+}
+
+// One half-sweep of colour c over the lane's rows of one trajectory, in the
+// order of the lane map (any map; the streaming path's and the general
+// on-chip one).  base: location of the trajectory (two colour planes).
+template <int DIM, bool FULL, int W, typename M>
+__device__ __forceinline__ void half_sweep(const JP& P, PhKey& K, const Lane& ln, const M& mem, const uint32_t base,
+                                           const uint32_t* __restrict__ thr, const int c, const uint32_t g,
+                                           const uint32_t j, const int pos, const int dpos, const bool work, int& dI) {
+  const int G = P.G;
+  const int cw = P.n * P.R * G;  // words per colour plane
+  const uint32_t bC = base + 4u * (uint32_t)(c * cw), bO = base + 4u * (uint32_t)((c ^ 1) * cw);
+  const int LyG = P.ly * G;
+  const int ltLyG = P.lt * LyG;
+  const int ywrap = (P.ly - 1) * G;
+  const uint32_t ctr3 = (1u << 28) | (uint32_t)c;
+  const int w = ln.w;
+  int r = ln.r0, t = ln.t0, y = ln.y0;
+  int rowbase = ln.rowbase0;
+  for (int kk = ln.kstart; kk < ln.kend; kk += ln.kstep) {
+    // the periodic wrap in t adds or removes one replica's rows; the one
+    // below t = 0 belongs to a row next to the cut (cut variant only)
+    const int tpo = LyG - ((t == P.lt - 1) ? ltLyG : 0);
+    const int ymo = (y == 0) ? ywrap : -G;
+    const int ypo = (y == P.ly - 1) ? -ywrap : G;
+    const uint32_t c0 = (uint32_t)((t * P.ly + y) * P.G8 + (w >> 1));
+    const uint32_t c3 = ctr3 | ((uint32_t)r << 1);
+    K.x0 = c3 ^ P.key1;
+    const uint32_t off = 4u * (uint32_t)(rowbase + w);
+    const auto row = [&](auto cut) {
+      constexpr bool CUT = decltype(cut)::value;
+      const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
+      const uint32_t ag = (CUT && t <= 1) ? bO + 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : bO + off;
+      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, bO + off, mem, ag, w, ln.wl, ln.wr, thr, c, g, j, pos,
+                                           dpos, work, dI, t, y, tmo, tpo, ymo, ypo, c0, c3);
+    };
+    // the code for rows next to the cut runs only where some lane of the
+    // wave has such a row
+    if (__builtin_amdgcn_ballot_w64(t <= 1) != 0) row(std::true_type{});
+    else row(std::false_type{});
+    // next row of this lane
+    rowbase += ln.step;
+    if (DIM == 3) {
+      y += ln.dy;
+      if (y >= P.ly) { y -= P.ly; ++t; }
+    }
+    t += ln.dt;
+    if (t >= P.lt) {
+      t -= P.lt;
+      r += ln.rinc;
+      rowbase -= ln.wrapadj;
+    }
+    r += ln.dr;
+  }
+}
+
+// Initial spins (phase 0 of the Philox streams): +1 iff u < 2^31.  PM: into
+// the class-by-class rows of the parity-major order, pitch words each.
+template <bool PM, typename M>
+__device__ void init_spins(const JP& P, const M& mem, uint32_t base, uint32_t j, int lt_, int T, int pitch) {
+  const int nR = P.n * P.R;
+  for (int q = lt_; q < P.traj_words; q += T) {
+    const int w = q % P.G;
+    const int rowg = q / P.G;
+    const int c = rowg / nR;
+    const int row = rowg - c * nR;
+    const int r = row / P.R;
+    const int rho = row - r * P.R;
+    uint32_t u[4];
+    philox10((uint32_t)(rho * P.G + w), 0u, j, ((uint32_t)r << 1) | (uint32_t)c, P.key0, P.key1, u);
+    uint32_t word = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (4 * w + i < P.H) word |= (uint32_t)(u[i] < 0x80000000u) << (8 * i);
+    const int at = PM ? (rowg - rho + pm_row(P, rho)) * pitch + w : q;
+    st_words<1>(mem, base + 4u * (uint32_t)at, &word);
+  }
 }
 
 }  // namespace

@@ -324,6 +324,13 @@ namespace {
 // Batch plans: device queue + job table + units, and a HIP graph of
 // [queue reset] -> [event] -> [persistent sweep kernel] -> [event] -> [estimator launches]
 // ---------------------------------------------------------------------------
+int is_whole(const ee_job* j) { return (j->d.flags & EE_FLAG_WHOLE) ? 1 : 0; }
+int any_whole(ee_job* const* jobs, int count) {
+  for (int i = 0; i < count; ++i)
+    if (is_whole(jobs[i])) return 1;
+  return 0;
+}
+
 bool same_lattice(const ee_job* a, const ee_job* b) {
   return a->d.dim == b->d.dim && a->d.lt == b->d.lt && a->d.lx == b->d.lx && a->d.ly == b->d.ly &&
          a->d.n_replicas == b->d.n_replicas;
@@ -342,6 +349,7 @@ struct Plan {
   int dim = 0;
   int block = 0, lds = 0, grid = 0, n_units = 0;
   int max_n = 0;  // most trajectories of a job
+  int whole = 0;  // a job runs the whole-region protocol
   void* dev_buf = nullptr;
   int* dev_queue = nullptr;
   const ee::JobDev** dev_jobtab = nullptr;
@@ -496,7 +504,7 @@ ee_status launch_sweep_for_job(ee_job* j, uint32_t flags, int n_therm) {
   }
   const int grid = (j->d.n_traj + k - 1) / k;
   const int lds = k * j->L.lds_words * 4;
-  const int rc = ee_k_launch_sweep(j->dev_jobdev(), k, nullptr, 0, nullptr, nullptr, flags, n_therm, (int)j->g, grid,
+  const int rc = ee_k_launch_sweep(is_whole(j), j->dev_jobdev(), k, nullptr, 0, nullptr, nullptr, flags, n_therm, (int)j->g, grid,
                                    block, lds, j->stream);
   if (rc != 0) return fail(EE_EHIP, "sweep kernel launch failed: %s", hipGetErrorString((hipError_t)rc));
   return EE_OK;
@@ -568,9 +576,9 @@ int auto_slots(const ee_job* j, int block, int lds) {
 
 // Persistent grid: as many workgroups of this shape as fit on the GPU at
 // once (or the config's count), at most one per unit.
-ee_status persistent_grid(int block, int lds, int n_units, const ee_launch_cfg& cfg, int* grid) {
+ee_status persistent_grid(int whole, int block, int lds, int n_units, const ee_launch_cfg& cfg, int* grid) {
   const void* fn = nullptr;
-  const int rc = ee_k_sweep_kernel_ptr(&fn);
+  const int rc = ee_k_sweep_kernel_ptr(whole, &fn);
   if (rc != 0) return fail(EE_EHIP, "kernel attribute: %s", hipGetErrorString((hipError_t)rc));
   int per_cu = 0;
   const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, lds + ee::kSweepTailBytes);
@@ -608,7 +616,7 @@ ee_status plan_units(ee_job* const* jobs, int count, int n_therm, const ee_launc
   out->lds = lds_need;
   out->units.resize(units.size());
   for (size_t i = 0; i < units.size(); ++i) out->units[i] = units[i].u;
-  return persistent_grid(out->block, out->lds, (int)units.size(), cfg, &out->grid);
+  return persistent_grid(any_whole(jobs, count), out->block, out->lds, (int)units.size(), cfg, &out->grid);
 }
 
 ee_status build_plan(ee_job* const* jobs, int count, int n_therm, const ee_launch_cfg& cfg,
@@ -626,9 +634,10 @@ ee_status build_plan(ee_job* const* jobs, int count, int n_therm, const ee_launc
   P->grid = up.grid;
   P->n_units = (int)up.units.size();
   P->max_n = max_traj(jobs, count);
+  P->whole = any_whole(jobs, count);
   const std::vector<ee::Unit>& units = up.units;
   const void* fn = nullptr;
-  int rc = ee_k_sweep_kernel_ptr(&fn);
+  int rc = ee_k_sweep_kernel_ptr(P->whole, &fn);
   if (rc != 0) { delete P; return fail(EE_EHIP, "kernel attribute: %s", hipGetErrorString((hipError_t)rc)); }
   hipError_t e = hipSuccess;
   // device metadata
@@ -748,7 +757,7 @@ ee_status run_plan(Plan* P, hipStream_t stream) {
     int rc = ee_k_launch_queue_reset(P->dev_queue, stream);
     if (rc) return fail(EE_EHIP, "queue reset launch: %s", hipGetErrorString((hipError_t)rc));
     HIP_TRY(hipEventRecord(P->ev_start, stream));
-    rc = ee_k_launch_sweep(nullptr, 0, P->dev_units, P->n_units, P->dev_queue, P->dev_jobtab,
+    rc = ee_k_launch_sweep(P->whole, nullptr, 0, P->dev_units, P->n_units, P->dev_queue, P->dev_jobtab,
                            ee::kFlagInit | ee::kFlagProto, P->n_therm, 0, P->grid, P->block, P->lds, stream);
     if (rc) return fail(EE_EHIP, "persistent sweep launch: %s", hipGetErrorString((hipError_t)rc));
     HIP_TRY(hipEventRecord(P->ev_stop, stream));
@@ -1093,7 +1102,7 @@ ee_status ee_batch_run_noalloc(ee_job* const* jobs, int32_t count, int32_t n_the
   HIP_TRY(hipStreamSynchronize(stream));
   rc = ee_k_launch_queue_reset(queue, stream);
   if (rc == 0)
-    rc = ee_k_launch_sweep(nullptr, 0, units, (int)up.units.size(), queue, jobtab, ee::kFlagInit | ee::kFlagProto,
+    rc = ee_k_launch_sweep(any_whole(jobs, count), nullptr, 0, units, (int)up.units.size(), queue, jobtab, ee::kFlagInit | ee::kFlagProto,
                            n_therm, 0, up.grid, up.block, up.lds, stream);
   if (rc == 0) rc = ee_k_launch_estimate(jobtab, count, max_traj(jobs, count), stream);
   if (rc) return fail(EE_EHIP, "allocation-free batch launch: %s", hipGetErrorString((hipError_t)rc));
@@ -1243,7 +1252,7 @@ ee_status server_launch(ee_server* S, SrvSlot& sl) {
   std::memset(sl.host, 0, S->off_tab);  // queue counter = 0
   const ee::JobDev** tab = reinterpret_cast<const ee::JobDev**>(sl.host + S->off_tab);
   ee::Unit* units = reinterpret_cast<ee::Unit*>(sl.host + S->off_units);
-  int block = C->block, lds = 0;
+  int block = C->block, lds = 0, whole = 0;
   for (int i = 0; i < take; ++i) {
     const SrvUnit& u = chunk[i];
     SrvJob& sj = S->jobs[u.id];
@@ -1265,15 +1274,16 @@ ee_status server_launch(ee_server* S, SrvSlot& sl) {
       }
     }
     sl.per_job[it->second].second += 1;
+    whole |= is_whole(sj.job);
     units[i] = ee::Unit{it->second, u.j0, u.count, u.k};
     lds = std::max(lds, u.k * sj.job->L.lds_words * 4);
   }
   int grid = 0;
-  ee_status s = persistent_grid(block, lds, take, S->cfg, &grid);
+  ee_status s = persistent_grid(whole, block, lds, take, S->cfg, &grid);
   if (s) return s;
   int* queue = reinterpret_cast<int*>(sl.dev);
   HIP_TRY(hipMemcpyAsync(sl.dev, sl.host, S->off_units + sizeof(ee::Unit) * take, hipMemcpyHostToDevice, sl.stream));
-  const int rc = ee_k_launch_sweep(nullptr, 0, reinterpret_cast<const ee::Unit*>(sl.dev + S->off_units), take, queue,
+  const int rc = ee_k_launch_sweep(whole, nullptr, 0, reinterpret_cast<const ee::Unit*>(sl.dev + S->off_units), take, queue,
                                    reinterpret_cast<const ee::JobDev* const*>(sl.dev + S->off_tab),
                                    ee::kFlagInit | ee::kFlagProto, S->n_therm, 0, grid, block, lds, sl.stream);
   if (rc) return fail(EE_EHIP, "server chunk launch: %s", hipGetErrorString((hipError_t)rc));
@@ -1354,7 +1364,7 @@ ee_status server_class(ee_server* S, const ee_job* job, SrvClass** out) {
   c.block = block;
   c.budget = budget;
   int grid = 0;
-  ee_status s = persistent_grid(block, budget, 1 << 30, S->cfg, &grid);
+  ee_status s = persistent_grid(0, block, budget, 1 << 30, S->cfg, &grid);
   if (s) return s;
   c.chunk_units = std::min(S->max_chunk, 2 * grid);
   S->classes.push_back(c);
