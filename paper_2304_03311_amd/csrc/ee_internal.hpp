@@ -26,6 +26,7 @@
 #include <stdint.h>
 
 #include "../../include/ee.h"
+#include "ee_lanes.hpp"
 
 namespace ee {
 
@@ -65,6 +66,7 @@ struct alignas(256) JobDev {
   // the signed order): the high bytes in pt[0], pt[1], the low ones in pt[2],
   // pt[3], as v_perm_b32 selects them.
   uint32_t pt[4];
+  uint32_t thr_idx[8];  // full thresholds by neighbour index
   int32_t lds_words;         // LDS words of a trajectory on chip
   int32_t rag_W, rag_pitch;  // rows kept at their own pitch in LDS (ee_lanes.hpp: row_pitch); 0: as stored
   double beta;
@@ -93,6 +95,15 @@ inline Magic make_magic(uint32_t d) {
   return Magic{(uint32_t)m, l};
 }
 
+// What a streaming launch needs, by value.
+struct StreamArgs {
+  lanes::JP P;
+  const uint32_t* thr;      // full thresholds by neighbour index (device memory)
+  int lanes, slots, rows;   // lanes and row slots of a trajectory, its rows of one colour
+  int blocks, q8, rem8;     // workgroups of a trajectory; all of them over the eight XCDs
+  Magic bx, gw;             // divisions by blocks and by lanes per row
+};
+
 }  // namespace ee
 
 // Launch helpers implemented in ee_kernels.hip.
@@ -108,8 +119,8 @@ int ee_k_sweep_whole_ptr(const void** fn);
 int ee_k_queue_reset_ptr(const void** fn);
 int ee_k_estimate_plan(int count, int max_n, ee::EstLaunch out[4]);
 int ee_k_max_lds_bytes();
-int ee_k_launch_stream_sweep(const ee::JobDev* job, int n_traj, int lanes, int c, uint32_t g, int pos, int dpos,
-                             int work, void* stream);
+int ee_k_launch_stream(const ee::StreamArgs* args, int words_per_lane, int n_traj, int c, uint32_t g, int pos,
+                       int dpos, int work, void* stream);
 int ee_k_launch_stream_init(const ee::JobDev* job, int n_traj, int lanes, void* stream);
 int ee_k_launch_zero_work(const ee::JobDev* job, int n_traj, void* stream);
 // Plane-marching kernel: LDS bytes of a workgroup whose plane (one

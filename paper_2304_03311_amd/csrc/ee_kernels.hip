@@ -48,65 +48,68 @@ __device__ __forceinline__ void xcd_block(int bx, int total, int& j, int& b) {
   b = logical - j * bx;
 }
 
+// The trajectory, row slot and first word of a lane of a streaming
+// launch; false for a lane past the last slot.
+__device__ __forceinline__ bool stream_lane(const ee::StreamArgs& a, int W, uint32_t& j, int& slot, int& w) {
+  const int id = blockIdx.x, x = id % kXcd, k = id / kXcd;
+  const int logical = x * a.q8 + min(x, a.rem8) + k;  // as xcd_block
+  const int jj = (int)fdiv((uint32_t)logical, a.bx.mul, a.bx.shift);
+  const int lane = (logical - jj * a.blocks) * 256 + (int)threadIdx.x;
+  j = (uint32_t)jj;
+  slot = (int)fdiv((uint32_t)lane, a.gw.mul, a.gw.shift);
+  w = (lane - slot * (a.P.G / W)) * W;
+  return lane < a.lanes;
+}
+
+// One row at a time, in storage order over the lanes: consecutive lanes read
+// consecutive words.  (Pairs of neighbouring rows per lane, as on chip, cost
+// 150 instead of 190 instructions a row but read every other row: 5.3 against
+// 3.7 ms on the job below.)  Bound by memory on large jobs: 3D 96^3 x 32
+// trajectories 17 us a launch, 5.0 TB/s on its 3 B per attempt, as fast as a
+// large copy.  What is the same for every lane comes by value in the
+// arguments, with the multipliers of its divisions, and the lanes have no
+// barrier; made from the job's description in memory, behind one dependent
+// load after the other, it was a fifth of the time and kept small jobs at four
+// rows per lane: 96^3 x 32, 110 sweeps 4.05 -> 3.75 ms, 48^3 x 16, 600 sweeps
+// 7.72 -> 5.52 ms, the 2D L = 128 cylinder x 256, 200 sweeps 7.95 -> 7.12 ms.
 template <int DIM, bool FULL, int W>
-__device__ __forceinline__ void stream_half(const JP& P, uint32_t* s_thr, int lanes, int c, uint32_t g, int pos,
-                                            int dpos, bool work) {
-  const int bx = (lanes + 255) / 256;
-  int jj, b;
-  xcd_block(bx, (int)gridDim.x, jj, b);
-  const int lt_ = b * blockDim.x + threadIdx.x;
-  const uint32_t j = (uint32_t)jj;
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
+stream_row_kernel(ee::StreamArgs a, int c, uint32_t g, int pos, int dpos, int work) {
+  const JP& P = a.P;
+  uint32_t j;
+  int slot, w;
+  if (!stream_lane(a, W, j, slot, w)) return;
   const HbmMem mem{P.spins + (size_t)j * P.traj_words};
-  int dI = 0;
   PhKey K;
   key_unit(K, P);
   key_sweep(K, P, g, j);
-  const Lane ln = make_lane(P, lt_ < lanes ? lt_ : 0, lanes, W, false);
-  if (lt_ < lanes && ln.kstart < ln.kend)
-    half_sweep<DIM, FULL, W>(P, K, ln, mem, 0u, s_thr, c, g, j, pos, dpos, work, dI);
-  if (dI != 0) atomicAdd(reinterpret_cast<unsigned long long*>(&P.work[j]), (unsigned long long)(long long)dI);
-}
-
-// Body of the streaming launches: the widest lane width (words per lane)
-// that the job's rows allow.
-__device__ __forceinline__ void stream_body(const JobDev* J, int lanes, int c, uint32_t g, int pos, int dpos,
-                                            int work) {
-  __shared__ uint32_t s_thr[8];
-  const JP P = load_jp(J);
-  const int dim = uni(J->dim);
-  if (threadIdx.x < 8)
-    s_thr[threadIdx.x] = thr_entry(P, dim, threadIdx.x);
-  __syncthreads();
-  const bool full = (P.H & 3) == 0;
-  const bool w = work != 0;
-  switch (words_per_lane(P, lanes)) {
-    case 4:
-      if (dim == 3) stream_half<3, true, 4>(P, s_thr, lanes, c, g, pos, dpos, w);
-      else stream_half<2, true, 4>(P, s_thr, lanes, c, g, pos, dpos, w);
-      return;
-    case 3:
-      if (dim == 3) stream_half<3, true, 3>(P, s_thr, lanes, c, g, pos, dpos, w);
-      else stream_half<2, true, 3>(P, s_thr, lanes, c, g, pos, dpos, w);
-      return;
-    case 2:
-      if (dim == 3) stream_half<3, true, 2>(P, s_thr, lanes, c, g, pos, dpos, w);
-      else stream_half<2, true, 2>(P, s_thr, lanes, c, g, pos, dpos, w);
-      return;
-    default:
-      if (dim == 3) {
-        if (full) stream_half<3, true, 1>(P, s_thr, lanes, c, g, pos, dpos, w);
-        else stream_half<3, false, 1>(P, s_thr, lanes, c, g, pos, dpos, w);
-      } else {
-        if (full) stream_half<2, true, 1>(P, s_thr, lanes, c, g, pos, dpos, w);
-        else stream_half<2, false, 1>(P, s_thr, lanes, c, g, pos, dpos, w);
-      }
+  const int G = P.G, LyG = P.ly * G, ltLyG = P.lt * LyG, cw = P.n * P.R * G;
+  const uint32_t bC = 4u * (uint32_t)(c * cw), bO = 4u * (uint32_t)((c ^ 1) * cw);
+  const int wl = (w == 0) ? G - 1 : w - 1, wr = (w + W == G) ? 0 : w + W;
+  int dI = 0;
+  for (int m = slot; m < a.rows; m += a.slots) {
+    const int r = (int)fdiv((uint32_t)m, P.mR, P.sR);
+    const int rho = m - r * P.R;
+    const int t = (DIM == 2) ? rho : (int)fdiv((uint32_t)rho, P.mLy, P.sLy);
+    const int y = (DIM == 2) ? 0 : rho - t * P.ly;
+    const int tpo = LyG - ((t == P.lt - 1) ? ltLyG : 0);
+    const int ymo = (y == 0) ? (P.ly - 1) * G : -G;
+    const int ypo = (y == P.ly - 1) ? -(P.ly - 1) * G : G;
+    const uint32_t c0 = (uint32_t)(rho * P.G8 + (w >> 1));
+    const uint32_t c3 = (1u << 28) | ((uint32_t)r << 1) | (uint32_t)c;
+    K.x0 = c3 ^ P.key1;
+    const uint32_t off = 4u * (uint32_t)(m * G + w);
+    const auto row = [&](auto cut) {
+      constexpr bool CUT = decltype(cut)::value;
+      const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
+      const uint32_t ag = (CUT && t <= 1) ? bO + 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : bO + off;
+      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, bO + off, mem, ag, w, wl, wr, a.thr, c, g, j, pos, dpos,
+                                           work != 0, dI, t, y, tmo, tpo, ymo, ypo, c0, c3);
+    };
+    if (__builtin_amdgcn_ballot_w64(t <= 1) != 0) row(std::true_type{});
+    else row(std::false_type{});
   }
-}
-
-// 4 waves per SIMD (128 VGPRs), up to four words per lane.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
-stream_sweep_kernel(const JobDev* J, int lanes, int c, uint32_t g, int pos, int dpos, int work) {
-  stream_body(J, lanes, c, g, pos, dpos, work);
+  if (dI != 0) atomicAdd(reinterpret_cast<unsigned long long*>(&P.work[j]), (unsigned long long)(long long)dI);
 }
 
 // ---------------------------------------------------------------------------
@@ -860,12 +863,22 @@ int ee_k_launch_sweep(int whole, const ee::JobDev* single_job, int single_k, con
   return (int)hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds_bytes + ee::kSweepTailBytes, (hipStream_t)stream);
 }
 
-int ee_k_launch_stream_sweep(const ee::JobDev* job, int n_traj, int lanes, int c, uint32_t g, int pos, int dpos,
-                             int work, void* stream) {
-  const int bx = (lanes + 255) / 256;
-  // one-dimensional grid: bx blocks per trajectory, remapped per XCD in the kernel
-  hipLaunchKernelGGL(stream_sweep_kernel, dim3(bx * n_traj), dim3(256), 0, (hipStream_t)stream, job, lanes, c, g,
-                     pos, dpos, work);
+int ee_k_launch_stream(const ee::StreamArgs* a, int W, int n_traj, int c, uint32_t g, int pos, int dpos, int work,
+                       void* stream) {
+  const auto go = [&](auto dim, auto w, auto full) {
+    hipLaunchKernelGGL((stream_row_kernel<decltype(dim)::value, decltype(full)::value, decltype(w)::value>),
+                       dim3(a->blocks * n_traj), dim3(256), 0, (hipStream_t)stream, *a, c, g, pos, dpos, work);
+  };
+  const auto width = [&](auto dim) {
+    using T_ = std::true_type;
+    if ((a->P.H & 3) != 0) go(dim, std::integral_constant<int, 1>{}, std::false_type{});
+    else if (W == 4) go(dim, std::integral_constant<int, 4>{}, T_{});
+    else if (W == 3) go(dim, std::integral_constant<int, 3>{}, T_{});
+    else if (W == 2) go(dim, std::integral_constant<int, 2>{}, T_{});
+    else go(dim, std::integral_constant<int, 1>{}, T_{});
+  };
+  if (a->P.dim == 3) width(std::integral_constant<int, 3>{});
+  else width(std::integral_constant<int, 2>{});
   return (int)hipGetLastError();
 }
 

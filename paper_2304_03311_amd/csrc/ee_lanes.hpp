@@ -54,12 +54,12 @@ struct Lane {
 //    that replica in the order rho = (k + 2 ly) mod R, so that the rows
 //    next to the cut (t = 0, 1) come last: one iteration of the lane's loop
 //    meets them instead of one per replica.
-//  * otherwise: slot s takes rows s, s+S, ... of the planes in storage order.
-//    The streaming kernel keeps this order: its rows come from HBM through
-//    the caches, and it measured 11% faster than the grouped order.
+//  * otherwise: slot s takes rows s, s+S, ... of the planes in storage order,
+//    as the streaming kernel does: its rows come from HBM through the caches,
+//    and it measured 11% faster than in the grouped order.
 // The rows of a colour are independent within a half-sweep, so the order
 // does not change any result.  Divisions by R and ly use the job's magic
-// multipliers (the streaming kernel builds this map at every launch).
+// multipliers.
 EE_HDI Lane make_lane(const JP& P, int lt_, int T, int W, bool groups) {
   const int GW = P.G / W;
   const int S = T / GW;

@@ -391,20 +391,6 @@ bool same_cfg(const ee_launch_cfg& a, const ee_launch_cfg& b) {
          a.grid_blocks == b.grid_blocks && a.use_graph == b.use_graph && a.flags == b.flags;
 }
 
-// Lanes per trajectory of the streaming path: every lane walks about 4 rows
-// (measured on 96^3: 4% faster than 8 rows, and faster than 2).  W: the
-// words per lane the streaming kernel takes for these rows (four for a
-// multiple of 16 sites per colour, three for rows of 12, two for a
-// multiple of 8, else one).
-int stream_lanes(const ee_job* j) {
-  const int nrows = j->d.n_replicas * j->L.R;
-  const int H = j->L.H;
-  const int W = ((H & 15) == 0) ? 4 : (H == 12) ? 3 : ((H & 7) == 0) ? 2 : 1;
-  const int GW = j->L.G / W;
-  const int nrg = std::max(1, (nrows + 3) / 4);
-  return nrg * GW;
-}
-
 // Words of one plane of the plane-marching kernel (one replica, one t,
 // both colours, all y): a slot of its LDS ring.
 int plane_words(const ee_job* j) { return 2 * j->d.ly * j->L.G; }
@@ -454,10 +440,55 @@ int march_segments(const ee_job* j) {
   return best;
 }
 
+// Words per lane of the streaming kernel: four for a multiple of 16 sites per
+// colour, three for rows of 12, two for a multiple of 8, else one.
+int stream_words(const ee_job* j) {
+  const int H = j->L.H;
+  return ((H & 15) == 0) ? 4 : (H == 12) ? 3 : ((H & 7) == 0) ? 2 : 1;
+}
+
+// Arguments of the streaming launches.  A lane takes two rows where that
+// leaves eight waves per SIMD over the GPU, else one: 3D 96^3 x 32 at 1, 2, 4
+// and 8 rows per lane 4.26, 3.75, 3.74 and 4.08 ms, the 2D L = 128 cylinder x
+// 256 7.96, 7.12, 7.43 and 7.66 ms, 3D 48^3 x 16 (3.4 waves per SIMD at one
+// row) 5.52, 5.94, 6.99 and 8.93 ms.  More rows per lane only where the grid
+// would pass the 2^32 - 1 lanes of a launch.
+ee::StreamArgs stream_args(const ee_job* j) {
+  ee::StreamArgs a{};
+  const ee::JobDev& D = j->host_jobdev;
+  ee::lanes::JP& P = a.P;
+  P.dim = D.dim; P.n = D.n; P.lt = D.lt; P.ly = D.ly; P.l = D.l; P.N = D.N; P.S = D.S;
+  P.subsets = D.subsets; P.whole = D.whole; P.H = D.H; P.G = D.G; P.G8 = (D.H + 7) >> 3; P.R = D.R;
+  P.traj_words = D.traj_words; P.key0 = D.key0; P.key1 = D.key1;
+  P.thr0 = D.thr_bulk[0]; P.thr1 = D.thr_bulk[1]; P.thr2 = D.thr_bulk[2];
+  P.reverse = D.reverse; P.spin_format = D.spin_format;
+  P.pt_hi0 = D.pt[0]; P.pt_hi1 = D.pt[1]; P.pt_lo0 = D.pt[2]; P.pt_lo1 = D.pt[3];
+  P.mR = D.magic_R; P.sR = D.shift_R; P.mLy = D.magic_Ly; P.sLy = D.shift_Ly;
+  P.ramp = D.ramp_thr; P.spins = D.spins; P.work = D.work;
+  a.thr = j->dev_jobdev()->thr_idx;
+  const int GW = j->L.G / stream_words(j);
+  const int rows = j->d.n_replicas * j->L.R;
+  a.rows = rows;
+  int per_lane = ((long)rows * GW * j->d.n_traj > 4L * device_info().cus * 1024) ? 2 : 1;
+  for (;; per_lane *= 2) {
+    a.slots = (rows + per_lane - 1) / per_lane;
+    a.lanes = a.slots * GW;
+    a.blocks = (a.lanes + 255) / 256;
+    if ((long)a.blocks * j->d.n_traj < (1L << 24) || a.slots == 1) break;
+  }
+  const int total = a.blocks * j->d.n_traj;
+  a.q8 = total / 8;
+  a.rem8 = total % 8;
+  a.bx = ee::make_magic((uint32_t)a.blocks);
+  a.gw = ee::make_magic((uint32_t)GW);
+  return a;
+}
+
 ee_status stream_sweeps(ee_job* j, int n_sweeps, bool protocol) {
-  const int lanes = stream_lanes(j);
   const int nt = j->d.n_traj;
   const int nseg = march_segments(j);
+  const int W = stream_words(j);
+  const ee::StreamArgs args = stream_args(j);
   if (nseg < 0)
     return fail(EE_EUNSUPPORTED, "EE_LAUNCH_MARCH: a plane ring of %d bytes exceeds the %d bytes of LDS",
                 ee_k_march_lds_bytes(plane_words(j)), ee_k_max_lds_bytes());
@@ -474,8 +505,8 @@ ee_status stream_sweeps(ee_job* j, int n_sweeps, bool protocol) {
                              dpos, protocol ? 1 : 0, j->stream);
       continue;
     }
-    rc = ee_k_launch_stream_sweep(j->dev_jobdev(), nt, lanes, 0, g, pos, dpos, protocol ? 1 : 0, j->stream);
-    if (rc == 0) rc = ee_k_launch_stream_sweep(j->dev_jobdev(), nt, lanes, 1, g, pos, dpos, 0, j->stream);
+    rc = ee_k_launch_stream(&args, W, nt, 0, g, pos, dpos, protocol ? 1 : 0, j->stream);
+    if (rc == 0) rc = ee_k_launch_stream(&args, W, nt, 1, g, pos, dpos, 0, j->stream);
   }
   if (rc) return fail(EE_EHIP, "streaming sweep launch failed: %s", hipGetErrorString((hipError_t)rc));
   return EE_OK;
@@ -484,7 +515,7 @@ ee_status stream_sweeps(ee_job* j, int n_sweeps, bool protocol) {
 ee_status launch_sweep_for_job(ee_job* j, uint32_t flags, int n_therm) {
   if (j->streaming) {
     if (flags & ee::kFlagInit) {
-      const int rc = ee_k_launch_stream_init(j->dev_jobdev(), j->d.n_traj, stream_lanes(j), j->stream);
+      const int rc = ee_k_launch_stream_init(j->dev_jobdev(), j->d.n_traj, stream_args(j).lanes, j->stream);
       if (rc) return fail(EE_EHIP, "streaming init launch failed: %s", hipGetErrorString((hipError_t)rc));
     }
     if (flags & ee::kFlagProto) return stream_sweeps(j, j->d.n_step, true);
@@ -849,6 +880,7 @@ ee_status ee_job_create(const ee_job_desc* desc, void* dev_arena, size_t arena_b
   for (int i = 0; i < 8; ++i) {
     const int a = (dim == 2 && i >= 4) ? 7 - i : i;
     const uint32_t t16 = ((a < dim ? D.thr_bulk[a] : 0xFFFFFFFFu) >> 16) ^ 0x8000u;
+    D.thr_idx[i] = a < dim ? D.thr_bulk[a] : 0xFFFFFFFFu;
     D.pt[i >> 2] |= (t16 >> 8) << (8 * (i & 3));
     D.pt[2 + (i >> 2)] |= (t16 & 0xFFu) << (8 * (i & 3));
   }
