@@ -211,7 +211,7 @@ def streaming_run(n_traj: int = 32, march: bool = False) -> dict:
     dt = time.perf_counter() - t0
     job.close()
     bpa = BYTES_PER_ATTEMPT if march else STREAM_BYTES_PER_ATTEMPT
-    kernel = "march_kernel + march_fixup_kernel" if march else "stream_sweep_kernel (one launch per colour)"
+    kernel = "march_kernel + march_fixup_kernel" if march else "stream_row_kernel (one launch per colour)"
     return {"workload": f"3D 96^3, n=2, n_t={n_traj}, N=100, N_therm=10, int8 in HBM", "kernel": kernel,
             "attempts_per_ns": r.attempts / (dt * 1e9), "ms": dt * 1e3, "launches": 2 * 110 + 3,
             "algorithmic_bytes_per_attempt": bpa, "hbm_GBps_algorithmic": bpa * r.attempts / dt / 1e9,

@@ -240,8 +240,11 @@ ee_status ee_batch_run_cfg(ee_job* const* jobs, int32_t count, int32_t n_therm,
  * kernels and bit-identical results.  The queue counter, job table and
  * unit table go into a fixed static device array of 2 MiB per GPU, held
  * until the process ends; a batch whose tables need more (256 + 8 count
- * rounded up to 256, plus 16 bytes per work unit) returns EE_EINVAL before
- * any device work.  It calls no hipMalloc or hipFree, records no graph and
+ * rounded up to 256, plus 16 bytes per work unit, at as many trajectories a
+ * unit as lds_bytes, by default 80 KB, holds) returns EE_EINVAL before any
+ * device work.  Where the runtime's shape takes smaller units than that, a
+ * set near the limit runs in several launches, and the call waits for all
+ * but the last.  It calls no hipMalloc or hipFree, records no graph and
  * creates no event (cfg->use_graph is ignored; ee_batch_kernel_ms does not
  * time it).  The unit table is copied from host memory on hip_stream, and
  * the call waits for that copy (and so for the work queued before it).

@@ -2,12 +2,15 @@
 // estimator (Bulgarelli & Panero, arXiv:2304.03311).
 //
 // sweep_kernel (ee_sweep.hpp): one workgroup holds k trajectories of one job
-//   in LDS and runs all their sweeps on chip.  One lane updates W 32-bit words = 4W same-colour sites of a row.  One
-//   Philox4x32-10 call gives a 16-bit field to each of 8 sites; a site
+//   in LDS and runs all their sweeps on chip.  One lane updates W 32-bit
+//   words = 4W same-colour sites of a row.  One Philox4x32-10 call gives a 16-bit field to each of 8 sites; a site
 //   accepts when its field is below the top half of its uint32 threshold,
 //   and only a tie (probability 2^-16) draws the low 16 bits from a second
 //   call.  In batch mode the workgroups are persistent and pull work units
 //   (job, block of trajectories) from a device queue.
+// stream_row_kernel: one colour of every trajectory of a job that stays in
+//   HBM; march_kernel and march_fixup_kernel: the same jobs plane by plane
+//   through LDS, on request.
 // estimate_kernel, est_*_kernel: Jarzynski estimator (App. A): integer
 //   max/min of I_j, FP64 sum of exp(beta (I_j - I_max)/N), log-sum-exp,
 //   delete-one jackknife.
@@ -513,8 +516,8 @@ __global__ void queue_reset_kernel(int* queue) {
 // rounded ones of ee_dd.hpp.
 //
 // What bounds it is then the chain of dependent FP64 adds (some 17 cycles a
-// term for a wave alone on its SIMD), and how many of the n^2 adds of the leave-one-out sums run beside
-// each other.  Up to kEstSmall trajectories one workgroup does a job
+// term for a wave alone on its SIMD), and how many of the n^2 adds of the
+// leave-one-out sums run beside each other.  Up to kEstSmall trajectories one workgroup does a job
 // (estimate_kernel): lane i forms sum i, lane n the full sum, all in one walk
 // over the e_j in LDS, and one more wave the other sums.  Above, four
 // launches: the exponentials over many workgroups (est_exp_kernel), the plain

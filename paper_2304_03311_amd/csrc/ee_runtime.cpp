@@ -4,7 +4,7 @@
 // Metropolis threshold tables on the host (FP64 libm exp; compiled with
 // -ffp-contract=off so the expression is evaluated exactly as written),
 // lays the job out in the caller's arena, runs the job state machine and
-// launches the kernels of ee_kernels.hip.  The batch path keeps a plan per
+// launches the kernels of the .hip files.  The batch path keeps a plan per
 // job set (device work queue + job table + a HIP graph of the launches).
 #include <hip/hip_runtime.h>
 
@@ -407,10 +407,10 @@ int march_block(const ee_job* j) {
 
 // Segments per trajectory of the plane-marching kernel for this job, or 0 if
 // the two-pass kernel runs it.  The march reads and writes each plane once
-// per sweep (2 B per site against the two-pass kernel's 3 B), but both
-// kernels are bound by their issue rate and latency rather than by HBM,
-// and the march, with one row per lane between barriers, runs slower
-// (96^3, n = 2, 256 trajectories: 828 attempts/ns against 1213), so it runs
+// per sweep (2 B per site against the two-pass kernel's 3 B), but the march,
+// with one row per lane between barriers, is bound by its issue rate and
+// latency, and runs slower (96^3, n = 2: 828-890 attempts/ns at 256
+// trajectories against the two-pass kernel's 1650 at 32), so it runs
 // only when EE_LAUNCH_MARCH asks for it.  A workgroup marches one segment of
 // one replica of one trajectory, and each segment boundary costs a fix-up
 // pass over two planes; without a segment count in grid_blocks the count
@@ -1099,6 +1099,29 @@ ee_status ee_batch_run(ee_job* const* jobs, int32_t count, int32_t n_therm, void
   return ee_batch_run_cfg(jobs, count, n_therm, nullptr, hip_stream);
 }
 
+// Bytes of tables that the limit of the allocation-free entry point counts:
+// one unit per as many trajectories as the LDS budget holds in their stored
+// size on a workgroup of the config's lanes (else of one lane per four row
+// words, up to 1024).  The launch may take more, smaller units.
+static size_t limit_bytes(ee_job* const* jobs, int count, const ee_launch_cfg& cfg) {
+  int block = cfg.block_threads > 0 ? cfg.block_threads : 64, budget = cfg.lds_bytes > 0 ? cfg.lds_bytes : kDefaultLdsBudget;
+  for (int i = 0; i < count; ++i) {
+    const Layout& L = jobs[i]->L;
+    const long lanes = ((long)jobs[i]->d.n_replicas * L.R * L.G + 3) / 4;
+    if (cfg.block_threads <= 0) block = std::max(block, (int)std::min<long>(1024, (lanes + 63) / 64 * 64));
+    block = std::max(block, min_block(L));
+    budget = std::max(budget, L.traj_words * 4);
+  }
+  size_t units = 0;
+  for (int i = 0; i < count; ++i) {
+    Layout L = jobs[i]->L;
+    L.lds_words = L.traj_words;
+    const int k = choose_slots(L, jobs[i]->d.n_replicas, block, budget, jobs[i]->d.n_traj);
+    units += (jobs[i]->d.n_traj + k - 1) / k;
+  }
+  return align_up(kAlign + sizeof(void*) * count) + sizeof(ee::Unit) * units;
+}
+
 ee_status ee_batch_run_noalloc(ee_job* const* jobs, int32_t count, int32_t n_therm, const ee_launch_cfg* cfg,
                                void* hip_stream) {
   g_err.clear();
@@ -1112,30 +1135,37 @@ ee_status ee_batch_run_noalloc(ee_job* const* jobs, int32_t count, int32_t n_the
   // the tables in the fixed scratch array: [queue counter][job table][units]
   const size_t off_tab = kAlign;
   const size_t off_units = align_up(off_tab + sizeof(void*) * count);
-  const size_t bytes = off_units + sizeof(ee::Unit) * up.units.size();
+  const size_t bytes = limit_bytes(jobs, count, c);
   if (bytes > ee_k_scratch_bytes())
-    return fail(EE_EINVAL, "the batch needs %zu bytes of tables (%d jobs, %zu work units), more than the %zu-byte "
-                "scratch of the allocation-free entry point", bytes, count, up.units.size(), ee_k_scratch_bytes());
+    return fail(EE_EINVAL, "the batch needs %zu bytes of tables (%d jobs), more than the %zu-byte "
+                "scratch of the allocation-free entry point", bytes, count, ee_k_scratch_bytes());
   void* scr = nullptr;
   int rc = ee_k_scratch_ptr(&scr);
   if (rc) return fail(EE_EHIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString((hipError_t)rc));
   for (int i = 0; i < count; ++i)
     if (jobs[i]->stream != stream) HIP_TRY(hipStreamSynchronize(jobs[i]->stream));
-  std::vector<uint8_t> host(bytes - off_tab);
-  for (int i = 0; i < count; ++i) reinterpret_cast<const ee::JobDev**>(host.data())[i] = jobs[i]->dev_jobdev();
-  std::memcpy(host.data() + (off_units - off_tab), up.units.data(), sizeof(ee::Unit) * up.units.size());
   uint8_t* base = reinterpret_cast<uint8_t*>(scr);
   int* queue = reinterpret_cast<int*>(base);
   const ee::JobDev* const* jobtab = reinterpret_cast<const ee::JobDev* const*>(base + off_tab);
   const ee::Unit* units = reinterpret_cast<const ee::Unit*>(base + off_units);
-  // stream-ordered after the previous user of the array on this stream; the
-  // host buffer must outlive the copy, so the call waits for it
-  HIP_TRY(hipMemcpyAsync(base + off_tab, host.data(), host.size(), hipMemcpyHostToDevice, stream));
-  HIP_TRY(hipStreamSynchronize(stream));
-  rc = ee_k_launch_queue_reset(queue, stream);
-  if (rc == 0)
-    rc = ee_k_launch_sweep(any_whole(jobs, count), nullptr, 0, units, (int)up.units.size(), queue, jobtab, ee::kFlagInit | ee::kFlagProto,
-                           n_therm, 0, up.grid, up.block, up.lds, stream);
+  // as many units at a time as the array holds (all of them but for sets near
+  // its limit, which the chosen shape may cut into more units than counted)
+  const size_t cap = (ee_k_scratch_bytes() - off_units) / sizeof(ee::Unit);
+  for (size_t u0 = 0; u0 < up.units.size() && rc == 0; u0 += cap) {
+    const size_t nu = std::min(cap, up.units.size() - u0);
+    std::vector<uint8_t> host(off_units - off_tab + sizeof(ee::Unit) * nu);
+    for (int i = 0; i < count; ++i) reinterpret_cast<const ee::JobDev**>(host.data())[i] = jobs[i]->dev_jobdev();
+    std::memcpy(host.data() + (off_units - off_tab), up.units.data() + u0, sizeof(ee::Unit) * nu);
+    // stream-ordered after the previous user of the array on this stream; the
+    // host buffer must outlive the copy, so the call waits for it
+    HIP_TRY(hipMemcpyAsync(base + off_tab, host.data(), host.size(), hipMemcpyHostToDevice, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    rc = ee_k_launch_queue_reset(queue, stream);
+    if (rc == 0)
+      rc = ee_k_launch_sweep(any_whole(jobs, count), nullptr, 0, units, (int)nu, queue, jobtab,
+                             ee::kFlagInit | ee::kFlagProto, n_therm, 0, std::min(up.grid, (int)nu), up.block, up.lds,
+                             stream);
+  }
   if (rc == 0) rc = ee_k_launch_estimate(jobtab, count, max_traj(jobs, count), stream);
   if (rc) return fail(EE_EHIP, "allocation-free batch launch: %s", hipGetErrorString((hipError_t)rc));
   mark_batch_done(jobs, count, n_therm, stream);

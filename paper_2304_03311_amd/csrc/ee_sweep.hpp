@@ -61,8 +61,9 @@ __device__ __forceinline__ uint32_t edge_word(const uint32_t A[W]) {
 // Bound by VALU issue: 280 instructions for the 32 sites of a step (bulk, 2D;
 // 298 in 3D), of which 148 are the four Philox calls.  Measured against one
 // row at a time with scalar keys and the rows in storage order: 2D 64x64, 64
-// jobs x 1024 trajectories 151 against 177 ms (10.6 against 12.3
-// instructions per attempt), 3D 32^3 x 512 trajectories 21.4 against 25.1 ms.
+// jobs x 1024 trajectories 151 against 177 ms (145 with the whole-region
+// protocol in a kernel of its own), 3D 32^3 x 512 trajectories 21.4 (20.9)
+// against 25.1 ms.
 // has_cut: some lane of the wave starts with rows next to the cut.  cut_mask:
 // the lane's glued_bits in its rows next to the cut (0 if it has none), of
 // word q and x parity p moved to bit 4 p + q of each byte.  has_ramp: these

@@ -68,3 +68,19 @@ def test_rows_with_pad_sites_match_oracle(dim, lx, block):
             opts["l"], lx if opts.get("whole") else lx - 1)})
         if 2 * s.n * s.lt * s.ly * -(-lx // 8) * 4 <= 160 * 1024 - 256:
             check(s, dict(block_threads=block, lds_bytes=1024), n_therm=1)
+
+
+def test_noalloc_batch_of_more_units_than_its_scratch_holds():
+    # accepted (ten of these trajectories in 80 KB), and run one to a workgroup:
+    # 136,070 units of 16 bytes, in two pieces
+    specs = [ee.JobSpec(dim=2, lt=64, lx=64, ly=1, n=2, beta=BC2, l=9, n_step=1, n_traj=n, seed=88 + i)
+             for i, n in enumerate((65535, 65535, 5000))]
+    out = []
+    for run in (ee.batch_run_noalloc, ee.batch_run):
+        jobs = [ee.Job(s) for s in specs]
+        run(jobs, 0, cfg=None)
+        out.append([(j.work(), j.estimate().dF) for j in jobs])
+        for j in jobs:
+            j.close()
+    for (wa, fa), (wb, fb) in zip(*out):
+        assert np.array_equal(wa, wb) and fa == fb
