@@ -82,12 +82,12 @@ stream_row_kernel(ee::StreamArgs a, int c, uint32_t g, int pos, int dpos, int wo
   uint32_t j;
   int slot, w;
   if (!stream_lane(a, W, j, slot, w)) return;
-  const HbmMem mem{P.spins + (size_t)j * P.traj_words};
+  uint32_t* const traj = P.spins + (size_t)j * P.traj_words;
+  const HbmMem own{traj + plane_start(P, c)}, oth{traj + plane_start(P, c ^ 1)};
   PhKey K;
   key_unit(K, P);
   key_sweep(K, P, g, j);
-  const int G = P.G, LyG = P.ly * G, ltLyG = P.lt * LyG, cw = P.n * P.R * G;
-  const uint32_t bC = 4u * (uint32_t)(c * cw), bO = 4u * (uint32_t)((c ^ 1) * cw);
+  const int G = P.G, LyG = P.ly * G, ltLyG = P.lt * LyG;
   const int wl = (w == 0) ? G - 1 : w - 1, wr = (w + W == G) ? 0 : w + W;
   int dI = 0;
   for (int m = slot; m < a.rows; m += a.slots) {
@@ -101,12 +101,12 @@ stream_row_kernel(ee::StreamArgs a, int c, uint32_t g, int pos, int dpos, int wo
     const uint32_t c0 = (uint32_t)(rho * P.G8 + (w >> 1));
     const uint32_t c3 = (1u << 28) | ((uint32_t)r << 1) | (uint32_t)c;
     K.x0 = c3 ^ P.key1;
-    const uint32_t off = 4u * (uint32_t)(m * G + w);
+    const uint32_t off = plane_byte(m * G + w);
     const auto row = [&](auto cut) {
       constexpr bool CUT = decltype(cut)::value;
       const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
-      const uint32_t ag = (CUT && t <= 1) ? bO + 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : bO + off;
-      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, bO + off, mem, ag, w, wl, wr, a.thr, c, g, j, pos, dpos,
+      const uint32_t ag = (CUT && t <= 1) ? plane_byte(glued_row(P, r, t, y) * G + w) : off;
+      update_row<DIM, FULL, W, CUT, false>(P, K, own, off, oth, off, oth, ag, w, wl, wr, a.thr, c, g, j, pos, dpos,
                                            work != 0, dI, t, y, tmo, tpo, ymo, ypo, c0, c3);
     };
     if (__builtin_amdgcn_ballot_w64(t <= 1) != 0) row(std::true_type{});
@@ -299,7 +299,7 @@ __device__ __forceinline__ void march_colour(const JP& P, PhKey& K, uint32_t* wi
                                              uint32_t j, int pos, int dpos, bool work, int& dI, const RowDesc& d0) {
   const int G = P.G, GW = G / W, ly = P.ly;
   const LdsMem mem;
-  const HbmMem hbm{traj};
+  const HbmMem hbm{traj + plane_start(P, 1)};  // the glued partners' plane
   const uint32_t ring = lds_address(win);
   const uint32_t own = ring + 4u * (uint32_t)(s0 * PW + c * ly * G);
   const uint32_t oth = ring + 4u * (uint32_t)(s0 * PW + (c ^ 1) * ly * G);
@@ -311,7 +311,7 @@ __device__ __forceinline__ void march_colour(const JP& P, PhKey& K, uint32_t* wi
     // glued partners: colour 1 of replica r+1 in plane 1 (t = 0) or of
     // replica r-1 in plane 0 (t = 1), in HBM
     const int rgl = (t == 0) ? ((r + 1 == P.n) ? 0 : r + 1) : ((r == 0) ? P.n - 1 : r - 1);
-    const int ogl = ((P.n + rgl) * P.R + (1 - t) * ly) * G;
+    const int ogl = (rgl * P.R + (1 - t) * ly) * G;
     RowDesc d = d0;
     for (int it = threadIdx.x; it < ly * GW;) {
       const int y = d.y, w = d.w;
@@ -319,7 +319,7 @@ __device__ __forceinline__ void march_colour(const JP& P, PhKey& K, uint32_t* wi
       const int ymo = (y == 0) ? (ly - 1) * G : -G, ypo = (y == ly - 1) ? -(ly - 1) * G : G;
       const uint32_t c0 = (uint32_t)((t * ly + y) * P.G8 + (w >> 1));
       const uint32_t off = 4u * (uint32_t)(y * G + w);
-      update_row<DIM, FULL, W, CUT, false>(P, K, mem, own + off, oth + off, hbm, CUT ? 4u * (uint32_t)ogl + off : 0u,
+      update_row<DIM, FULL, W, CUT, false>(P, K, mem, own + off, mem, oth + off, hbm, CUT ? plane_byte(ogl) + off : 0u,
                                            w, wl, wr, thr, c, g, j, pos, dpos, work, dI, t, y, tmo, tpo, ymo, ypo,
                                            c0, c3);
       it += blockDim.x;
@@ -398,11 +398,10 @@ __device__ __forceinline__ void fixup_plane(const JP& P, const uint32_t* thr, in
   const uint32_t j = (uint32_t)jj;
   uint32_t* traj = P.spins + (size_t)j * P.traj_words;
   const int G = P.G, GW = G / W, ly = P.ly, R = P.R;
-  const HbmMem mem{traj};
+  const HbmMem own{traj + plane_start(P, 1)}, oth{traj};
   PhKey K;
   key_unit(K, P);
   key_sweep(K, P, g, j);
-  const uint32_t bC = 4u * (uint32_t)(P.n * R * G);  // colour 1; colour 0 is at 0
   const int LyG = ly * G, ltLyG = P.lt * LyG;
   const int tpo = LyG - ((t == P.lt - 1) ? ltLyG : 0);
   const int tmo = -LyG + ((t == 0) ? ltLyG : 0);
@@ -418,9 +417,9 @@ __device__ __forceinline__ void fixup_plane(const JP& P, const uint32_t* thr, in
       const uint32_t c0 = (uint32_t)((t * ly + y) * P.G8 + (w >> 1));
       const uint32_t c3 = (1u << 28) | ((uint32_t)r << 1) | 1u;
       K.x0 = c3 ^ P.key1;
-      const uint32_t off = 4u * (uint32_t)(rowbase + w);
-      const uint32_t ag = CUT ? 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : off;
-      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, off, mem, ag, w, wl, wr, thr, 1, g, j, pos, dpos,
+      const uint32_t off = plane_byte(rowbase + w);
+      const uint32_t ag = CUT ? plane_byte(glued_row(P, r, t, y) * G + w) : off;
+      update_row<DIM, FULL, W, CUT, false>(P, K, own, off, oth, off, oth, ag, w, wl, wr, thr, 1, g, j, pos, dpos,
                                            false, dI, t, y, tmo, tpo, ymo, ypo, c0, c3);
     }
   };
@@ -492,7 +491,11 @@ __global__ void __launch_bounds__(256) stream_init_kernel(const JobDev* J, int l
   const JP P = load_jp(J);
   const uint32_t j = blockIdx.y;
   const int lt_ = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lt_ < lanes) init_spins<false>(P, HbmMem{P.spins + (size_t)j * P.traj_words}, 0u, j, lt_, lanes, P.G);
+  if (lt_ >= lanes) return;
+  uint32_t* const traj = P.spins + (size_t)j * P.traj_words;
+  // unsigned: the last step may pass 2^31
+  for (uint32_t q = (uint32_t)lt_; q < (uint32_t)P.traj_words; q += (uint32_t)lanes)
+    traj[q] = init_word(P, j, (int)q).word;
 }
 
 __global__ void zero_work_kernel(const JobDev* J) {

@@ -215,7 +215,8 @@ __device__ __forceinline__ bool tied(uint32_t d) { return ((d & 0xFFFFu) == 0) |
 
 // ---------------------------------------------------------------------------
 // Spin words in memory.  A location is a byte address: in LDS, or relative to
-// the trajectory's first word in device memory.  The W consecutive words of
+// the start of a colour plane of the trajectory in device memory (ee_lanes.hpp:
+// plane_start, plane_byte).  The W consecutive words of
 // a lane are one 4W-byte access.  Where W is 2 or 4, the address is 4W-byte
 // aligned (the row pitch G and every plane and trajectory offset are
 // multiples of W), and the lanes of a wave cover consecutive LDS banks; W
@@ -235,7 +236,7 @@ struct LdsMem {
   __device__ __forceinline__ ptr<T> at(uint32_t a) const { return (ptr<T>)(uintptr_t)a; }
 };
 struct HbmMem {
-  uint32_t* base;  // the trajectory (uniform)
+  uint32_t* base;  // a colour plane of the trajectory (uniform)
   template <typename T>
   using ptr = __attribute__((address_space(1))) T*;
   template <typename T>
@@ -563,11 +564,11 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 
 // The Metropolis update of the sites of one row of colour c that a lane owns
 // (words w .. w+W-1 of the row), parity of the row known only at run time.
-//   aC, aO  locations of word w of the row in its own colour plane and in the
-//           other one
+//   own, aC and oth, aO  locations of word w of the row in its own colour
+//           plane and in the other one
 //   tmo, tpo, ymo, ypo  word offsets from aO of the same words in rows t-1,
 //           t+1, y-1 and y+1 (periodic)
-//   gmem, ag  where the glued partner row is (CUT; a location that may be
+//   glu, ag  where the glued partner row is (CUT; a location that may be
 //           read also for rows away from the cut)
 //   (r, t, y)  the row; c0, c3 Philox counter words 0 and 3 of its first call
 // FULL: lx/2 is a multiple of 4 (no pad bytes, x-neighbours by byte
@@ -577,8 +578,8 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // 2 takes the next one).  CUT: the code for rows next to the cut (t = 0, 1)
 // is compiled in; without it the row must have t > 1.
 template <int DIM, bool FULL, int W, bool CUT, bool LA, typename M, typename GM>
-__device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M& mem, const uint32_t aC,
-                                           const uint32_t aO, const GM& gmem, const uint32_t ag, const int w,
+__device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M& own, const uint32_t aC, const M& oth,
+                                           const uint32_t aO, const GM& glu, const uint32_t ag, const int w,
                                            const int wl, const int wr, const uint32_t* __restrict__ thr, const int c,
                                            const uint32_t g, const uint32_t j, const int pos, const int dpos,
                                            const bool work, int& dI, const int t, const int y, const int tmo,
@@ -595,16 +596,16 @@ __device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M&
   CutRow<W> cr[1];
   // towards the cut and away from it, by address: the sum is symmetric
   const int toff0 = (CUT && t == 1) ? tmo : tpo, toff1 = (CUT && t == 1) ? tpo : tmo;
-  ld_words<W>(mem, aO, A);
-  const uint32_t E = ld_word(mem, at((p ? wr : wl) - w));
-  ld_words<W>(mem, aC, S[0]);
-  ld_words<W>(mem, at(toff0), Tp);
-  ld_words<W>(mem, at(toff1), Tm);
-  if constexpr (CUT) ld_words<W>(gmem, ag, cr[0].Tg);
+  ld_words<W>(oth, aO, A);
+  const uint32_t E = ld_word(oth, at((p ? wr : wl) - w));
+  ld_words<W>(own, aC, S[0]);
+  ld_words<W>(oth, at(toff0), Tp);
+  ld_words<W>(oth, at(toff1), Tm);
+  if constexpr (CUT) ld_words<W>(glu, ag, cr[0].Tg);
   uint32_t Ym[W], Yp[W];
   if constexpr (DIM == 3) {
-    ld_words<W>(mem, at(ymo), Ym);
-    ld_words<W>(mem, at(ypo), Yp);
+    ld_words<W>(oth, at(ymo), Ym);
+    ld_words<W>(oth, at(ypo), Yp);
   } else {
 #pragma unroll
     for (int q = 0; q < W; ++q) Ym[q] = Yp[q] = 0;
@@ -650,10 +651,10 @@ __device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M&
   for (int q = 0; q < W; ++q) fm[q] = fmask;
   decide_rows<DIM, W, 1, CUT>(P, U, &c0, c3, g, j, w, fm, thr, S, idx, cr, pos, dpos, work, dI, Sn,
                               [&](int, uint32_t* Tc, uint32_t* Tg) {
-                                ld_words<W>(mem, at(toff0), Tc);
-                                ld_words<W>(gmem, ag, Tg);
+                                ld_words<W>(oth, at(toff0), Tc);
+                                ld_words<W>(glu, ag, Tg);
                               });
-  st_words<W>(mem, aC, Sn[0]);
+  st_words<W>(own, aC, Sn[0]);
 }
 
 // One half-sweep of colour c over the lane's rows of one trajectory, in the
@@ -687,7 +688,7 @@ __device__ __forceinline__ void half_sweep(const JP& P, PhKey& K, const Lane& ln
       constexpr bool CUT = decltype(cut)::value;
       const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
       const uint32_t ag = (CUT && t <= 1) ? bO + 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : bO + off;
-      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, bO + off, mem, ag, w, ln.wl, ln.wr, thr, c, g, j, pos,
+      update_row<DIM, FULL, W, CUT, false>(P, K, mem, bC + off, mem, bO + off, mem, ag, w, ln.wl, ln.wr, thr, c, g, j, pos,
                                            dpos, work, dI, t, y, tmo, tpo, ymo, ypo, c0, c3);
     };
     // the code for rows next to the cut runs only where some lane of the
@@ -710,27 +711,29 @@ __device__ __forceinline__ void half_sweep(const JP& P, PhKey& K, const Lane& ln
   }
 }
 
-// Initial spins (phase 0 of the Philox streams): +1 iff u < 2^31.  PM: into
-// the class-by-class rows of the parity-major order, pitch words each.
-template <bool PM, typename M>
-__device__ void init_spins(const JP& P, const M& mem, uint32_t base, uint32_t j, int lt_, int T, int pitch) {
+// Initial spins (phase 0 of the Philox streams) of word q of trajectory j in
+// storage order: +1 iff u < 2^31.  Word w of row rho of its replica, row rowg
+// over colours and replicas.
+struct InitWord {
+  uint32_t word;
+  int w, rowg, rho;
+};
+__device__ __forceinline__ InitWord init_word(const JP& P, uint32_t j, int q) {
   const int nR = P.n * P.R;
-  for (int q = lt_; q < P.traj_words; q += T) {
-    const int w = q % P.G;
-    const int rowg = q / P.G;
-    const int c = rowg / nR;
-    const int row = rowg - c * nR;
-    const int r = row / P.R;
-    const int rho = row - r * P.R;
-    uint32_t u[4];
-    philox10((uint32_t)(rho * P.G + w), 0u, j, ((uint32_t)r << 1) | (uint32_t)c, P.key0, P.key1, u);
-    uint32_t word = 0;
+  InitWord I;
+  I.w = q % P.G;
+  I.rowg = q / P.G;
+  const int c = I.rowg / nR;
+  const int row = I.rowg - c * nR;
+  const int r = row / P.R;
+  I.rho = row - r * P.R;
+  uint32_t u[4];
+  philox10((uint32_t)(I.rho * P.G + I.w), 0u, j, ((uint32_t)r << 1) | (uint32_t)c, P.key0, P.key1, u);
+  I.word = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (4 * w + i < P.H) word |= (uint32_t)(u[i] < 0x80000000u) << (8 * i);
-    const int at = PM ? (rowg - rho + pm_row(P, rho)) * pitch + w : q;
-    st_words<1>(mem, base + 4u * (uint32_t)at, &word);
-  }
+  for (int i = 0; i < 4; ++i)
+    if (4 * I.w + i < P.H) I.word |= (uint32_t)(u[i] < 0x80000000u) << (8 * i);
+  return I;
 }
 
 }  // namespace

@@ -36,7 +36,7 @@ __device__ __forceinline__ void half_sweep_la(const JP& P, const Lane& ln, const
     constexpr bool CUT = decltype(cut)::value;
     const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
     const uint32_t ag = (CUT && t <= 1) ? bO + 4u * (uint32_t)(glued_row(P, r, t, y) * G + w) : bO + off;
-    update_row<DIM, FULL, W, CUT, true>(P, Kn, mem, bC + off, bO + off, mem, ag, w, ln.wl, ln.wr, thr, c, g, j, pos,
+    update_row<DIM, FULL, W, CUT, true>(P, Kn, mem, bC + off, mem, bO + off, mem, ag, w, ln.wl, ln.wr, thr, c, g, j, pos,
                                         dpos, work, dI, t, y, tmo, tpo, ymo, ypo, c0, c3, U);
   };
   if (__builtin_amdgcn_ballot_w64(t <= 1) != 0) row(std::true_type{});
@@ -269,6 +269,18 @@ __device__ __forceinline__ int lds_row(const JP& P, int rowg) {
   return rowg - rho + pm_row(P, rho);
 }
 
+// Initial spins into LDS (PM: into the class-by-class rows of the parity-major
+// order), pitch words per row.
+template <bool PM>
+__device__ void init_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T, int pitch) {
+  const LdsMem mem;
+  for (int q = lt_; q < P.traj_words; q += T) {
+    const InitWord I = init_word(P, j, q);
+    const int at = PM ? (I.rowg - I.rho + pm_row(P, I.rho)) * pitch + I.w : q;
+    st_words<1>(mem, base + 4u * (uint32_t)at, &I.word);
+  }
+}
+
 template <bool PM>
 __device__ void load_spins(const JP& P, uint32_t base, uint32_t j, int lt_, int T, int pitch) {
   const LdsMem mem;
@@ -360,7 +372,7 @@ __device__ __noinline__ void run_unit(const JobDev* J_, uint32_t lds, uint32_t t
   }
   if (pitch != P.G) __syncthreads();
   if (active) {
-    if (flags & ee::kFlagInit) init_spins<PM>(P, mem, L, j, lt_, T, pitch);
+    if (flags & ee::kFlagInit) init_spins<PM>(P, L, j, lt_, T, pitch);
     else load_spins<PM>(P, L, j, lt_, T, pitch);
   }
   PhKey K;

@@ -1,0 +1,116 @@
+"""Streamed trajectories of more than 4 GiB: the offsets by which the kernels
+reach their words (csrc/ee_lanes.hpp: plane_start, plane_byte), built for the
+host, against 64-bit arithmetic around 4 and 8 GiB; and, on the GPU, sweeps of
+such trajectories at a temperature where every spin's move is known."""
+from __future__ import annotations
+
+import os
+import subprocess
+import sys
+
+import pytest
+
+from oracle import oracle as eo
+from paper_2304_03311_amd import ee
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2304_03311_amd", "csrc")
+
+HARNESS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <initializer_list>
+#include "ee_lanes.hpp"
+using namespace ee::lanes;
+typedef unsigned long long u64;
+
+int main(int argc, char** argv) {
+  JP P{};
+  P.n = atoi(argv[1]); P.lt = atoi(argv[2]); P.ly = atoi(argv[3]); P.G = atoi(argv[4]);
+  P.R = P.lt * P.ly;
+  const u64 rows = (u64)P.n * P.R, plane = rows * P.G;
+  int fails = 0;
+  for (int c = 0; c < 2; ++c)
+    for (u64 near : {(u64)0, rows / 2, rows - 1, ((1ull << 30) / P.G) % rows, rows - (u64)P.R, (u64)P.R - 1})
+      for (int d = -1; d <= 1; ++d) {
+        const u64 row = (near + rows + d) % rows;
+        for (int w : {0, P.G - 1}) {
+          const uint32_t off = plane_byte((int)(row * P.G) + w);
+          if (4 * plane_start(P, c) + off != 4 * (c * plane + row * P.G + w)) ++fails;
+          // neighbour rows of the same replica: offsets of either sign, modulo 2^32
+          const int r = (int)(row / P.R), t = (int)(row % P.R) / P.ly, y = (int)(row % P.R) % P.ly;
+          const int LyG = P.ly * P.G, tpo = LyG - ((t == P.lt - 1) ? P.lt * LyG : 0), tmo = -LyG + ((t == 0) ? P.lt * LyG : 0);
+          const auto at = [&](int tt) { return 4 * (((u64)r * P.R + (u64)tt * P.ly + y) * P.G + w); };
+          if (off + 4u * (uint32_t)tpo != at((t + 1) % P.lt) || off + 4u * (uint32_t)tmo != at((t + P.lt - 1) % P.lt)) ++fails;
+          if (t <= 1 && plane_byte(glued_row(P, r, t, y) * P.G + w) !=
+                            4 * (((u64)((t == 0) ? (r + 1) % P.n : (r + P.n - 1) % P.n) * P.R + (u64)(1 - t) * P.ly + y) * P.G + w))
+            ++fails;
+        }
+      }
+  printf("fails %d\n", fails);
+  return fails != 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def offsets(tmp_path_factory):
+    d = tmp_path_factory.mktemp("offsets")
+    (d / "o.cpp").write_text(HARNESS)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Wno-unknown-pragmas", "-I", CSRC, str(d / "o.cpp"), "-o", str(d / "o")], check=True)
+    return str(d / "o")
+
+
+# replicas, lt, ly, words per row: trajectories of a row less than 2^30 words,
+# of 2^30 and of a row more; the largest below 2^31; small ones
+@pytest.mark.parametrize("shape", [(2, 16777214, 1, 16), (2, 16777216, 1, 16), (2, 16777218, 1, 16),
+                                   (44, 460, 460, 58), (11, 50000000, 1, 1), (2, 536870910, 1, 1), (2, 8, 1, 4),
+                                   (3, 4, 6, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_offsets_reach_every_word(offsets, shape):
+    r = subprocess.run([offsets, *map(str, shape)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+# 1.1e9 words each.  At beta = 20 a spin moves where two or more of its four
+# neighbours are anti-aligned, and else with a chance of 2^-32 per attempt
+# (about one of these attempts; its neighbours may follow): up to 40 sites
+# may differ from the rule without it.  With no glued column the replicas are
+# independent, so the rule is applied one replica at a time.
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,lt,lx,flags", [(11, 50000000, 2, ee.EE_LAUNCH_TWO_PASS),
+                                           (44, 3125000, 32, ee.EE_LAUNCH_TWO_PASS),
+                                           (44, 3125000, 32, ee.EE_LAUNCH_MARCH)], ids=["lx2", "lx32", "lx32_march"])
+def test_trajectory_above_4_gib(n, lt, lx, flags):
+    import torch
+
+    H, G, seed = lx // 2, (lx // 2 + 3) // 4, 77
+    print(f"[gpu] n {n} lt {lt} lx {lx} flags {flags}", file=sys.stderr, flush=True)
+    j = ee.Job(ee.JobSpec(dim=2, lt=lt, lx=lx, ly=1, n=n, beta=20.0, l=0, n_step=1, n_traj=1, seed=seed))
+    words = 2 * n * lt * G
+    assert 4 * words > 1 << 32
+    spins = j.arena[j.bytes - -(-4 * words // 256) * 256:][:4 * words].view(2, n, lt, 4 * G)
+    j.set_launch({"flags": flags})
+    j.thermalize(0)
+    torch.cuda.synchronize()
+    for c, r, t in ((0, 0, 0), (0, n - 1, lt - 1), (1, 0, 0), (1, n // 2, 5), (1, n - 1, 0), (1, n - 1, lt - 1)):
+        u = [eo.philox((t * G + w, 0, 0, (r << 1) | c), (seed, 0)) for w in range(G)]
+        want = [int(u[h >> 2][h & 3] < 1 << 31) for h in range(H)] + [0] * (4 * G - H)
+        assert spins[c, r, t].tolist() == want, (c, r, t)
+    old = spins.clone()
+    j.thermalize(1)
+    torch.cuda.synchronize()
+    odd = (torch.arange(lt, device="cuda") & 1).bool()[:, None]
+    wrong = 0
+    for r in range(n):
+        s = old[:, r, :, :H].clone()
+        for c in (0, 1):
+            o = s[1 - c]
+            right = odd if c == 0 else ~odd  # x parity 1: the other x neighbour is the next one
+            x = torch.where(right, torch.roll(o, -1, 1), torch.roll(o, 1, 1))
+            anti = (o ^ s[c]) + (x ^ s[c]) + (torch.roll(o, 1, 0) ^ s[c]) + (torch.roll(o, -1, 0) ^ s[c])
+            s[c] ^= (anti >= 2).to(torch.uint8)
+        wrong += int((s != spins[:, r, :, :H]).sum())
+    moved = int((old[1, n - 1] != spins[1, n - 1]).sum())
+    assert moved > lt * H // 100
+    j.close()
+    assert wrong <= 40, wrong
