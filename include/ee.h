@@ -95,7 +95,9 @@ typedef enum {
  * Constraints: dim in {2,3}; lt, lx even >= 2; ly == 1 for dim 2, even >= 2
  * for dim 3; n_replicas >= 2; beta finite >= 0; 0 <= l < lx (1 <= l <= lx
  * with EE_FLAG_WHOLE); n_step >= 1;
- * 1 <= n_traj <= 65535.  Violations return EE_EINVAL.
+ * 1 <= n_traj <= 65535.  Violations return EE_EINVAL.  A trajectory (two
+ * colour planes of int8 rows padded to words of four sites) must take less
+ * than 8 GiB (EE_EUNSUPPORTED).
  */
 typedef struct {
   int32_t dim;          /* D = 2 or 3                                        */

@@ -103,6 +103,10 @@ ee_status validate(const ee_job_desc* d) {
   if (2.0 * d->n_replicas * d->ly * ramped_cols * (double)d->n_step >= 2147483647.0)
     return fail(EE_EINVAL, "the work bound 2*n*ly*(ramped columns)*n_step exceeds the int32 range");
   if ((double)d->lt * d->ly * d->lx > 1e8) return fail(EE_EINVAL, "lattice too large");
+  // the kernels and the layout below index a trajectory's words by int
+  const int64_t words = 2 * (int64_t)d->n_replicas * d->lt * d->ly * ((d->lx / 2 + 3) / 4);
+  if (words > 0x7FFFFFFF)
+    return fail(EE_EUNSUPPORTED, "a trajectory of %lld bytes (limit: below 8 GiB)", 4 * (long long)words);
   return EE_OK;
 }
 
@@ -168,7 +172,7 @@ int min_block(const Layout& L) { return (L.G + 63) / 64 * 64; }
 // A job runs on chip when one trajectory fits a workgroup's LDS and one row
 // fits a workgroup's lanes; otherwise it is streamed from HBM.
 bool fits_on_chip(const Layout& L) {
-  return L.traj_words * 4 <= ee_k_max_lds_bytes() && min_block(L) <= kMaxBlock;
+  return L.traj_words <= ee_k_max_lds_bytes() / 4 && min_block(L) <= kMaxBlock;
 }
 constexpr int kDefaultLdsBudget = 80 * 1024;  // two workgroups per CU
 
@@ -818,9 +822,9 @@ ee_status ee_job_footprint(const ee_job_desc* desc, size_t* bytes) {
   Layout L = layout_of(desc);
   if (!fits_on_chip(L) && desc->spin_format != EE_SPINS_INT8)
     return fail(EE_EUNSUPPORTED,
-                "a trajectory of %d bytes with rows of %d words exceeds the on-chip tile (%d bytes, %d words "
+                "a trajectory of %lld bytes with rows of %d words exceeds the on-chip tile (%d bytes, %d words "
                 "per row); such lattices are streamed from HBM and need EE_SPINS_INT8 storage",
-                L.traj_words * 4, L.G, ee_k_max_lds_bytes(), kMaxBlock);
+                4LL * L.traj_words, L.G, ee_k_max_lds_bytes(), kMaxBlock);
   *bytes = L.total;
   return EE_OK;
 }
