@@ -144,6 +144,12 @@ ee_status ee_job_footprint(const ee_job_desc* desc, size_t* bytes);
  * streamed from HBM (per-job path only).  No device work. */
 ee_status ee_job_on_chip(const ee_job_desc* desc, int32_t* on_chip);
 
+/* LDS bytes that one trajectory takes on chip: the unit in which a launch's
+ * lds_bytes is filled.  Rows whose words do not fill whole lanes are padded
+ * there where the trajectory still fits, so it can exceed the int8 storage
+ * size.  No device work. */
+ee_status ee_job_lds_bytes(const ee_job_desc* desc, size_t* bytes);
+
 /* Validate desc, build the geometry and the uint32 threshold tables on the
  * host (FP64 libm exp, Sec. 3 couplings), and enqueue their upload into the
  * arena on hip_stream.  arena: device pointer, 256-byte aligned, at least

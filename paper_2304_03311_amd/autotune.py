@@ -44,8 +44,8 @@ CANDIDATES = [
 
 
 def traj_bytes(s: ee.JobSpec) -> int:
-    """LDS bytes of one trajectory (int8 colour planes, whole 32-bit words per row)."""
-    return 2 * s.n * s.lt * s.ly * ((s.lx // 2 + 3) // 4) * 4
+    """LDS bytes of one trajectory (int8 colour planes, rows padded to whole lanes)."""
+    return ee.ee_job_lds_bytes(s.desc())
 
 
 def candidates_for(specs: list[ee.JobSpec]) -> list[dict]:

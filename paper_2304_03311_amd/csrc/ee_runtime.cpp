@@ -838,6 +838,15 @@ ee_status ee_job_on_chip(const ee_job_desc* desc, int32_t* on_chip) {
   return EE_OK;
 }
 
+ee_status ee_job_lds_bytes(const ee_job_desc* desc, size_t* bytes) {
+  g_err.clear();
+  if (!bytes) return fail(EE_EINVAL, "bytes is NULL");
+  ee_status s = validate(desc);
+  if (s) return s;
+  *bytes = (size_t)layout_of(desc).lds_words * 4;
+  return EE_OK;
+}
+
 ee_status ee_job_create(const ee_job_desc* desc, void* dev_arena, size_t arena_bytes, void* hip_stream,
                         ee_job** out) {
   g_err.clear();

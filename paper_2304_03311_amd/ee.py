@@ -57,6 +57,7 @@ _lib = None
 _SIGS = {
     "ee_job_footprint": [ctypes.POINTER(ee_job_desc), ctypes.POINTER(ctypes.c_size_t)],
     "ee_job_on_chip": [ctypes.POINTER(ee_job_desc), ctypes.POINTER(ctypes.c_int32)],
+    "ee_job_lds_bytes": [ctypes.POINTER(ee_job_desc), ctypes.POINTER(ctypes.c_size_t)],
     "ee_job_create": [ctypes.POINTER(ee_job_desc), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
                       ctypes.POINTER(ctypes.c_void_p)],
     "ee_thermalize": [ctypes.c_void_p, ctypes.c_int32],
@@ -131,6 +132,12 @@ def ee_job_on_chip(desc: ee_job_desc) -> bool:
     out = ctypes.c_int32()
     _check("ee_job_on_chip", lib().ee_job_on_chip(ctypes.byref(desc), ctypes.byref(out)))
     return bool(out.value)
+
+
+def ee_job_lds_bytes(desc: ee_job_desc) -> int:
+    out = ctypes.c_size_t()
+    _check("ee_job_lds_bytes", lib().ee_job_lds_bytes(ctypes.byref(desc), ctypes.byref(out)))
+    return int(out.value)
 
 
 def ee_job_create(desc: ee_job_desc, arena_ptr: int, arena_bytes: int, stream: int) -> int:
