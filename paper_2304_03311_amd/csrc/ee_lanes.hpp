@@ -239,7 +239,7 @@ struct PmPos {
 
 template <int DIM>
 EE_HDI PmPos make_pm_pos(const JP& P, const LanePM& lp) {
-  const int half = P.R >> 1, hy = P.ly >> 1;
+  const int hy = P.ly >> 1;
   const bool in = lp.r0 < P.n;  // a slot past the last replica has no rows
   const int m = !in ? 0 : (DIM == 2) ? (lp.t >> 1) : lp.t * hy + (lp.y[0] >> 1);
   PmPos X;
@@ -307,18 +307,22 @@ EE_HDI int pm_lanes(const JP& P, int T, int W) {
   return use_pm(P, lanes, W) ? lanes : 0;
 }
 
+// Instructions of a pair of rows (2D, parity-major order) on a lane of W words,
+// of the compiled loops.
+EE_HDI int step_instr(int W) { return W == 4 ? 300 : W == 3 ? 250 : W == 2 ? 165 : 105; }
+
 // Rows whose words do not split evenly into lanes of several words (lx/2 not
 // a multiple of 4, or an odd word count) are kept in LDS at a pitch of a
 // multiple of the lane's W words; the last lane of a row then has pad sites,
-// which never flip.  W by the instructions of a pair of rows: about 105, 165,
-// 250 and 300 for lanes of 1 to 4 words (3 only where a row is one lane: its
-// Philox calls serve two words each).  22 sites in x: one lane of three words
-// instead of three of one, 250 instructions against 315, and one edge.
+// which never flip.  W by the instructions of a pair of rows (3 only where a
+// row is one lane: its Philox calls serve two words each).  22 sites in x: one
+// lane of three words instead of three of one, 250 instructions against 315,
+// and one edge.
 struct RowPitch {
   int W, pitch;  // words per lane; words per row in LDS, 0: as stored
 };
 EE_HDI RowPitch row_pitch(int H, int G) {
-  const auto cost = [&](int W) { return (G + W - 1) / W * (W == 4 ? 300 : W == 3 ? 250 : W == 2 ? 165 : 105); };
+  const auto cost = [&](int W) { return (G + W - 1) / W * step_instr(W); };
   // what words_per_lane takes for whole rows (1 where lx/2 is no multiple of 4)
   const int plain = (H & 15) == 0 ? 4 : H == 12 ? 3 : (H & 7) == 0 ? 2 : 1;
   if ((H & 3) == 0 && G % plain == 0 && plain > 1) return RowPitch{plain, 0};

@@ -657,11 +657,11 @@ __device__ __forceinline__ void update_row(const JP& P, const PhKey& K, const M&
   st_words<W>(own, aC, Sn[0]);
 }
 
-// One half-sweep of colour c over the lane's rows of one trajectory, in the
-// order of the lane map (any map; the streaming path's and the general
-// on-chip one).  base: location of the trajectory (two colour planes).
-template <int DIM, bool FULL, int W, typename M>
-__device__ __forceinline__ void half_sweep(const JP& P, PhKey& K, const Lane& ln, const M& mem, const uint32_t base,
+// One half-sweep of colour c over the lane's rows of one trajectory on chip, in
+// the order of the lane map.  base: location of the trajectory (two colour
+// planes).
+template <int DIM, bool FULL, int W>
+__device__ __forceinline__ void half_sweep(const JP& P, PhKey& K, const Lane& ln, const LdsMem& mem, const uint32_t base,
                                            const uint32_t* __restrict__ thr, const int c, const uint32_t g,
                                            const uint32_t j, const int pos, const int dpos, const bool work, int& dI) {
   const int G = P.G;

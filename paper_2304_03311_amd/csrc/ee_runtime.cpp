@@ -140,7 +140,11 @@ Layout layout_of(const ee_job_desc* d) {
   return L;
 }
 
-using JP_shape = ee::lanes::JP;  // only the extents are set
+// What the launch-shape model knows of a job's lattice.
+struct Rows {
+  ee::lanes::JP P;       // only the extents are set
+  int rag_W, rag_pitch;  // rows with pad sites: words per lane and pitch in LDS (0: as stored)
+};
 
 struct DeviceInfo {
   int cus = 0;
@@ -193,35 +197,35 @@ constexpr int kDefaultLdsBudget = 80 * 1024;  // two workgroups per CU
 // lanes in a wave, two waves per CU: 13.7 ms of sweeps with these kernels, now
 // 5.2; the 2D 256 x 32 cylinder, 32 jobs x 256: 27.4 ms, now 23.2.
 // ---------------------------------------------------------------------------
-JP_shape shape_of(const ee_job_desc& d, const Layout& L) {
-  JP_shape P{};
-  P.dim = d.dim; P.n = d.n_replicas; P.ly = d.ly; P.lt = d.lt;
-  P.H = L.H; P.G = L.G; P.R = L.R;
-  P.traj_words = L.rag_pitch;  // half_sweep_instr: the pitch and words per lane of rows with pad sites
-  P.packed_row_words = L.rag_W;
-  return P;
+Rows rows_of(const ee_job_desc& d, const Layout& L) {
+  Rows r{};
+  r.P.dim = d.dim; r.P.n = d.n_replicas; r.P.ly = d.ly; r.P.lt = d.lt;
+  r.P.H = L.H; r.P.G = L.G; r.P.R = L.R;
+  r.rag_W = L.rag_W;
+  r.rag_pitch = L.rag_pitch;
+  return r;
 }
 
 // Instructions per wave of one half-sweep of a trajectory on T lanes.
-double half_sweep_instr(const JP_shape& P, int T) {
+double half_sweep_instr(const Rows& rows, int T) {
+  const ee::lanes::JP& P = rows.P;
   int W = ee::lanes::words_per_lane(P, T);
   const double y = (P.dim == 3) ? 20.0 : 0.0;  // the two more neighbours
   int lanes = (P.H & 3) == 0 ? ee::lanes::pm_lanes(P, T, W) : 0;
   int GW = P.G / W;
-  if (P.traj_words > 0) {  // rows with pad sites: traj_words holds their pitch
-    JP_shape Q = P;
-    Q.G = P.traj_words;
-    const int rW = P.packed_row_words;
-    if (const int n = ee::lanes::pm_lanes(Q, T, rW)) {
+  if (rows.rag_pitch > 0) {
+    ee::lanes::JP Q = P;
+    Q.G = rows.rag_pitch;
+    if (const int n = ee::lanes::pm_lanes(Q, T, rows.rag_W)) {
       lanes = n;
-      W = rW;
-      GW = Q.G / rW;
+      W = rows.rag_W;
+      GW = Q.G / W;
     }
   }
   if (lanes) {
     const int B = lanes / GW / P.n;
     const int steps = (P.R / 2 + B - 1) / B;
-    const double step = (W == 4 ? 300.0 : W == 3 ? 250.0 : W == 2 ? 165.0 : 105.0) + y;
+    const double step = ee::lanes::step_instr(W) + y;
     // the sweep loop, and the rows next to the cut in the waves that have them
     const double waves = (T + 63) / 64, cut = P.n * ((P.ly * GW + 63) / 64);
     return steps * step + 50.0 + 90.0 * std::min(1.0, cut / waves);
@@ -239,7 +243,7 @@ struct Shape {
 
 // The shape for n_traj trajectories (of one job, or of equal jobs together).
 Shape launch_shape(const ee_job_desc& d, const Layout& L, long n_traj) {
-  const JP_shape P = shape_of(d, L);
+  const Rows rows = rows_of(d, L);
   const int tb = L.lds_words * 4;
   const int cus = device_info().cus;
   const long words = (long)d.n_replicas * L.R * L.G;
@@ -252,7 +256,7 @@ Shape launch_shape(const ee_job_desc& d, const Layout& L, long n_traj) {
     const int fit = std::max(1, std::min(160 * 1024 / (k * tb + 256), 16 / waves));  // workgroups per CU
     const int used = (int)std::min<long>(fit, (units + cus - 1) / cus);
     const double per_simd = std::max(1.0, used * waves / 4.0);
-    const double t = half_sweep_instr(P, T) * std::max(6.0, 3.6 * per_simd + 0.8) + 60.0 + 25.0 * waves;
+    const double t = half_sweep_instr(rows, T) * std::max(6.0, 3.6 * per_simd + 0.8) + 60.0 + 25.0 * waves;
     const double rounds = (double)((units + (long)fit * cus - 1) / ((long)fit * cus));
     // a last round that is nearly empty costs a whole one; with many rounds
     // the units' ends spread out
@@ -591,19 +595,19 @@ int lds_budget(ee_job* const* jobs, int count, const ee_launch_cfg& cfg) {
 // Relative cost of one unit of job j (k trajectories per workgroup of
 // `block` lanes).
 double unit_cost(const ee_job* j, int block, int k, int n_therm) {
-  return half_sweep_instr(shape_of(j->d, j->L), block / k) * (double)(n_therm + j->d.n_step);
+  return half_sweep_instr(rows_of(j->d, j->L), block / k) * (double)(n_therm + j->d.n_step);
 }
 
 // Slots per workgroup of job j in a persistent launch whose shape the caller
 // left to the runtime: the k, within the launch's LDS, that finishes most
 // trajectories per issued instruction.
 int auto_slots(const ee_job* j, int block, int lds) {
-  const JP_shape P = shape_of(j->d, j->L);
+  const Rows rows = rows_of(j->d, j->L);
   int best = 1;
   double rate = 0.0;
   for (int k = 1; k <= ee::kMaxSlots && k <= j->d.n_traj; ++k) {
     if (k * j->L.lds_words * 4 > lds || block / k < j->L.G) break;
-    const double r = k / half_sweep_instr(P, block / k);
+    const double r = k / half_sweep_instr(rows, block / k);
     if (r > rate * 1.02) { rate = r; best = k; }
   }
   return best;
@@ -702,7 +706,7 @@ ee_status build_plan(ee_job* const* jobs, int count, int n_therm, const ee_launc
     P->graph = g;
     const void* f_reset = nullptr;
     ee_k_queue_reset_ptr(&f_reset);
-    hipGraphNode_t n_reset, n_ev0, n_sweep, n_ev1;
+    hipGraphNode_t n_reset = nullptr, n_ev0 = nullptr, n_sweep = nullptr, n_ev1 = nullptr;
     int* q = P->dev_queue;
     void* a_reset[] = {&q};
     hipKernelNodeParams kp{};
