@@ -134,6 +134,26 @@ EE_HDI uint32_t glued_mask(int v) {
 }
 
 
+// gm of the W words from word w on: bit 0 of byte i of word q is set where
+// its site, x = 8 (w + q) + 2 i + p, has x < l.  The borrow of a byte-wise
+// comparison against the number of such sites.
+template <int W>
+EE_HDI void glued_bits(const JP& P, bool on, int p, int w, uint32_t gm[W]) {
+  int n = (P.l - p - 8 * w + 1) >> 1;  // glued sites from word w on
+  n = n < 0 ? 0 : (n > 4 * W ? 4 * W : n);
+  const uint32_t v = (uint32_t)(on ? n : 0) * 0x01010101u;
+#pragma unroll
+  for (int q = 0; q < W; ++q) gm[q] = ((v + (0x7C7D7E7Fu - (uint32_t)q * 0x04040404u)) >> 7) & 0x01010101u;
+}
+
+// Word of its lane (0 .. W-1) that holds x = l, the same for every lane, and
+// whether the lane's words hold it, in the rows of parity l & 1.  The
+// whole-region protocol has no single ramped column.
+template <int W>
+EE_HDI int ramp_word(const JP& P) { return (W == 3) ? (P.l >> 3) : ((P.l >> 3) & (W - 1)); }
+template <int W>
+EE_HDI bool ramp_lane(const JP& P, int w) { return !P.whole && w == (P.l >> 3) - ramp_word<W>(P); }
+
 // Parity-major row order (grouped lane map, rows of whole words).  The rows
 // (t, y) of a replica fall into two classes by the parity q of t + y, and in
 // a half-sweep of colour c the sites of the class-q rows have x parity
@@ -153,7 +173,10 @@ EE_HDI uint32_t glued_mask(int v) {
 // their y-neighbour offsets; dt is the t stride (uniform).
 // For the lane's rows next to the cut (if any) it also holds their glued
 // rows' word offsets og and the byte masks gm[p] of the glued columns x < l
-// of its words for x parity p.
+// of its words for x parity p.  The offsets and masks are those of rows in
+// storage order, for the test of the enumeration; the kernel takes its own from
+// PmPos and glued_bits, and only r0, w, wl, wr, c3, t, dt, y, c0 and d_c0 from
+// here.
 struct LanePM {
   int w, wl, wr, r0, dt;
   uint32_t c3;  // Philox counter word 3 without the colour bit
@@ -331,6 +354,31 @@ EE_HDI RowPitch row_pitch(int H, int G) {
     if ((v != 3 || G <= 3) && cost(v) < cost(W)) W = v;
   if (W == 1 && (H & 3) == 0) return RowPitch{1, 0};
   return RowPitch{W, (G + W - 1) / W * W};
+}
+
+// What a lane of W words from word w on of a row with pad sites (H real ones)
+// needs beside its offsets.
+struct RagLane {
+  uint32_t fm[4];    // bit 0 of every real site's byte, per word
+  uint32_t e_shift;  // brings the last site of the row to the top byte (first lane; 0 elsewhere)
+  uint32_t last;     // 0xFF in the lane that holds the row's last site, 0 elsewhere
+  int wl, wr;        // words that hold the left and right edge neighbour
+};
+template <int W>
+EE_HDI RagLane rag_lane(int H, int w) {
+  RagLane r;
+  const int wl = (H - 1) >> 2;  // word of the row's last site
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int n = H - 4 * (w + q);
+    r.fm[q] = (q >= W || n <= 0) ? 0u : 0x01010101u >> (n >= 4 ? 0 : 32 - 8 * n);
+  }
+  const bool last = wl >= w && wl < w + W;
+  r.e_shift = (w == 0) ? 8u * (3 - ((H - 1) & 3)) : 0u;
+  r.last = last ? 0xFFu : 0u;
+  r.wl = (w == 0) ? wl : w - 1;
+  r.wr = last ? 0 : w + W;
+  return r;
 }
 
 }  // namespace lanes

@@ -322,26 +322,6 @@ struct CutRow {
   uint32_t Tc[W], Tg[W];
 };
 
-// gm of the W words from word w on: bit 0 of byte i of word q is set where
-// its site, x = 8 (w + q) + 2 i + p, has x < l.  The borrow of a byte-wise
-// comparison against the number of such sites.
-template <int W>
-__device__ __forceinline__ void glued_bits(const JP& P, bool on, int p, int w, uint32_t gm[W]) {
-  int n = (P.l - p - 8 * w + 1) >> 1;  // glued sites from word w on
-  n = n < 0 ? 0 : (n > 4 * W ? 4 * W : n);
-  const uint32_t v = (uint32_t)(on ? n : 0) * 0x01010101u;
-#pragma unroll
-  for (int q = 0; q < W; ++q) gm[q] = ((v + (0x7C7D7E7Fu - (uint32_t)q * 0x04040404u)) >> 7) & 0x01010101u;
-}
-
-// Word of its lane (0 .. W-1) that holds x = l, the same for every lane, and
-// whether the lane's words hold it, in the rows of parity l & 1.  The
-// whole-region protocol has no single ramped column.
-template <int W>
-__device__ __forceinline__ int ramp_word(const JP& P) { return (W == 3) ? (P.l >> 3) : ((P.l >> 3) & (W - 1)); }
-template <int W>
-__device__ __forceinline__ bool ramp_lane(const JP& P, int w) { return !P.whole && w == (P.l >> 3) - ramp_word<W>(P); }
-
 // The partners counted in the bulk sum: the glued ones where bit 0 of the
 // bytes of gm[q] (glued_bits; other bits do not matter) is set.
 template <int W>

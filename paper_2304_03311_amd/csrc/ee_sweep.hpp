@@ -70,29 +70,6 @@ __device__ __forceinline__ uint32_t edge_word(const uint32_t A[W]) {
 // rows hold the ramped site.
 // RAG: rows with pad sites (row_pitch; P.G is the pitch), whose lanes have
 // what RagLane says.
-struct RagLane {
-  uint32_t fm[4];    // bit 0 of every real site's byte, per word
-  uint32_t e_shift;  // brings the last site of the row to the top byte (first lane; 0 elsewhere)
-  uint32_t last;     // 0xFF in the lane that holds the row's last site, 0 elsewhere
-  int wl, wr;        // words that hold the left and right edge neighbour
-};
-template <int W>
-__device__ __forceinline__ RagLane rag_lane(int H, int w) {
-  RagLane r;
-  const int wl = (H - 1) >> 2;  // word of the row's last site
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = H - 4 * (w + q);
-    r.fm[q] = (q >= W || n <= 0) ? 0u : 0x01010101u >> (n >= 4 ? 0 : 32 - 8 * n);
-  }
-  const bool last = wl >= w && wl < w + W;
-  r.e_shift = (w == 0) ? 8u * (3 - ((H - 1) & 3)) : 0u;
-  r.last = last ? 0xFFu : 0u;
-  r.wl = (w == 0) ? wl : w - 1;
-  r.wr = last ? 0 : w + W;
-  return r;
-}
-
 template <int DIM, int W, int GW, int C, bool RAG = false>
 __device__ __forceinline__ void rows_pm(const JP& P, PhKey& K, const LanePM& lp, const PmPos& pp, const RagLane& rl,
                                         const uint32_t base,
