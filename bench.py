@@ -325,9 +325,10 @@ def main() -> int:
         # HBM roofline of the dominant kernel on the algorithmic bytes (2 per
         # attempt) of one launch; traffic = the bytes rocprofv3 counted per
         # launch (FETCH_SIZE + WRITE_SIZE, calibrated), null when the kernel
-        # changed since they were taken.
+        # changed since they were taken.  The lattices stay in LDS, so frac
+        # can pass 1: what limits the kernel is in limited_by.
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBPS, "unit": "GB/s",
-                     "frac": achieved / PEAK_HBM_GBPS, "traffic": traffic,
+                     "frac": achieved / PEAK_HBM_GBPS, "limited_by": "VALU issue", "traffic": traffic,
                      "kernel": "sweep_kernel (persistent)", "kernel_ms": k_avg_s * 1e3,
                      "bytes_per_attempt": BYTES_PER_ATTEMPT, "attempts_per_launch": attempts_per_step,
                      "attempts_per_ns_in_kernel": attempts_per_step / (k_avg_s * 1e9)},

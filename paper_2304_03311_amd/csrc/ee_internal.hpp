@@ -38,8 +38,12 @@ constexpr int kMaxSlots = 16;  // trajectories per workgroup at most
 constexpr int kSweepTailBytes = 128;
 static_assert((4 + kMaxSlots + 8) * 4 <= kSweepTailBytes, "sweep LDS tables");
 inline int sweep_tail_words(int lds_bytes) { return (lds_bytes + 15) / 16 * 4; }
-constexpr int kEstSmall = 895;  // trajectories of a job whose estimate is one workgroup's (n + 1 lanes and a wave)
-struct EstLaunch {              // one launch of the estimator
+// Trajectories of a job whose estimate is one workgroup's: n + 1 lanes and a
+// wave, 960 lanes.  Near here the one workgroup takes as long as the four
+// launches that larger jobs get (ee_kernels.hip: 895 trajectories 66 against 65
+// us).
+constexpr int kEstSmall = 895;
+struct EstLaunch {  // one launch of the estimator
   const void* fn;
   int gx, gy, block;
 };

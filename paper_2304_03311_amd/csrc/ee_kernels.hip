@@ -3,11 +3,12 @@
 //
 // sweep_kernel (ee_sweep.hpp): one workgroup holds k trajectories of one job
 //   in LDS and runs all their sweeps on chip.  One lane updates W 32-bit
-//   words = 4W same-colour sites of a row.  One Philox4x32-10 call gives a 16-bit field to each of 8 sites; a site
-//   accepts when its field is below the top half of its uint32 threshold,
-//   and only a tie (probability 2^-16) draws the low 16 bits from a second
-//   call.  In batch mode the workgroups are persistent and pull work units
-//   (job, block of trajectories) from a device queue.
+//   words = 4W same-colour sites of a row.  One Philox4x32-10 call gives a
+//   16-bit field to each of 8 sites; a site accepts when its field is below
+//   the top half of its uint32 threshold, and only a tie (probability 2^-16)
+//   draws the low 16 bits from a second call.  In batch mode the workgroups
+//   are persistent and pull work units (job, block of trajectories) from a
+//   device queue.
 // stream_row_kernel: one colour of every trajectory of a job that stays in
 //   HBM; march_kernel and march_fixup_kernel: the same jobs plane by plane
 //   through LDS, on request.
@@ -30,9 +31,10 @@ namespace {
 // ---------------------------------------------------------------------------
 // Streaming path: lattices larger than one workgroup's LDS.  The spins stay
 // in HBM (INT8 colour planes); one launch updates one colour of every
-// trajectory of a job.  Block (x, y) covers lanes of trajectory y; a
-// trajectory has `lanes` lanes, each walking its rows as in the on-chip
-// path.  The neighbour rows are read through the vector caches, and the
+// trajectory of a job.  The grid is one-dimensional, `blocks` workgroups per
+// trajectory, mapped to trajectories as below; of a trajectory's row slots,
+// slot s takes the rows s, s + slots, ... in storage order, one lane per W
+// words.  The neighbour rows are read through the vector caches, and the
 // integer work goes to HBM with 64-bit atomics.
 // ---------------------------------------------------------------------------
 // Workgroups are dispatched to the XCDs (kXcd of them, each with its own L2)
@@ -66,15 +68,18 @@ __device__ __forceinline__ bool stream_lane(const ee::StreamArgs& a, int W, uint
 
 // One row at a time, in storage order over the lanes: consecutive lanes read
 // consecutive words.  (Pairs of neighbouring rows per lane, as on chip, cost
-// 150 instead of 190 instructions a row but read every other row: 5.3 against
-// 3.7 ms on the job below.)  Bound by memory on large jobs: 3D 96^3 x 32
-// trajectories 17 us a launch, 5.0 TB/s on its 3 B per attempt, as fast as a
+// 150 instead of 190 instructions a row but read every other row: 4.9 against
+// 3.7 ms on 96^3 and 9.2 against 7.1 ms on the cylinder below, though 5.3
+// against 5.5 ms on 48^3.)  Bound by memory on large jobs: 3D 96^3 x 32
+// trajectories 16.6 us a launch, 5.1 TB/s on its 3 B per attempt, as fast as a
 // large copy.  What is the same for every lane comes by value in the
 // arguments, with the multipliers of its divisions, and the lanes have no
 // barrier; made from the job's description in memory, behind one dependent
 // load after the other, it was a fifth of the time and kept small jobs at four
 // rows per lane: 96^3 x 32, 110 sweeps 4.05 -> 3.75 ms, 48^3 x 16, 600 sweeps
 // 7.72 -> 5.52 ms, the 2D L = 128 cylinder x 256, 200 sweeps 7.95 -> 7.12 ms.
+// Each colour plane has a base of its own (a trajectory may pass 4 GiB), which
+// also spares every access an addition: 3.65, 5.47 and 7.06 ms.
 template <int DIM, bool FULL, int W>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 stream_row_kernel(ee::StreamArgs a, int c, uint32_t g, int pos, int dpos, int work) {
@@ -528,7 +533,10 @@ __global__ void queue_reset_kernel(int* queue) {
 // wave per 64 of them (est_loo_kernel) and their spread (est_err_kernel).
 // Sums i of a wave start from the full sum's prefix, which is their own
 // beginning.  16384 trajectories: 0.64 against 9.8 ms in one workgroup; 64
-// jobs of 1024: 59 against 145 us; 8 trajectories: 9 against 29 us.
+// jobs of 1024: 59 against 145 us; 8 trajectories: 9 against 29 us.  From the
+// first launch's start to the last one's end, one workgroup / four launches:
+// 64 trajectories 8 / 45 us, 512 34 / 51, 640 41 / 54, 768 54 / 52, 895 66 / 65,
+// 958 70 / 67: they meet at 700 to 900, and the line (kEstSmall) lies there.
 // ---------------------------------------------------------------------------
 #pragma clang fp contract(off)
 constexpr int kEstTileN = 256;  // e_j per workgroup of est_exp_kernel

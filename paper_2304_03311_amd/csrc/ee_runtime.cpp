@@ -456,10 +456,11 @@ int stream_words(const ee_job* j) {
 }
 
 // Arguments of the streaming launches.  A lane takes two rows where that
-// leaves eight waves per SIMD over the GPU, else one: 3D 96^3 x 32 at 1, 2, 4
-// and 8 rows per lane 4.26, 3.75, 3.74 and 4.08 ms, the 2D L = 128 cylinder x
-// 256 7.96, 7.12, 7.43 and 7.66 ms, 3D 48^3 x 16 (3.4 waves per SIMD at one
-// row) 5.52, 5.94, 6.99 and 8.93 ms.  More rows per lane only where the grid
+// leaves eight waves per SIMD over the GPU, else one: 3D 96^3 x 32 (13.5 waves
+// per SIMD at two rows) at 1, 2, 4 and 8 rows per lane 4.19, 3.67, 3.55 and
+// 3.86 ms, the 2D L = 128 cylinder x 256 (16) 7.90, 7.06, 7.26 and 7.47 ms, 3D
+// 48^3 x 16 (1.7; 3.4 at one row) 5.52, 5.95, 6.98 and 8.99 ms.  More rows per
+// lane only where the grid
 // would pass the 2^32 - 1 lanes of a launch.
 ee::StreamArgs stream_args(const ee_job* j) {
   ee::StreamArgs a{};
