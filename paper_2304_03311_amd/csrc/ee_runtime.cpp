@@ -418,7 +418,7 @@ int march_block(const ee_job* j) {
 // per sweep (2 B per site against the two-pass kernel's 3 B), but the march,
 // with one row per lane between barriers, is bound by its issue rate and
 // latency, and runs slower (96^3, n = 2: 828-890 attempts/ns at 256
-// trajectories against the two-pass kernel's 1650 at 32), so it runs
+// trajectories against the two-pass kernel's 1700 at 32), so it runs
 // only when EE_LAUNCH_MARCH asks for it.  A workgroup marches one segment of
 // one replica of one trajectory, and each segment boundary costs a fix-up
 // pass over two planes; without a segment count in grid_blocks the count
