@@ -9,15 +9,18 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <deque>
 #include <list>
-#include <unordered_map>
+#include <map>
 #include <mutex>
+#include <set>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "ee_internal.hpp"
@@ -339,10 +342,8 @@ int any_whole(ee_job* const* jobs, int count) {
   return 0;
 }
 
-bool same_lattice(const ee_job* a, const ee_job* b) {
-  return a->d.dim == b->d.dim && a->d.lt == b->d.lt && a->d.lx == b->d.lx && a->d.ly == b->d.ly &&
-         a->d.n_replicas == b->d.n_replicas;
-}
+using Lattice = std::array<int, 5>;
+Lattice lattice_of(const ee_job* j) { return {j->d.dim, j->d.lt, j->d.lx, j->d.ly, j->d.n_replicas}; }
 
 int max_traj(ee_job* const* jobs, int count) {
   int n = 0;
@@ -570,17 +571,19 @@ ee_status check_cfg(const ee_launch_cfg* cfg) {
 // lattice's; *lds: the LDS that the largest of them takes); at least one lane
 // per row word of every job.
 int launch_block(ee_job* const* jobs, int count, const ee_launch_cfg& cfg, int* lds) {
-  int block = 64;
+  int block = cfg.block_threads > 0 ? cfg.block_threads : 64;
   *lds = 0;
-  long n_traj = 0;
-  for (int i = 0; i < count; ++i) n_traj += jobs[i]->d.n_traj;
-  for (int i = 0; i < count; ++i) {
-    if (i > 0 && same_lattice(jobs[i], jobs[i - 1])) continue;
-    const Shape sh = launch_shape(jobs[i]->d, jobs[i]->L, n_traj);
-    block = std::max(block, sh.block);
-    *lds = std::max(*lds, sh.k * jobs[i]->L.lds_words * 4);
+  if (cfg.block_threads <= 0) {
+    long n_traj = 0;
+    for (int i = 0; i < count; ++i) n_traj += jobs[i]->d.n_traj;
+    std::set<Lattice> seen;  // the model is evaluated once per lattice
+    for (int i = 0; i < count; ++i) {
+      if (!seen.insert(lattice_of(jobs[i])).second) continue;
+      const Shape sh = launch_shape(jobs[i]->d, jobs[i]->L, n_traj);
+      block = std::max(block, sh.block);
+      *lds = std::max(*lds, sh.k * jobs[i]->L.lds_words * 4);
+    }
   }
-  if (cfg.block_threads > 0) block = cfg.block_threads;
   for (int i = 0; i < count; ++i) block = std::max(block, min_block(jobs[i]->L));
   return block;
 }
@@ -640,23 +643,32 @@ ee_status plan_units(ee_job* const* jobs, int count, int n_therm, const ee_launc
   out->block = launch_block(jobs, count, cfg, &lds_auto);
   const int budget = lds_budget(jobs, count, cfg);
   const bool automatic = cfg.block_threads <= 0 && cfg.lds_bytes <= 0;
-  struct U { ee::Unit u; double cost; };
-  std::vector<U> units;
-  int lds_need = 0;
+  struct Part { int job, k; double cost; };  // the units of a job cost the same
+  std::vector<Part> parts(count);
+  std::map<std::pair<Lattice, int>, int> slots;
+  size_t n_units = 0;
   for (int i = 0; i < count; ++i) {
     ee_job* j = jobs[i];
-    const int k = automatic ? auto_slots(j, out->block, lds_auto)
-                            : choose_slots(j->L, j->d.n_replicas, out->block, budget, j->d.n_traj);
-    lds_need = std::max(lds_need, k * j->L.lds_words * 4);
-    const double cost = unit_cost(j, out->block, k, n_therm);
-    for (int j0 = 0; j0 < j->d.n_traj; j0 += k)
-      units.push_back({ee::Unit{i, j0, std::min(k, j->d.n_traj - j0), k}, cost});
+    int k;
+    if (automatic) {
+      // auto_slots depends on the lattice and on n_traj up to kMaxSlots
+      const auto at = slots.emplace(std::make_pair(lattice_of(j), std::min((int)j->d.n_traj, ee::kMaxSlots)), 0).first;
+      if (at->second == 0) at->second = auto_slots(j, out->block, lds_auto);
+      k = at->second;
+    } else {
+      k = choose_slots(j->L, j->d.n_replicas, out->block, budget, j->d.n_traj);
+    }
+    out->lds = std::max(out->lds, k * j->L.lds_words * 4);
+    parts[i] = Part{i, k, unit_cost(j, out->block, k, n_therm)};
+    n_units += (j->d.n_traj + k - 1) / k;
   }
-  std::stable_sort(units.begin(), units.end(), [](const U& a, const U& b) { return a.cost > b.cost; });
-  out->lds = lds_need;
-  out->units.resize(units.size());
-  for (size_t i = 0; i < units.size(); ++i) out->units[i] = units[i].u;
-  return persistent_grid(any_whole(jobs, count), out->block, out->lds, (int)units.size(), cfg, &out->grid);
+  std::stable_sort(parts.begin(), parts.end(), [](const Part& a, const Part& b) { return a.cost > b.cost; });
+  out->units.reserve(n_units);
+  for (const Part& p : parts) {
+    const int n = jobs[p.job]->d.n_traj;
+    for (int j0 = 0; j0 < n; j0 += p.k) out->units.push_back(ee::Unit{p.job, j0, std::min(p.k, n - j0), p.k});
+  }
+  return persistent_grid(any_whole(jobs, count), out->block, out->lds, (int)n_units, cfg, &out->grid);
 }
 
 ee_status build_plan(ee_job* const* jobs, int count, int n_therm, const ee_launch_cfg& cfg,

@@ -1,7 +1,8 @@
 """The host runtime's launches, with the HIP calls replaced by a recording
 stand-in (csrc/ee_runtime.cpp is included whole): the pieces in which an
 allocation-free batch runs when its chosen shape takes more units than the
-scratch array holds, and the rows per lane of the streaming sweeps."""
+scratch array holds, the rows per lane of the streaming sweeps, and how a batch
+is planned."""
 from __future__ import annotations
 
 import os
@@ -23,12 +24,13 @@ static int fails = 0;
 
 static int g_cus = 256;
 alignas(256) static unsigned char g_scratch[size_t(2) << 20];
+static int n_device_queries;  // one per evaluation of the launch-shape model
 static int n_resets, n_sweeps, n_estimates, fresh;  // fresh: the queue counter was reset since the last sweep
 static std::map<std::pair<int, int>, int> seen;      // (job, trajectory) -> times run
 static std::vector<ee_job*> g_jobs;
 
 extern "C" {
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { ++n_device_queries; *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_cus; return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
   unsigned char* p = (unsigned char*)d;
@@ -124,6 +126,31 @@ int main(int argc, char** argv) {
     CHECK((int)seen.size() == total, "%zu of %d trajectories", seen.size(), total);
     for (const auto& kv : seen) CHECK(kv.second == 1, "trajectory %d of job %d ran %d times", kv.first.second, kv.first.first, kv.second);
     printf("pieces %d fails %d\n", pieces, fails);
+  } else if (argv[1][0] == 'q') {  // plan: block threads, LDS bytes
+    const int lats[4][5] = {{2, 24, 24, 1, 2}, {3, 16, 16, 16, 2}, {2, 64, 34, 1, 3}, {2, 24, 24, 1, 3}};
+    for (int i = 0; i < 60; ++i) {
+      const int* l = lats[i % 4];
+      g_jobs.push_back(make(ee_job_desc{l[0], l[1], l[2], l[3], l[4], 1, 10 + i % 7, 1 + i * i % 97, 0.3, 7, 0, 0}));
+    }
+    const ee_launch_cfg cfg{atoi(argv[3]), atoi(argv[4]), 0, 1, 0};
+    n_device_queries = 0;
+    UnitPlan up;
+    CHECK(plan_units(g_jobs.data(), 60, 5, cfg, &up) == EE_OK, "plan");
+    const int queries = n_device_queries;
+    int next[60] = {0};
+    double last = 1e300;
+    for (size_t i = 0; i < up.units.size(); ++i) {
+      const ee::Unit& u = up.units[i];
+      const double cost = unit_cost(g_jobs[u.job], up.block, u.slots, 5);
+      CHECK(cost <= last, "unit %zu is longer than the one before", i);
+      CHECK(u.j0 == next[u.job], "unit %zu: job %d from %d, not %d", i, u.job, u.j0, next[u.job]);
+      // equal ones in the order of the jobs
+      if (i && cost == last) CHECK(u.job >= up.units[i - 1].job, "unit %zu out of order", i);
+      next[u.job] = u.j0 + u.count;
+      last = cost;
+    }
+    for (int i = 0; i < 60; ++i) CHECK(next[i] == g_jobs[i]->d.n_traj, "job %d ends at %d", i, next[i]);
+    printf("queries %d fails %d\n", queries, fails);
   } else {  // rows per lane: dim lt lx ly n n_traj
     ee_job* j = make(ee_job_desc{atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]), atoi(argv[7]), 1, 1, atoi(argv[8]),
                                  0.3, 7, 0, 0});
@@ -174,3 +201,11 @@ def test_rows_per_lane_of_streamed_jobs(runtime, lattice, per_traj, cus):
     n = 4 * cus * 1024 // per_traj
     assert runtime("rows", cus, *lattice, n) == 1
     assert runtime("rows", cus, *lattice, n + 1) == 2
+
+
+# four lattices, interleaved: the model is evaluated once for each where it
+# gives the block size, and not at all where the caller does; one more query is
+# the grid's
+@pytest.mark.parametrize("cfg,evaluations", [((0, 0), 4), ((0, 8192), 4), ((256, 0), 0), ((256, 8192), 0)], ids=str)
+def test_plan_of_an_uneven_batch(runtime, cfg, evaluations):
+    assert runtime("query", 256, *cfg) == evaluations + 1
