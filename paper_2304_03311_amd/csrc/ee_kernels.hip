@@ -71,15 +71,15 @@ __device__ __forceinline__ bool stream_lane(const ee::StreamArgs& a, int W, uint
 // 150 instead of 190 instructions a row but read every other row: 4.9 against
 // 3.7 ms on 96^3 and 9.2 against 7.1 ms on the cylinder below, though 5.3
 // against 5.5 ms on 48^3.)  Bound by memory on large jobs: 3D 96^3 x 32
-// trajectories 16.6 us a launch, 5.1 TB/s on its 3 B per attempt, as fast as a
+// trajectories 17.0 us a launch, 5.0 TB/s on its 3 B per attempt, as fast as a
 // large copy.  What is the same for every lane comes by value in the
 // arguments, with the multipliers of its divisions, and the lanes have no
 // barrier; made from the job's description in memory, behind one dependent
 // load after the other, it was a fifth of the time and kept small jobs at four
 // rows per lane: 96^3 x 32, 110 sweeps 4.05 -> 3.75 ms, 48^3 x 16, 600 sweeps
 // 7.72 -> 5.52 ms, the 2D L = 128 cylinder x 256, 200 sweeps 7.95 -> 7.12 ms.
-// Each colour plane has a base of its own (a trajectory may pass 4 GiB), which
-// also spares every access an addition: 3.65, 5.47 and 7.06 ms.
+// Each colour plane has a base of its own, since a trajectory may pass 4 GiB:
+// 3.73, 5.24 and 7.09 ms, 2D 1760 x 220 x 20, 158 sweeps 3.42 -> 3.36 ms.
 template <int DIM, bool FULL, int W>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 stream_row_kernel(ee::StreamArgs a, int c, uint32_t g, int pos, int dpos, int work) {
@@ -87,8 +87,8 @@ stream_row_kernel(ee::StreamArgs a, int c, uint32_t g, int pos, int dpos, int wo
   uint32_t j;
   int slot, w;
   if (!stream_lane(a, W, j, slot, w)) return;
-  uint32_t* const traj = P.spins + (size_t)j * P.traj_words;
-  const HbmMem own{traj + plane_start(P, c)}, oth{traj + plane_start(P, c ^ 1)};
+  uint32_t* const traj = P.spins + (uint64_t)j * (uint32_t)P.traj_words;
+  const HbmMem own{traj + plane_start(a.rows, P.G, c)}, oth{traj + plane_start(a.rows, P.G, c ^ 1)};
   PhKey K;
   key_unit(K, P);
   key_sweep(K, P, g, j);
@@ -106,7 +106,10 @@ stream_row_kernel(ee::StreamArgs a, int c, uint32_t g, int pos, int dpos, int wo
     const uint32_t c0 = (uint32_t)(rho * P.G8 + (w >> 1));
     const uint32_t c3 = (1u << 28) | ((uint32_t)r << 1) | (uint32_t)c;
     K.x0 = c3 ^ P.key1;
-    const uint32_t off = plane_byte(m * G + w);
+    // opaque to the compiler (the empty asm statement emits nothing): it would
+    // carry an induction variable per access, some 30 instructions more
+    uint32_t off = plane_byte(m * G + w);
+    asm volatile("" : "+v"(off));
     const auto row = [&](auto cut) {
       constexpr bool CUT = decltype(cut)::value;
       const int tmo = -LyG + ((CUT && t == 0) ? ltLyG : 0);
@@ -304,7 +307,7 @@ __device__ __forceinline__ void march_colour(const JP& P, PhKey& K, uint32_t* wi
                                              uint32_t j, int pos, int dpos, bool work, int& dI, const RowDesc& d0) {
   const int G = P.G, GW = G / W, ly = P.ly;
   const LdsMem mem;
-  const HbmMem hbm{traj + plane_start(P, 1)};  // the glued partners' plane
+  const HbmMem hbm{traj + plane_start(P.n * P.R, G, 1)};  // the glued partners' plane
   const uint32_t ring = lds_address(win);
   const uint32_t own = ring + 4u * (uint32_t)(s0 * PW + c * ly * G);
   const uint32_t oth = ring + 4u * (uint32_t)(s0 * PW + (c ^ 1) * ly * G);
@@ -403,7 +406,7 @@ __device__ __forceinline__ void fixup_plane(const JP& P, const uint32_t* thr, in
   const uint32_t j = (uint32_t)jj;
   uint32_t* traj = P.spins + (size_t)j * P.traj_words;
   const int G = P.G, GW = G / W, ly = P.ly, R = P.R;
-  const HbmMem own{traj + plane_start(P, 1)}, oth{traj};
+  const HbmMem own{traj + plane_start(P.n * R, G, 1)}, oth{traj};
   PhKey K;
   key_unit(K, P);
   key_sweep(K, P, g, j);

@@ -34,11 +34,12 @@ struct JP {
 
 
 // Where a trajectory's words lie in device memory: the word at which its
-// colour plane c starts, in 64 bits, and within a plane a 32-bit byte offset.
-// A trajectory has fewer than 2^31 words (int indices) and a plane fewer than
-// 2^30, so such an offset reaches every word of a plane; counted from the
-// start of the trajectory it would wrap in one of more than 4 GiB.
-EE_HDI uint64_t plane_start(const JP& P, int c) { return c ? (uint64_t)(P.n * P.R) * (uint64_t)P.G : 0; }
+// colour plane c (rows of G words) starts, to be added to a 64-bit pointer,
+// and within a plane a 32-bit byte offset.  A trajectory has fewer than 2^31
+// words (int indices) and a plane fewer than 2^30, so such an offset reaches
+// every word of a plane; counted from the start of the trajectory it would
+// wrap in one of more than 4 GiB.
+EE_HDI uint32_t plane_start(int rows, int G, int c) { return c ? (uint32_t)rows * (uint32_t)G : 0u; }
 EE_HDI uint32_t plane_byte(int word) { return 4u * (uint32_t)word; }
 
 // Per-lane iteration state of one work unit (the same for every sweep): the

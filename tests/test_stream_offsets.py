@@ -36,7 +36,7 @@ int main(int argc, char** argv) {
         const u64 row = (near + rows + d) % rows;
         for (int w : {0, P.G - 1}) {
           const uint32_t off = plane_byte((int)(row * P.G) + w);
-          if (4 * plane_start(P, c) + off != 4 * (c * plane + row * P.G + w)) ++fails;
+          if (4 * (u64)plane_start(P.n * P.R, P.G, c) + off != 4 * (c * plane + row * P.G + w)) ++fails;
           // neighbour rows of the same replica: offsets of either sign, modulo 2^32
           const int r = (int)(row / P.R), t = (int)(row % P.R) / P.ly, y = (int)(row % P.R) % P.ly;
           const int LyG = P.ly * P.G, tpo = LyG - ((t == P.lt - 1) ? P.lt * LyG : 0), tmo = -LyG + ((t == 0) ? P.lt * LyG : 0);
