@@ -419,7 +419,7 @@ int march_block(const ee_job* j) {
 // per sweep (2 B per site against the two-pass kernel's 3 B), but the march,
 // with one row per lane between barriers, is bound by its issue rate and
 // latency, and runs slower (96^3, n = 2: 828-890 attempts/ns at 256
-// trajectories against the two-pass kernel's 1700 at 32), so it runs
+// trajectories against the two-pass kernel's 1670 at 32), so it runs
 // only when EE_LAUNCH_MARCH asks for it.  A workgroup marches one segment of
 // one replica of one trajectory, and each segment boundary costs a fix-up
 // pass over two planes; without a segment count in grid_blocks the count
@@ -458,11 +458,10 @@ int stream_words(const ee_job* j) {
 
 // Arguments of the streaming launches.  A lane takes two rows where that
 // leaves eight waves per SIMD over the GPU, else one: 3D 96^3 x 32 (13.5 waves
-// per SIMD at two rows) at 1, 2, 4 and 8 rows per lane 4.19, 3.67, 3.55 and
-// 3.86 ms, the 2D L = 128 cylinder x 256 (16) 7.90, 7.06, 7.26 and 7.47 ms, 3D
-// 48^3 x 16 (1.7; 3.4 at one row) 5.52, 5.95, 6.98 and 8.99 ms.  More rows per
-// lane only where the grid
-// would pass the 2^32 - 1 lanes of a launch.
+// per SIMD at two rows) at 1, 2, 4 and 8 rows per lane 4.14, 3.74, 3.80 and
+// 4.15 ms, the 2D L = 128 cylinder x 256 (16) 7.94, 7.09, 7.33 and 7.54 ms, 3D
+// 48^3 x 16 (1.7; 3.4 at one row) 5.24, 5.80, 6.70 and 8.41 ms.  More rows per
+// lane only where the grid would pass the 2^32 - 1 lanes of a launch.
 ee::StreamArgs stream_args(const ee_job* j) {
   ee::StreamArgs a{};
   const ee::JobDev& D = j->host_jobdev;
