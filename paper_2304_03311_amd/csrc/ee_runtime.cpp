@@ -199,21 +199,30 @@ constexpr int kDefaultLdsBudget = 80 * 1024;  // two workgroups per CU
 // 80 KB hold) ran 16384 trajectories of 2D 64 x 32 at ten trajectories of six
 // lanes in a wave, two waves per CU: 13.7 ms of sweeps with these kernels, now
 // 5.2; the 2D 256 x 32 cylinder, 32 jobs x 256: 27.4 ms, now 23.2.
+//
+// Up to one trajectory per CU no two workgroups share a CU, and the chain of
+// a half-sweep decides more than what it issues (half_sweep_cycles).
 // ---------------------------------------------------------------------------
 Rows rows_of(const ee_job_desc& d, const Layout& L) {
   Rows r{};
-  r.P.dim = d.dim; r.P.n = d.n_replicas; r.P.ly = d.ly; r.P.lt = d.lt;
+  r.P.dim = d.dim; r.P.n = d.n_replicas; r.P.ly = d.ly; r.P.lt = d.lt; r.P.l = d.l;
+  r.P.whole = (d.flags & EE_FLAG_WHOLE) ? 1 : 0;
   r.P.H = L.H; r.P.G = L.G; r.P.R = L.R;
   r.rag_W = L.rag_W;
   r.rag_pitch = L.rag_pitch;
   return r;
 }
 
-// Instructions per wave of one half-sweep of a trajectory on T lanes.
-double half_sweep_instr(const Rows& rows, int T) {
+// The path of a half-sweep of a trajectory on T lanes: W words per lane, GW
+// lanes per row, and its steps: pairs of rows in parity-major order (pm), else
+// rows in lane-map order.
+struct Path {
+  bool pm;
+  int W, GW, steps;
+};
+Path path_of(const Rows& rows, int T) {
   const ee::lanes::JP& P = rows.P;
   int W = ee::lanes::words_per_lane(P, T);
-  const double y = (P.dim == 3) ? 20.0 : 0.0;  // the two more neighbours
   int lanes = (P.H & 3) == 0 ? ee::lanes::pm_lanes(P, T, W) : 0;
   int GW = P.G / W;
   if (rows.rag_pitch > 0) {
@@ -227,16 +236,53 @@ double half_sweep_instr(const Rows& rows, int T) {
   }
   if (lanes) {
     const int B = lanes / GW / P.n;
-    const int steps = (P.R / 2 + B - 1) / B;
-    const double step = ee::lanes::step_instr(W) + y;
-    // the sweep loop, and the rows next to the cut in the waves that have them
-    const double waves = (T + 63) / 64, cut = P.n * ((P.ly * GW + 63) / 64);
-    return steps * step + 50.0 + 90.0 * std::min(1.0, cut / waves);
+    return Path{true, W, GW, (P.R / 2 + B - 1) / B};
   }
   const int slots = T / GW;
-  const int passes = (slots >= P.n) ? (P.R + slots / P.n - 1) / (slots / P.n) : (P.n * P.R + slots - 1) / slots;
-  const double row = (W == 4 ? 190.0 : W == 3 ? 165.0 : W == 2 ? 120.0 : 100.0) + y;
-  return passes * row + 90.0;
+  return Path{false, W, GW,
+              (slots >= P.n) ? (P.R + slots / P.n - 1) / (slots / P.n) : (P.n * P.R + slots - 1) / slots};
+}
+int row_instr(int W) { return W == 4 ? 190 : W == 3 ? 165 : W == 2 ? 120 : 100; }  // of a row in lane-map order
+
+// Instructions per wave of one half-sweep of a trajectory on T lanes.
+double half_sweep_instr(const Rows& rows, int T) {
+  const ee::lanes::JP& P = rows.P;
+  const double y = (P.dim == 3) ? 20.0 : 0.0;  // the two more neighbours
+  const Path p = path_of(rows, T);
+  if (!p.pm) return p.steps * (row_instr(p.W) + y) + 90.0;
+  // the sweep loop, and the rows next to the cut in the waves that have them
+  const double waves = (T + 63) / 64, cut = P.n * ((P.ly * p.GW + 63) / 64);
+  return p.steps * (ee::lanes::step_instr(p.W) + y) + 50.0 + 90.0 * std::min(1.0, cut / waves);
+}
+
+// Cycles of one half-sweep of a trajectory that has a CU to itself, on T lanes:
+// the latency of its chain (the steps, one after the other; a lane's only row
+// has its random numbers a half-sweep ahead), and 2.5 more for each instruction
+// and wave per SIMD.  With the whole-region protocol a lane also decides the
+// sites of its ramped words one after the other.
+//
+// A fit to 6200 shapes of 550 random jobs of up to 256 trajectories: 11% rms,
+// and the shape it picks is 2.3% slower than the best one on average.  By
+// instructions alone the time was 33% off and the shape 11% slower (the
+// whole-region protocol up to twice): 2D 22 x 60, three replicas, one
+// trajectory 193 instead of 142 us, 2D 96 x 52 whole-region, 36 trajectories
+// 365 instead of 251.
+double half_sweep_cycles(const Rows& rows, int T) {
+  const ee::lanes::JP& P = rows.P;
+  const int y = (P.dim == 3) ? 1 : 0;
+  const Path p = path_of(rows, T);
+  const int W = p.W;
+  const int ramped = P.whole ? std::min(W, (P.l + 7) / 8) : 0;
+  const double per_simd = T / 256.0;
+  if (p.pm) {
+    const double step = W == 4 ? 1550.0 : W == 3 ? 1300.0 : W == 2 ? 800.0 : 650.0;
+    const double cut = W == 4 ? 5600.0 : W == 3 ? 4300.0 : W == 2 ? 2000.0 : 900.0;  // all W words ramped
+    return p.steps * (step + 90.0 * y) + 900.0 + cut * ramped / W +
+           2.5 * per_simd * p.steps * (ee::lanes::step_instr(W) + 20.0 * y);
+  }
+  const double ahead = W == 4 ? 2150.0 : W == 3 ? 1850.0 : W == 2 ? 1700.0 : 1500.0;
+  const double chain = p.steps == 1 ? ahead + 90.0 * y : p.steps * (7.0 * row_instr(W) + 90.0 * y) + 1050.0;
+  return chain + 400.0 * ramped + 2.5 * per_simd * p.steps * (row_instr(W) + 20.0 * y);
 }
 
 struct Shape {
@@ -254,6 +300,11 @@ Shape launch_shape(const ee_job_desc& d, const Layout& L, long n_traj) {
   const auto consider = [&](int block, int k) {
     const int T = block / k;
     if (T < L.G || k * (long)tb > ee_k_max_lds_bytes()) return;
+    if (n_traj <= cus) {
+      const double cost = half_sweep_cycles(rows, T);
+      if (k == 1 && cost < best.cost) best = Shape{block, k, cost};
+      return;
+    }
     const int waves = block / 64;
     const long units = (n_traj + k - 1) / k;
     const int fit = std::max(1, std::min(160 * 1024 / (k * tb + 256), 16 / waves));  // workgroups per CU

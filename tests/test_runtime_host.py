@@ -151,6 +151,12 @@ int main(int argc, char** argv) {
     }
     for (int i = 0; i < 60; ++i) CHECK(next[i] == g_jobs[i]->d.n_traj, "job %d ends at %d", i, next[i]);
     printf("queries %d fails %d\n", queries, fails);
+  } else if (argv[1][0] == 's') {  // shape: dim lt lx ly n l n_traj flags
+    ee_job* j = make(ee_job_desc{atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]), atoi(argv[7]), atoi(argv[8]), 1,
+                                 atoi(argv[9]), 0.3, 7, 0, (uint32_t)atoi(argv[10])});
+    const Shape s = launch_shape(j->d, j->L, j->d.n_traj);
+    CHECK(s.k == 1, "%d trajectories per workgroup", s.k);
+    printf("block %d fails %d\n", s.block, fails);
   } else {  // rows per lane: dim lt lx ly n n_traj
     ee_job* j = make(ee_job_desc{atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]), atoi(argv[7]), 1, 1, atoi(argv[8]),
                                  0.3, 7, 0, 0});
@@ -209,3 +215,47 @@ def test_rows_per_lane_of_streamed_jobs(runtime, lattice, per_traj, cus):
 @pytest.mark.parametrize("cfg,evaluations", [((0, 0), 4), ((0, 8192), 4), ((256, 0), 0), ((256, 8192), 0)], ids=str)
 def test_plan_of_an_uneven_batch(runtime, cfg, evaluations):
     assert runtime("query", 256, *cfg) == evaluations + 1
+
+
+# Microseconds per half-sweep of jobs of few trajectories over the workgroup
+# sizes, one trajectory each, as measured on 256 CUs: (dim, lt, lx, ly, n,
+# trajectories, l, whole-region), {threads: us}.  The runtime's own choice is
+# within a quarter of the best (twice the scatter of its model).
+MEASURED = [
+    ((2, 116, 28, 1, 2, 1, 23, 0),
+     {64: 1.73, 128: 1.16, 192: 1.13, 256: 1.73, 320: 1.71, 384: 1.71, 448: 1.38, 512: 1.44, 576: 1.22, 640: 1.22,
+      704: 1.24, 768: 1.2, 832: 1.26, 896: 1.26, 960: 1.03}),
+    ((3, 14, 20, 10, 3, 30, 18, 1),
+     {64: 5.15, 128: 3.65, 192: 4.53, 256: 3.61, 320: 3.48, 384: 3.48, 448: 2.23, 512: 2.22, 576: 2.33, 640: 2.1,
+      704: 2.25, 768: 2.25, 832: 2.26, 896: 1.94, 960: 1.94, 1024: 1.91}),
+    ((2, 56, 28, 1, 3, 1, 25, 0),
+     {64: 1.7, 128: 1.12, 192: 1.71, 256: 1.41, 320: 1.41, 384: 1.45, 448: 1.44, 512: 1.31, 576: 1.21, 640: 1.2,
+      704: 0.91}),
+    ((2, 22, 118, 1, 2, 100, 79, 0),
+     {64: 1.8, 128: 1.2, 192: 1.72, 256: 1.46, 320: 1.42, 384: 1.35, 448: 1.41, 512: 1.48, 576: 1.38, 640: 1.51,
+      704: 0.93}),
+    ((2, 28, 68, 1, 2, 30, 43, 1),
+     {64: 2.52, 128: 2.4, 192: 1.96, 256: 1.95, 320: 1.33, 384: 1.34, 448: 1.34, 512: 0.95}),
+    ((3, 26, 32, 18, 2, 30, 22, 1),
+     {64: 11.11, 128: 5.85, 192: 4.25, 256: 3.68, 320: 3.56, 384: 3.72, 448: 3.57, 512: 3.81, 576: 3.65, 640: 3.68,
+      704: 3.18, 768: 3.19, 832: 3.14, 896: 3.17, 960: 2.58, 1024: 2.65}),
+    ((2, 78, 54, 1, 3, 4, 36, 1),
+     {64: 5.21, 128: 4.28, 192: 4.81, 256: 4.02, 320: 3.93, 384: 4.31, 448: 4.65, 512: 2.21, 576: 2.41, 640: 2.4,
+      704: 2.5, 768: 2.59, 832: 2.41, 896: 2.35, 960: 2.22, 1024: 2.08}),
+    ((2, 68, 38, 1, 2, 1, 28, 1),
+     {64: 2.61, 128: 2.04, 192: 2.02, 256: 1.65, 320: 1.6, 384: 1.6, 448: 1.58, 512: 1.55, 576: 1.37, 640: 1.38,
+      704: 0.97}),
+    ((2, 106, 84, 1, 2, 4, 61, 1),
+     {64: 6.59, 128: 4.9, 192: 4.14, 256: 4.04, 320: 3.47, 384: 3.48, 448: 3.45, 512: 4.45, 576: 4.09, 640: 2.96,
+      704: 2.38, 768: 2.25, 832: 2.38, 896: 2.39, 960: 2.26, 1024: 2.37}),
+    ((3, 10, 20, 8, 3, 1, 9, 0),
+     {64: 2.35, 128: 1.09, 192: 1.15, 256: 1.54, 320: 1.85, 384: 1.62, 448: 1.62, 512: 1.62, 576: 1.36, 640: 1.79,
+      704: 2.11, 768: 1.15}),
+]
+
+
+@pytest.mark.parametrize("job,us", MEASURED, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_shape_of_few_trajectories(runtime, job, us):
+    dim, lt, lx, ly, n, n_traj, l, whole = job
+    block = runtime("shape", 256, dim, lt, lx, ly, n, l, n_traj, 4 if whole else 0)
+    assert us[block] <= 1.25 * min(us.values()), (block, us)
